@@ -16,15 +16,23 @@
 //   * X (.) g enters the matrix cores as two operands, hi + lo, at every M: the kernel that ran these
 //     sizes before kept the product in fp32.  hi is the product cut off (not rounded) one fp32 ulp below its
 //     value, lo what is left: both have the product's sign and neither is zero unless the product is, so
-//     that an infinite W gives what it gives in fp32, and together they are the product exactly (bf16: 8 + 8
-//     bits; fp16: 11 + 11).  fp16 has no range to spare, so the first kernel also scales every row of X by
-//     the power of two that puts its largest product with g below 2^15, and leaves the row's
-//     factor 1 / rms, with that power taken out, for the epilogue.
+//     that an infinite W gives what it gives in fp32.  In bf16 they are the product exactly (8 + 8 bits).
+//     fp16 (11 + 11 bits) has no range to spare (products reach from 2^-48 to 2^32, operands from 2^-24 to
+//     2^16), so a wave multiplies its rows' fp32 products by a power of two, and its sums by the inverse at the end.
+//     The power puts the largest product of the wave's first 64 k between 2^3 and 2^4; the wave keeps track of the largest
+//     of all, and where that one ends up outside 2^3 to 2^15 it goes over its runs once more with the power
+//     that the row's products call for.  What is left out of a product is below 2^-24, scaled: less than the rounding of
+//     the fp32 sums.  (A power found in a first kernel from the largest |x| times the largest |g| of a
+//     row, and applied to X in fp16, cost what x lost as a subnormal: 6e-3 of the row's rms for a large
+//     gain on a small x beside a large x on a small gain.  Sums that are scaled down whenever a larger product comes need
+//     no second pass, but registers for it in every step: 136 of them spilled at 64 rows.)
 //
-// Bound by streaming W, like the skinny kernel.  24 x 4096 x 32003: bf16 50 us (264 MB, 5.2 TB/s), fp16 with its
-// first kernel 57 us; the plain kernel that ran these sizes before takes 2460 us.  Large M is bound by every row
+// Bound by streaming W, like the skinny kernel.  24 x 4096 x 32003: bf16 50 us (264 MB, 5.2 TB/s), fp16 51 us (54 with
+// the first kernel it had; but 256 x 4095 x 4099, where the vector instructions count, 59 us against 52);
+// the plain kernel that ran these sizes before takes 2460 us.  Large M is bound by every row
 // block's own copy of W out of L2: 2048 x 4096 x 4099 272 us (253 TFLOP/s).
 #include <algorithm>
+#include <type_traits>
 #include "common.hpp"
 #include "splitk.hpp"
 
@@ -68,76 +76,15 @@ template <> struct TwoPart<Fp16> {
 };
 
 // ------------------------------------------------------------------------------------ first kernel
-// One workgroup per row of X: the row, times 2^r for fp16, to Xp [M][Kp] with zeros from K on, and
-// rfac = 2^-r / rms.  Workgroup M: g to gp [Kp], likewise.  Bound by latency (a few rows): 1024 threads,
-// with the first 8192 elements of a row in registers between the two sweeps.
-constexpr int kRowThreads = 1024, kRowPer = 8;
-template <typename T>
+// K % 8 != 0.  One workgroup per row of X: the row to Xp [M][Kp], with zeros from K on.  Workgroup M: g to gp [Kp].
+constexpr int kRowThreads = 1024;
 __global__ __launch_bounds__(kRowThreads) void odd_rows_kernel(const u16* __restrict__ X, const u16* __restrict__ g,
-                                                       u16* __restrict__ Xp, u16* __restrict__ gp, float* __restrict__ rfac,
-                                                       int M, int K, int Kp, float eps, float inv_K)
+                                                               u16* __restrict__ Xp, u16* __restrict__ gp, int M, int K, int Kp)
 {
-    __shared__ float part[3][kRowThreads / 64];
-    if (int(blockIdx.x) == M) {
-        for (int k = threadIdx.x; k < Kp; k += kRowThreads) gp[k] = k < K ? g[k] : u16(0);
-        return;
-    }
-    const u16* x = X + size_t(blockIdx.x) * K;
-    u16* xp = Xp + size_t(blockIdx.x) * Kp;
-    constexpr bool kScale = __is_same(T, Fp16);
-    float ss = 0.f, xmax = 0.f, gmax = 0.f;
-    u16 xv[kRowPer], gv[kRowPer];
-#pragma unroll
-    for (int j = 0; j < kRowPer; ++j) {
-        const int k = threadIdx.x + j * kRowThreads;
-        xv[j] = k < K ? x[k] : u16(0);
-        gv[j] = kScale && k < K ? g[k] : u16(0);
-    }
-    auto take = [&](u16 xe, u16 ge) {
-        const float v = Elem<T>::to_f32(xe);
-        ss = __fmaf_rn(v, v, ss);
-        if (kScale) {
-            xmax = fmaxf(xmax, fabsf(v));
-            gmax = fmaxf(gmax, fabsf(Elem<T>::to_f32(ge)));
-        }
-    };
-#pragma unroll
-    for (int j = 0; j < kRowPer; ++j) take(xv[j], gv[j]);
-    for (int k = threadIdx.x + kRowPer * kRowThreads; k < K; k += kRowThreads) take(x[k], kScale ? g[k] : u16(0));
-    ss = wave_sum(ss);
-    if (kScale)
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            xmax = fmaxf(xmax, __shfl_xor(xmax, off, 64));
-            gmax = fmaxf(gmax, __shfl_xor(gmax, off, 64));
-        }
-    if ((threadIdx.x & 63) == 0) { part[0][threadIdx.x >> 6] = ss; part[1][threadIdx.x >> 6] = xmax; part[2][threadIdx.x >> 6] = gmax; }
-    __syncthreads();
-    ss = 0.f;
-#pragma unroll
-    for (int v = 0; v < kRowThreads / 64; ++v) {
-        ss += part[0][v];
-        xmax = fmaxf(xmax, part[1][v]);
-        gmax = fmaxf(gmax, part[2][v]);
-    }
-    int r = 0;
-    if (kScale) {
-        if (xmax > 0.f && xmax <= 65504.f) {             // (a zero row, or one with an infinity, stays as it is)
-            // largest x in [2^e, 2^(e+1)), largest g below 2^t: x 2^(14 - t - e) g stays below 2^15
-            const int e = int(__float_as_uint(xmax) >> 23) - 127;
-            const int t = gmax <= 65504.f ? max(0, int(__float_as_uint(gmax) >> 23) - 126) : 0;
-            r = 14 - t - e;
-        }
-    }
-    const float up = __uint_as_float(uint32_t(127 + r) << 23);
-    auto scaled = [&](u16 xe) { return kScale ? Elem<T>::from_f32(Elem<T>::to_f32(xe) * up) : xe; };
-#pragma unroll
-    for (int j = 0; j < kRowPer; ++j) {
-        const int k = threadIdx.x + j * kRowThreads;
-        if (k < Kp) xp[k] = scaled(xv[j]);               // (zero from K on)
-    }
-    for (int k = threadIdx.x + kRowPer * kRowThreads; k < Kp; k += kRowThreads) xp[k] = k < K ? scaled(x[k]) : u16(0);
-    if (threadIdx.x == 0) rfac[blockIdx.x] = row_scale(ss, inv_K, eps) * __uint_as_float(uint32_t(127 - r) << 23);
+    const bool gain = int(blockIdx.x) == M;
+    const u16* src = gain ? g : X + size_t(blockIdx.x) * K;
+    u16* dst = gain ? gp : Xp + size_t(blockIdx.x) * Kp;
+    for (int k = threadIdx.x; k < Kp; k += kRowThreads) dst[k] = k < K ? src[k] : u16(0);
 }
 
 // ------------------------------------------------------------------------------------- the product
@@ -146,11 +93,9 @@ struct OddCold {                             // what the first loads do not need
     float eps, inv_K;
     int ldp;                                 // row length of the partial tiles: N rounded up to a multiple of 4
     float* ws_partial; float* ws_sumsq; unsigned* counter;
-    const float* rfac;
 };
 
-// PRE: X and g are the first kernel's copies, rows Kx long, and the row factors are in rfac; otherwise X
-// and g are the caller's (Kx = K, a multiple of 8) and the squares are summed here, as in the skinny kernel.
+// PRE: X and g are the first kernel's copies, rows Kx long; otherwise the caller's (Kx = K, a multiple of 8).
 template <typename T, int MB, bool ODDN, bool PRE>
 __global__ __launch_bounds__(64 * kOddWaves) void odd_kernel(
     const u16* W, const u16* X, const u16* g, int M, int K, int Kx, int N, int S, int n_tiles, int RB, OddCold a)
@@ -234,42 +179,37 @@ __global__ __launch_bounds__(64 * kOddWaves) void odd_kernel(
                 wrs, int(woff0 + unsigned(__builtin_amdgcn_readfirstlane(int(unsigned(t) * unsigned(wpair) + unsigned((8 * h + j) * wrow) -
                                                                              (ODDN && (j & 1) ? 2u : 0u))))), 0, 2);
     };
-    // every load is issued whether or not its step exists, in this order: the waits count on it
-    __builtin_amdgcn_sched_barrier(0);
-    issue_w(0, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    issue_x(0);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int d = 1; d < D; ++d) {
-        issue_w(d, d);
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    asm volatile("" ::: "memory");
-
     float4_t acc[MB][8];
     float ss[MB];
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-        ss[mb] = 0.f;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) acc[mb][c] = float4_t{0.f, 0.f, 0.f, 0.f};
-    }
+    constexpr bool kScale = std::is_same<T, Fp16>::value;
+    float top[MB], up[MB];                   // fp16: row i's largest product so far, and what its products are multiplied by
+    // the power of two that puts v between 2^e and 2^(e + 1); v: a row's largest product, lanes i + 16 q
+    auto power = [&](float v, int e) {
+        v = fmaxf(v, __shfl_xor(v, 16, 64));
+        v = fmaxf(v, __shfl_xor(v, 32, 64));
+        return v > 0.f && v <= 3.0e38f ? __uint_as_float(uint32_t(254 + e) * 0x00800000u - (__float_as_uint(v) & 0x7f800000u)) : 64.f;
+    };
     auto consume = [&](int d, int t, int h, const char* stg) {
         uint4_t ahi[MB], alo[MB];
         const uint4_t gq = *reinterpret_cast<const uint4_t*>(stg + st_g + ((2 * q + h) << 4));
+        // (the sum with +0 turns -0 into +0)
+        auto product = [&](const uint4_t& x, int e, int half) {
+            return half ? __fmaf_rn(Elem<T>::hi(x[e]), Elem<T>::hi(gq[e]), 0.f) : __fmaf_rn(Elem<T>::lo(x[e]), Elem<T>::lo(gq[e]), 0.f);
+        };
+        uint4_t xq[MB];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) xq[mb] = *reinterpret_cast<const uint4_t*>(stg + ((st_r0 ^ (h << 4)) + 2048 * mb));
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
-            const uint4_t xq = *reinterpret_cast<const uint4_t*>(stg + ((st_r0 ^ (h << 4)) + 2048 * mb));
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const float x0 = Elem<T>::lo(xq[e]), x1 = Elem<T>::hi(xq[e]);
-                if (!PRE) {
-                    ss[mb] = __fmaf_rn(x0, x0, ss[mb]);
-                    ss[mb] = __fmaf_rn(x1, x1, ss[mb]);
-                }
-                uint32_t hi, lo;             // (the sum with +0 turns -0 into +0)
-                TwoPart<T>::split(__fmaf_rn(x0, Elem<T>::lo(gq[e]), 0.f), __fmaf_rn(x1, Elem<T>::hi(gq[e]), 0.f), &hi, &lo);
+                const float x0 = Elem<T>::lo(xq[mb][e]), x1 = Elem<T>::hi(xq[mb][e]);
+                ss[mb] = __fmaf_rn(x0, x0, ss[mb]);
+                ss[mb] = __fmaf_rn(x1, x1, ss[mb]);
+                uint32_t hi, lo;
+                const float p0 = product(xq[mb], e, 0), p1 = product(xq[mb], e, 1);
+                if (kScale) top[mb] = fmaxf(fmaxf(top[mb], fabsf(p0)), fabsf(p1));
+                TwoPart<T>::split(kScale ? p0 * up[mb] : p0, kScale ? p1 * up[mb] : p1, &hi, &lo);
                 ahi[mb][e] = hi; alo[mb][e] = lo;
             }
         }
@@ -305,41 +245,96 @@ __global__ __launch_bounds__(64 * kOddWaves) void odd_kernel(
     };
 
     constexpr int PU = (D % 2 == 0) ? D / 2 : D;    // runs per trip: ring slots repeat every 2 PU steps
-    for (int t0 = 0; t0 < nPairs; t0 += PU) {
+    for (int pass = 0;; ++pass) {
+        // every load is issued whether or not its step exists, in this order: the waits count on it
+        __builtin_amdgcn_sched_barrier(0);
+        issue_w(0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        issue_x(0);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int p = 0; p < PU; ++p) {
-            const int t = t0 + p;
-            const bool there = t < nPairs;   // uniform over the wave; only the arithmetic is skipped
-            const char* stg = stage + (t & 1) * STG;
-            // this run's X was asked for a run ago; the 16 loads of W issued since are younger
+        for (int d = 1; d < D; ++d) {
+            issue_w(d, d);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        asm volatile("" ::: "memory");
+
+        if (kScale && pass == 0) {               // X of the first run is there once only the 16 youngest loads of W are not
             __builtin_amdgcn_s_waitcnt((16 & 15) | ((16 >> 4) << 14) | (7 << 4) | (15 << 8));
             asm volatile("" ::: "memory");
-            __builtin_amdgcn_sched_barrier(0);
-            issue_x(t + 1);
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                if (there) consume((2 * p + h) % D, t, h, stg);
-                __builtin_amdgcn_sched_barrier(0);
-                issue_w(2 * t + h + D, (2 * p + h) % D);
-                asm volatile("" ::: "memory");
-                __builtin_amdgcn_sched_barrier(0);
+            for (int mb = 0; mb < MB; ++mb) {
+                float v = 0.f;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const uint4_t gq = *reinterpret_cast<const uint4_t*>(stage + st_g + ((2 * q + h) << 4));
+                    const uint4_t xq = *reinterpret_cast<const uint4_t*>(stage + ((st_r0 ^ (h << 4)) + 2048 * mb));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        v = fmaxf(v, fmaxf(fabsf(Elem<T>::lo(xq[e]) * Elem<T>::lo(gq[e])), fabsf(Elem<T>::hi(xq[e]) * Elem<T>::hi(gq[e]))));
+                }
+                up[mb] = nPairs > 0 ? power(v, 3) : 64.f;
             }
         }
-    }
-    // loads for the run past the end still write into the stage buffers, which the reduction buffer covers
-    __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8));
-    asm volatile("" ::: "memory");
-
-    if (!PRE) {                              // lanes i, i + 16, i + 32, i + 48 hold row i's shares
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
-            float v = ss[mb];
-            v += __shfl_xor(v, 16, 64);
-            v += __shfl_xor(v, 32, 64);
-            if (q == 0) s_sumsq[wave][mb * 16 + i] = v;
+            ss[mb] = top[mb] = 0.f;
+#pragma unroll
+            for (int c = 0; c < 8; ++c) acc[mb][c] = float4_t{0.f, 0.f, 0.f, 0.f};
         }
+        for (int t0 = 0; t0 < nPairs; t0 += PU) {
+#pragma unroll
+            for (int p = 0; p < PU; ++p) {
+                const int t = t0 + p;
+                const bool there = t < nPairs;   // uniform over the wave; only the arithmetic is skipped
+                const char* stg = stage + (t & 1) * STG;
+                // this run's X was asked for a run ago; the 16 loads of W issued since are younger
+                __builtin_amdgcn_s_waitcnt((16 & 15) | ((16 >> 4) << 14) | (7 << 4) | (15 << 8));
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_sched_barrier(0);
+                issue_x(t + 1);
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    if (there) consume((2 * p + h) % D, t, h, stg);
+                    __builtin_amdgcn_sched_barrier(0);
+                    issue_w(2 * t + h + D, (2 * p + h) % D);
+                    asm volatile("" ::: "memory");
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        }
+        // loads for the run past the end still write into the stage buffers, which the reduction buffer covers
+        __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8));
+        asm volatile("" ::: "memory");
+
+        if (!kScale || pass == 1) break;
+        bool again = false;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            const float v = top[mb] * up[mb];
+            again |= v >= 32768.f && v <= 3.0e38f;           // (the lanes of a row need not agree: any of them will do)
+            const float row = fmaxf(v, __shfl_xor(v, 16, 64)), all = fmaxf(row, __shfl_xor(row, 32, 64));
+            again |= all > 0.f && all < 8.f;
+        }
+        if (!__any(again)) break;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) up[mb] = power(top[mb], 14);
+    }
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {        // lanes i, i + 16, i + 32, i + 48 hold row i's shares
+        float v = ss[mb];
+        v += __shfl_xor(v, 16, 64);
+        v += __shfl_xor(v, 32, 64);
+        if (q == 0) s_sumsq[wave][mb * 16 + i] = v;
+        if (kScale)                          // the rows' powers of two out of their sums
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float f = __shfl(1.f / up[mb], 4 * q + r, 64);         // lanes 0 .. 15 hold rows 0 .. 15
+#pragma unroll
+                for (int c = 0; c < 8; ++c) acc[mb][c][r] *= f;
+            }
     }
     float* red = smem;                       // lane (i, q): rows 16mb + 4q + r, columns n0 + 8i + c
 #pragma unroll
@@ -354,23 +349,23 @@ __global__ __launch_bounds__(64 * kOddWaves) void odd_kernel(
 
     // every row block is a problem of its own to the epilogue
     TailArgs ta{a.Y + size_t(rb) * 64 * N, Mh, N, N_TILE, 0, 0, 0, a.eps, a.inv_K, S, nullptr, nullptr, nullptr, nullptr, 0,
-                a.ldp, PRE ? a.rfac + 64 * rb : nullptr};
+                a.ldp};
     if (S > 1) {
         ta.ws_partial = a.ws_partial + size_t(rb) * S * 64 * a.ldp;
         ta.ws_sumsq = a.ws_sumsq + size_t(rb) * total * kSumsqStride;
         ta.counter = a.counter + size_t(rb) * n_tiles * kCounterStride;
     }
-    splitk_tail<T, MT, N_TILE, !PRE, NW, false, true>(ta, red, &s_sumsq[0][0], s_rinv, &s_last, tile, slab, n0);
+    splitk_tail<T, MT, N_TILE, true, NW, false, true>(ta, red, &s_sumsq[0][0], s_rinv, &s_last, tile, slab, n0);
 }
 
 // ------------------------------------------------------------------------------------------- host
-struct OddPlan { int MB, RB, S, n_tiles, Kx, ldp; bool pre, ok; size_t lds, partial, gp, rfac, bytes; const char* why; };
+struct OddPlan { int MB, RB, S, n_tiles, Kx, ldp; bool pre, ok; size_t lds, partial, gp, bytes; const char* why; };
 
 static OddPlan odd_plan(const Problem& p)
 {
     OddPlan pl{};
     if (p.dt == F32 || !p.fused || p.gated) { pl.why = "the odd-size variant runs the fused block in the 16-bit types only"; return pl; }
-    pl.pre = p.dt == F16 || p.K % 8 != 0;
+    pl.pre = p.K % 8 != 0;
     // a few dozen k and at most one plain workgroup to a place on the chip: nothing to stream, and the plain kernel's
     // single launch is ahead (1 x 64 x 1001 fp16: 8.9 us, 13.1 us here; at K = 128 12.8 and 13.4, at 300 26.6 and 12.4)
     if (p.K <= 96 && int64_t(p.M) * p.N <= (1 << 17)) { pl.why = "too small for the odd-size variant"; return pl; }
@@ -385,11 +380,10 @@ static OddPlan odd_plan(const Problem& p)
     const int64_t blocks = int64_t(pl.n_tiles) * pl.RB;
     // byte offsets into a slab of W are 32-bit; the ring runs up to 2048 rows past its end
     auto slab_fits = [&](int s) { return (int64_t(64) * ((runs + s - 1) / s) + 2048) * p.N * 2 < (int64_t(1) << 31); };
-    // workspace: padded X, padded g, row factors, partial tiles
+    // workspace: padded X, padded g, partial tiles
     auto up = [](size_t b) { return (b + 255) / 256 * 256; };
     pl.gp = pl.pre ? up(size_t(p.M) * pl.Kx * 2) : 0;
-    pl.rfac = pl.gp + (pl.pre ? up(size_t(pl.Kx) * 2) : 0);
-    pl.partial = pl.rfac + (pl.pre ? up(size_t(p.M) * 4) : 0);
+    pl.partial = pl.gp + (pl.pre ? up(size_t(pl.Kx) * 2) : 0);
     auto partial_bytes = [&](int s) { return s > 1 ? size_t(pl.RB) * s * Mb * pl.ldp * 4 : size_t(0); };
     // a split needs one run per wave, room for counters and sums of squares, and partials that fit the smallest
     // workspace there is, so that every entry point takes the same one
@@ -446,6 +440,13 @@ static hipError_t odd_mb(const Problem& p, const OddPlan& pl, const u16* X, cons
     }
 }
 
+template <typename T>
+static hipError_t odd_types(const Problem& p, const OddPlan& pl, bool odd_n, const u16* X, const u16* g, const OddCold& c, hipStream_t s)
+{
+    if (pl.pre) return odd_n ? odd_mb<T, true, true>(p, pl, X, g, c, s) : odd_mb<T, false, true>(p, pl, X, g, c, s);
+    return odd_n ? odd_mb<T, true, false>(p, pl, X, g, c, s) : odd_mb<T, false, false>(p, pl, X, g, c, s);
+}
+
 hipError_t launch_odd(const Problem& p, hipStream_t s, const char** why)
 {
     OddPlan pl = odd_plan(p);
@@ -455,22 +456,18 @@ hipError_t launch_odd(const Problem& p, hipStream_t s, const char** why)
     const u16* X = (const u16*)p.X;
     const u16* g = (const u16*)p.g;
     const float inv_K = 1.0f / float(p.K);
-    OddCold c{(u16*)p.Y, p.eps, inv_K, pl.ldp, pl.S > 1 ? reinterpret_cast<float*>(ws + pl.partial) : nullptr, p.ws_sumsq, p.ws_counter,
-              nullptr};
+    OddCold c{(u16*)p.Y, p.eps, inv_K, pl.ldp, pl.S > 1 ? reinterpret_cast<float*>(ws + pl.partial) : nullptr, p.ws_sumsq, p.ws_counter};
     if (pl.pre) {
-        float* rfac = reinterpret_cast<float*>(ws + pl.rfac);
         u16* gp = reinterpret_cast<u16*>(ws + pl.gp);
-        if (p.dt == F16) odd_rows_kernel<Fp16><<<p.M + 1, kRowThreads, 0, s>>>(X, g, (u16*)ws, gp, rfac, p.M, p.K, pl.Kx, p.eps, inv_K);
-        else             odd_rows_kernel<Bf16><<<p.M + 1, kRowThreads, 0, s>>>(X, g, (u16*)ws, gp, rfac, p.M, p.K, pl.Kx, p.eps, inv_K);
+        odd_rows_kernel<<<p.M + 1, kRowThreads, 0, s>>>(X, g, (u16*)ws, gp, p.M, p.K, pl.Kx);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        X = (const u16*)ws; g = gp; c.rfac = rfac;
+        X = (const u16*)ws; g = gp;
     }
     if (p.plan) { p.plan[0] = kOddTile; p.plan[1] = pl.S; p.plan[2] = pl.n_tiles * pl.S * pl.RB; }
     const bool odd_n = (p.N & 1) != 0;
-    if (p.dt == F16) return odd_n ? odd_mb<Fp16, true, true>(p, pl, X, g, c, s) : odd_mb<Fp16, false, true>(p, pl, X, g, c, s);
-    if (pl.pre)      return odd_n ? odd_mb<Bf16, true, true>(p, pl, X, g, c, s) : odd_mb<Bf16, false, true>(p, pl, X, g, c, s);
-    return odd_n ? odd_mb<Bf16, true, false>(p, pl, X, g, c, s) : odd_mb<Bf16, false, false>(p, pl, X, g, c, s);
+    if (p.dt == F16) return odd_types<Fp16>(p, pl, odd_n, X, g, c, s);
+    return odd_types<Bf16>(p, pl, odd_n, X, g, c, s);
 }
 
 }  // namespace rmsnl

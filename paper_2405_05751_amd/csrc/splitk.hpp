@@ -26,7 +26,6 @@ struct TailArgs {
     float* ws_partial; float* ws_sumsq; unsigned* counter;
     unsigned long long* trace; int trace_groups;
     int ldp;             // ODD: row length of the partial workspace, a multiple of 4 (N otherwise)
-    const float* rfac;   // ODD without FUSED: the rows' factors
 };
 
 // NW waves per workgroup (4 or 8).  red: [NW][MT][N_TILE] fp32 in LDS (one copy per wave), complete
@@ -91,7 +90,7 @@ __device__ __forceinline__ void splitk_tail(const TailArgs& a, const float* red,
     const float4_t kZero4 = {0.f, 0.f, 0.f, 0.f};
 
     if (a.S == 1) {
-        if (tid < MT) s_rinv[tid] = FUSED ? Ar::rinv(asum, a.inv_K, a.eps) : ODD ? (tid < a.M ? a.rfac[tid] : 0.f) : Ar::one();
+        if (tid < MT) s_rinv[tid] = FUSED ? Ar::rinv(asum, a.inv_K, a.eps) : Ar::one();
         __syncthreads();
         if (GATED && 2 * a.half == N_TILE) {
             // full-width gated tile: one thread per output quad, so that no thread sits out on an up quad
@@ -216,7 +215,7 @@ __device__ __forceinline__ void splitk_tail(const TailArgs& a, const float* red,
         const int p = tid + qi * NT;
         const int m = p / (N_TILE / 4), c = (p % (N_TILE / 4)) * 4;
         if (poff[qi][0] != kNowhere)
-            store_y(m, c, yv[qi][0], yv[qi][NQ - 1], FUSED ? Ar::rinv(asq[qi], a.inv_K, a.eps) : ODD ? a.rfac[m] : Ar::one());
+            store_y(m, c, yv[qi][0], yv[qi][NQ - 1], FUSED ? Ar::rinv(asq[qi], a.inv_K, a.eps) : Ar::one());
     }
     trace_stamp(a.trace, a.trace_groups, 7);         // Y stored
     if (tid == 0)                            // ready for the next call on this stream

@@ -72,6 +72,36 @@ def test_fp16_range(rl, M, K, N):
         _check(to_host_f64(Y, "f16"), Z, "f16", f"scale {scale}")
 
 
+@pytest.mark.parametrize("what", ["small x, large gain", "large behind small", "first runs zero", "both large", "all small"])
+@pytest.mark.parametrize("M,K,N", [(3, 1001, 131), (40, 1024, 131), (70, 2049, 258)])
+def test_fp16_uneven_gain(rl, M, K, N, what):
+    """Products of very different size, and their largest in another column than the largest x or the largest gain: an
+    operand that is rounded, or a product that is cut off, shows above the fp32 sums (see _check)."""
+    import torch
+    w = workloads.make(M, K, N, "f16", 1e-5, 78 + M)
+    x, g = w.X.copy(), w.g.copy()
+    if what == "small x, large gain":
+        x[:, 5], g[5] = 7.4e-5, 60000.0                  # a product of 4.4
+        x[:, K - 1], g[K - 1] = 30000.0, 1e-4            # of 3, but x and g alone bound the row's by 1.8e9
+    elif what == "large behind small":
+        x[:, :260] *= np.float16(2.0 ** -12)             # (the first run of each wave)
+        x[:, K - 3], g[K - 3] = 30000.0, 3000.0
+    elif what == "first runs zero":
+        x[:, :300] = 0.0
+        x[0, 300:] *= np.float16(2.0 ** -12)
+        x[1, K - 3] = 30000.0
+    elif what == "both large":
+        x[:, 70], g[70] = 60000.0, 3000.0
+    else:
+        x *= np.float16(2.0 ** -16)
+    X, G, W = torch.from_numpy(x).cuda(), torch.from_numpy(g).cuda(), upload(w)[2]
+    Y = rl.rmsnorm_linear(X, G, W, 0.0)
+    torch.cuda.synchronize()
+    assert rl.rl_last_launch()[1] == 128
+    Z = oracle.rmsnorm_linear(x, g, w.W, "f16", 0.0)
+    _check(to_host_f64(Y, "f16"), Z, "f16", f"{M}x{K}x{N} {what}")
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("K", [264, 261])
 def test_special_values(rl, dtype, K):
