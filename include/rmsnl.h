@@ -45,8 +45,8 @@ typedef enum { RL_F16 = 0, RL_BF16 = 1, RL_F32 = 2 } rl_dtype;
 typedef enum {
     RL_AUTO = 0,          /* pick by shape: fp32: its matrix-core kernel, or the plain kernel for what that one does not run.  K or N not
                              a multiple of 8: the skinny kernel's form for any sizes (reported as RL_NAIVE, with 128 columns
-                             by rl_last_launch; the plain kernel for K <= 96 with M N <= 131072, without room for its workspace, for matmul, and for
-                             the gated block, there also with N not a multiple of 16).  Else GEMV
+                             by rl_last_launch; without room for its partial sums it is not split; the plain kernel for K <= 96 with M N <= 131072, for
+                             matmul, and for the gated block, there also with N not a multiple of 16).  Else GEMV
                              for M = 1 and N < 10240, and for M <= 4 while K N <= 6e6; M <= 64 skinny, and up to M = 1024 while
                              ceil(M / 64) K N <= 1.4e8 (0.9e8 for N > 6144 and M > 128); else the two-kernel tile form (above 64 rows also where
                              its 128-row tiles are estimated to be clearly ahead), or the
@@ -96,8 +96,7 @@ rl_status rmsnorm_linear(const void* X, const void* g, const void* W, float eps,
  * ignores rl_set_workspace.  The first call on a device looks the array's address up and enqueues a
  * small kernel on `stream` that zeroes the counters.
  * A shape whose split-K partials do not fit returns RL_ERR_WORKSPACE ("fixed scratch buffer") and
- * launches nothing; K or N not a multiple of 8 with more rows than fit (2 M K + 4 M bytes) runs the plain
- * kernel; the two-kernel tile form, which would need 2 M K bytes, gives way to the one fused
+ * launches nothing; the two-kernel tile form, which would need 2 M K bytes, gives way to the one fused
  * tile kernel, which needs none.
  * All calls on a device share that device's array: calls that overlap in time on one device (different
  * streams, or a graph replayed beside another call) race on it and must be ordered by the caller.
@@ -360,8 +359,8 @@ rl_status rl_ff_pairs(const void* X, const void* g, const void* W, void* Y, int6
  * stream is being captured into a graph: run the shape once before capturing, or lend a buffer.  rl_set_workspace lends a
  * caller-owned DEVICE buffer instead (for the current device; the first 256 KiB must be zero when lent);
  * NULL returns to the library's own buffer.  With a lent buffer too small for a call, the split-K variants
- * return RL_ERR_WORKSPACE; the two-kernel tile form is then skipped by RL_AUTO (the fused tile kernel runs), and so
- * is the kernel for K or N not a multiple of 8 (the plain kernel runs).
+ * return RL_ERR_WORKSPACE; the two-kernel tile form is then skipped by RL_AUTO (the fused tile kernel runs), and
+ * the kernel for K or N not a multiple of 8 runs unsplit.
  * rl_workspace_bytes gives the bytes an rmsnorm_linear call of that shape would like (0 if none).
  */
 rl_status rl_set_workspace(void* dev_ptr, size_t bytes);

@@ -257,36 +257,37 @@ rl_status run(Problem& p, void* stream, const Workspace* fixed = nullptr, const 
     hipStream_t s = static_cast<hipStream_t>(stream);
     tl_last_plan[0] = tl_last_plan[1] = tl_last_plan[2] = 0;
     p.plan = tl_last_plan;
-    rl_variant order[7];
+    Tuned order[8];                        // what is tried, one after the other: variant and launch shape
     int n_order = 0;
+    auto then = [&](rl_variant v, int k_split = 0) { order[n_order++] = Tuned{v, 0, k_split}; };
     if (forced != RL_AUTO) {
-        order[n_order++] = forced;
+        order[n_order++] = Tuned{forced, p.n_tile, p.k_split};
     } else {
         p.n_tile = 0;                      // tuning overrides apply to a forced variant only
         p.k_split = 0;
-        if (tuned.variant != RL_AUTO) order[n_order++] = tuned.variant;    // with its launch shape, see below
+        if (tuned.variant != RL_AUTO) order[n_order++] = tuned;
         rl_variant first = choose_auto(p);
-        if ((first == RL_MFMA_TILE && prefers_two_kernels(p)) || prefers_mid_tiles(p)) order[n_order++] = RL_MFMA_TILE_PRE;
-        if (first == RL_NAIVE) order[n_order++] = kOddSizes;
-        order[n_order++] = first;
-        if (first == RL_MFMA_SKINNY && p.M > 64) order[n_order++] = RL_MFMA_TILE;   // e.g. no room for the split
-        if (first != RL_NAIVE) order[n_order++] = RL_NAIVE;
+        if ((first == RL_MFMA_TILE && prefers_two_kernels(p)) || prefers_mid_tiles(p)) then(RL_MFMA_TILE_PRE);
+        if (first == RL_NAIVE) {
+            then(kOddSizes);
+            then(kOddSizes, 1);            // without a split, which needs no workspace
+        }
+        then(first);
+        if (first == RL_MFMA_SKINNY && p.M > 64) then(RL_MFMA_TILE);   // e.g. no room for the split
+        if (first != RL_NAIVE) then(RL_NAIVE);
     }
     const char* why = "variant cannot run this shape";
     for (int i = 0; i < n_order; ++i) {
-        rl_variant v = order[i];
+        rl_variant v = order[i].variant;
         why = "variant cannot run this shape";
-        if (forced == RL_AUTO) {
-            const bool use_tuned = (i == 0 && tuned.variant != RL_AUTO);
-            p.n_tile = use_tuned ? tuned.n_tile : 0;
-            p.k_split = use_tuned ? tuned.k_split : 0;
-        }
+        p.n_tile = order[i].n_tile;
+        p.k_split = order[i].k_split;
         rl_status ws_status;
         hipError_t e = launch_variant(v, p, s, &why, &ws_status, fixed);
         if (ws_status != RL_OK) {
             // the two-kernel form is an optimisation: without room for it the fused kernel runs; a
             // tuned launch shape likewise gives way to the built-in one, and the odd-size kernel, for
-            // whatever reason it has no workspace, to the plain one
+            // whatever reason it has no workspace, to itself without a split
             if (v == kOddSizes) continue;
             if (forced == RL_AUTO && ws_status == RL_ERR_WORKSPACE &&
                 (v == RL_MFMA_TILE_PRE || (i == 0 && tuned.variant != RL_AUTO))) continue;

@@ -11,8 +11,9 @@
 //     shift itself costs nothing, it is another selector of the same v_perm.  Lane 15 of a row has no next
 //     lane: the dwords it needs, 32 per 64 rows, come with one more load per run, through LDS (leaving that
 //     lane's columns out, tiles of 120 instead of 128, measured 74 us at 24 x 4096 x 32003, with them 50).
-//   * X.  Rows of X must start on 16 bytes for the direct loads to LDS, so with K % 8 != 0 a first kernel
-//     copies X and g to rows padded with zeros (M K elements, small beside W).
+//   * X.  The direct loads to LDS fetch 16-byte chunks of rows that start on 16 bytes.  With K % 8 != 0 X goes through
+//     registers: a chunk is loaded from the dword it starts in, with one dword more, shifted by half a dword
+//     where it starts in the middle of one, what lies behind K is zeroed, and the result is written to the same place.
 //   * X (.) g enters the matrix cores as two operands, hi + lo, at every M: the kernel that ran these
 //     sizes before kept the product in fp32.  hi is the product cut off (not rounded) one fp32 ulp below its
 //     value, lo what is left: both have the product's sign and neither is zero unless the product is, so
@@ -28,9 +29,9 @@
 //     no second pass, but registers for it in every step: 136 of them spilled at 64 rows.)
 //
 // Bound by streaming W, like the skinny kernel.  24 x 4096 x 32003: bf16 50 us (264 MB, 5.2 TB/s), fp16 51 us (54 with
-// the first kernel it had; but 256 x 4095 x 4099, where the vector instructions count, 59 us against 52);
+// the first kernel it had; but 256 x 4095 x 4099, where the vector instructions count, 59 us against 52, bf16 55 against 50);
 // the plain kernel that ran these sizes before takes 2460 us.  Large M is bound by every row
-// block's own copy of W out of L2: 2048 x 4096 x 4099 272 us (253 TFLOP/s).
+// block's own copy of W out of L2: 2048 x 4096 x 4099 bf16 220 us (312 TFLOP/s), fp16 241 us.
 #include <algorithm>
 #include <type_traits>
 #include "common.hpp"
@@ -75,18 +76,6 @@ template <> struct TwoPart<Fp16> {
     }
 };
 
-// ------------------------------------------------------------------------------------ first kernel
-// K % 8 != 0.  One workgroup per row of X: the row to Xp [M][Kp], with zeros from K on.  Workgroup M: g to gp [Kp].
-constexpr int kRowThreads = 1024;
-__global__ __launch_bounds__(kRowThreads) void odd_rows_kernel(const u16* __restrict__ X, const u16* __restrict__ g,
-                                                               u16* __restrict__ Xp, u16* __restrict__ gp, int M, int K, int Kp)
-{
-    const bool gain = int(blockIdx.x) == M;
-    const u16* src = gain ? g : X + size_t(blockIdx.x) * K;
-    u16* dst = gain ? gp : Xp + size_t(blockIdx.x) * Kp;
-    for (int k = threadIdx.x; k < Kp; k += kRowThreads) dst[k] = k < K ? src[k] : u16(0);
-}
-
 // ------------------------------------------------------------------------------------- the product
 struct OddCold {                             // what the first loads do not need
     u16* Y;
@@ -95,10 +84,10 @@ struct OddCold {                             // what the first loads do not need
     float* ws_partial; float* ws_sumsq; unsigned* counter;
 };
 
-// PRE: X and g are the first kernel's copies, rows Kx long; otherwise the caller's (Kx = K, a multiple of 8).
-template <typename T, int MB, bool ODDN, bool PRE>
+// SHIFT: K % 8 != 0, rows of X start anywhere.
+template <typename T, int MB, bool ODDN, bool SHIFT>
 __global__ __launch_bounds__(64 * kOddWaves) void odd_kernel(
-    const u16* W, const u16* X, const u16* g, int M, int K, int Kx, int N, int S, int n_tiles, int RB, OddCold a)
+    const u16* W, const u16* X, const u16* g, int M, int K, int N, int S, int n_tiles, int RB, OddCold a)
 {
     constexpr int NW = kOddWaves, MT = 16 * MB, D = odd_depth(MB), N_TILE = kOddTile;
     extern __shared__ __align__(16) float smem[];   // red [NW][MT][N_TILE]; the stage buffers of X before that
@@ -113,12 +102,12 @@ __global__ __launch_bounds__(64 * kOddWaves) void odd_kernel(
     const int total = n_tiles * S, b = xcd_run(blockIdx.x, total * RB);
     const int rb = b % RB, tile = b / RB / S, slab = b / RB % S;
     const int Mh = min(M - 64 * rb, 64);     // rows of this row block
-    const u16* Xb = X + size_t(rb) * 64 * Kx;
+    const u16* Xb = X + size_t(rb) * 64 * K;
     const int n0 = tile * N_TILE;
     const int runs = (K + 63) >> 6;          // 64-row runs of W; slab s takes runs [s R / S, (s + 1) R / S)
     const int run0 = int(int64_t(slab) * runs / S), run1 = int(int64_t(slab + 1) * runs / S);
     const int k0 = run0 * 64;
-    const int klen = min(run1 * 64, K) - k0, kxlen = min(run1 * 64, Kx) - k0;
+    const int klen = min(run1 * 64, K) - k0;
     const int nPairs = (run1 - run0 - wave + NW - 1) / NW;       // runs wave, wave + NW, ... of the slab
 
     // (an odd count of elements ends in the low half of a dword)
@@ -137,8 +126,8 @@ __global__ __launch_bounds__(64 * kOddWaves) void odd_kernel(
     constexpr int STG = MT * 128 + 1024 + 256;   // a run of X, the KiB that g's load writes, lane 15's dwords
     static_assert(2 * STG <= MT * N_TILE * 4, "two stage buffers fit the wave's part of the reduction buffer");
     const uint32_t stage_lds = __builtin_amdgcn_readfirstlane(uint32_t(uintptr_t(stage)));
-    const uint4_t xdesc = {uint32_t(uintptr_t(Xb)), uint32_t(uintptr_t(Xb) >> 32), uint32_t(Mh * Kx * 2), uint32_t(kOddFlags)};
-    const uint4_t gdesc = {uint32_t(uintptr_t(g)), uint32_t(uintptr_t(g) >> 32), uint32_t(Kx * 2), uint32_t(kOddFlags)};
+    const uint4_t xdesc = {uint32_t(uintptr_t(Xb)), uint32_t(uintptr_t(Xb) >> 32), uint32_t((Mh * K * 2 + 3) & ~3), uint32_t(kOddFlags)};
+    const uint4_t gdesc = {uint32_t(uintptr_t(g)), uint32_t(uintptr_t(g) >> 32), uint32_t((K * 2 + 3) & ~3), uint32_t(kOddFlags)};
     auto load_lds = [&](const uint4_t& rsrc, uint32_t dst, int v) {
         const uint4_t desc = rsrc;
         uint32_t keep;                       // M0 carries the LDS address; whatever it held is put back
@@ -158,17 +147,48 @@ __global__ __launch_bounds__(64 * kOddWaves) void odd_kernel(
                      : "=&s"(keep) : "s"(dst), "v"(v), "s"(desc) : "memory");
     };
     uint4_t w[D][8];
-    const int rlim = Mh - r8, xlane = r8 * Kx * 2, xlast = (Mh - 1) * Kx * 2;
+    const int rlim = Mh - r8, xlane = r8 * K * 2, xlast = (Mh - 1) * K * 2;
+    const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<u16*>(Xb), 0, (Mh * K * 2 + 3) & ~3, kOddFlags);
+    const __amdgpu_buffer_rsrc_t grs = __builtin_amdgcn_make_buffer_rsrc(const_cast<u16*>(g), 0, (K * 2 + 3) & ~3, kOddFlags);
+    uint4_t xv[SHIFT ? 2 * MB : 1], gv;      // SHIFT: the next run's chunks on their way, from the dword they start in,
+    uint32_t xn[SHIFT ? 2 * MB : 1];         // and the dword behind each
+    auto chunk_k = [&](int krun, int j) { return krun + ((c8 ^ (r8 >> 1) ^ (4 * (j & 1))) << 3); };
     auto issue_x = [&](int t) {              // rows that do not exist: the last row again, never stored
         const uint32_t sb = stage_lds + uint32_t(t & 1) * STG;
         const int krun = (NW * t + wave) * 64;
-        const int kg = krun + c8 * 8;
+        const int kg = krun + c8 * 8, go = (r8 == 0 && kg < klen) ? (k0 + kg) * 2 : kOddOut;
         if (ODDN) load_edge(sb + st_e, int(eoff0 + unsigned(t) * unsigned(wpair)));
-        load_lds(gdesc, sb + st_g, (r8 == 0 && kg < kxlen) ? (k0 + kg) * 2 : kOddOut);
+        if (SHIFT) gv = __builtin_amdgcn_raw_buffer_load_b128(grs, go, 0, 0);
+        else       load_lds(gdesc, sb + st_g, go);
 #pragma unroll
         for (int j = 0; j < 2 * MB; ++j) {
-            const int kr = krun + ((c8 ^ (r8 >> 1) ^ (4 * (j & 1))) << 3);
-            load_lds(xdesc, sb + 1024 * j, kr < kxlen ? (k0 + kr) * 2 + (8 * j < rlim ? xlane + 8 * j * Kx * 2 : xlast) : kOddOut);
+            const int kr = chunk_k(krun, j);
+            const int xo = kr < klen ? (k0 + kr) * 2 + (8 * j < rlim ? xlane + 8 * j * K * 2 : xlast) : kOddOut;
+            if (SHIFT) {
+                xv[j] = __builtin_amdgcn_raw_buffer_load_b128(xrs, xo & ~3, 0, 0);
+                xn[j] = __builtin_amdgcn_raw_buffer_load_b32(xrs, int(unsigned(xo & ~3) + 16u), 0, 0);
+            } else {
+                load_lds(xdesc, sb + 1024 * j, xo);
+            }
+        }
+    };
+    auto stage_x = [&](int t) {              // SHIFT: the run that has arrived, to where the direct loads would have put it
+        char* sb = stage + (t & 1) * STG;
+        const int krun = (NW * t + wave) * 64;
+        auto inside = [&](uint4_t v, int kr) {           // zeros from K on
+            if (krun + 64 > klen)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = kr + 2 * e + 1 < klen ? v[e] : kr + 2 * e < klen ? v[e] & 0xffffu : 0u;
+            return v;
+        };
+        if (r8 == 0) *reinterpret_cast<uint4_t*>(sb + st_g + 16 * lane) = inside(gv, krun + c8 * 8);
+#pragma unroll
+        for (int j = 0; j < 2 * MB; ++j) {
+            const int row = 8 * j < rlim ? 8 * j + r8 : Mh - 1;
+            const uint32_t sh = uint32_t(row & K & 1) * 16u;             // k0 and kr are even
+            const uint4_t v = {__builtin_amdgcn_alignbit(xv[j][1], xv[j][0], sh), __builtin_amdgcn_alignbit(xv[j][2], xv[j][1], sh),
+                               __builtin_amdgcn_alignbit(xv[j][3], xv[j][2], sh), __builtin_amdgcn_alignbit(xn[j], xv[j][3], sh)};
+            *reinterpret_cast<uint4_t*>(sb + 1024 * j + 16 * lane) = inside(v, chunk_k(krun, j));
         }
     };
     auto issue_w = [&](int s, int d) {
@@ -220,7 +240,7 @@ __global__ __launch_bounds__(64 * kOddWaves) void odd_kernel(
             for (int r = 0; r < 4; ++r) {
                 // the first row past the end of an odd K starts in the dword of W's last element, and the other
                 // half of that dword is not W's
-                if (PRE && (NW * t + wave) * 64 + 16 * q + 8 * h + 2 * r + 1 >= klen) w[d][2 * r + 1][0] = 0;
+                if (SHIFT && (NW * t + wave) * 64 + 16 * q + 8 * h + 2 * r + 1 >= klen) w[d][2 * r + 1][0] = 0;
                 next[r] = uint32_t(__builtin_amdgcn_update_dpp(int(edge[r]), int(w[d][2 * r + 1][0]), 0x101 /* row_shl:1 */, 0xf, 0xf, false));
             }
         }
@@ -262,6 +282,7 @@ __global__ __launch_bounds__(64 * kOddWaves) void odd_kernel(
         if (kScale && pass == 0) {               // X of the first run is there once only the 16 youngest loads of W are not
             __builtin_amdgcn_s_waitcnt((16 & 15) | ((16 >> 4) << 14) | (7 << 4) | (15 << 8));
             asm volatile("" ::: "memory");
+            if (SHIFT) stage_x(0);
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) {
                 float v = 0.f;
@@ -292,6 +313,11 @@ __global__ __launch_bounds__(64 * kOddWaves) void odd_kernel(
                 __builtin_amdgcn_s_waitcnt((16 & 15) | ((16 >> 4) << 14) | (7 << 4) | (15 << 8));
                 asm volatile("" ::: "memory");
                 __builtin_amdgcn_sched_barrier(0);
+                if (SHIFT) {
+                    stage_x(t);
+                    asm volatile("" ::: "memory");
+                    __builtin_amdgcn_sched_barrier(0);
+                }
                 issue_x(t + 1);
                 asm volatile("" ::: "memory");
                 __builtin_amdgcn_sched_barrier(0);
@@ -359,18 +385,16 @@ __global__ __launch_bounds__(64 * kOddWaves) void odd_kernel(
 }
 
 // ------------------------------------------------------------------------------------------- host
-struct OddPlan { int MB, RB, S, n_tiles, Kx, ldp; bool pre, ok; size_t lds, partial, gp, bytes; const char* why; };
+struct OddPlan { int MB, RB, S, n_tiles, ldp; bool ok; size_t lds, bytes; const char* why; };
 
 static OddPlan odd_plan(const Problem& p)
 {
     OddPlan pl{};
     if (p.dt == F32 || !p.fused || p.gated) { pl.why = "the odd-size variant runs the fused block in the 16-bit types only"; return pl; }
-    pl.pre = p.K % 8 != 0;
     // a few dozen k and at most one plain workgroup to a place on the chip: nothing to stream, and the plain kernel's
     // single launch is ahead (1 x 64 x 1001 fp16: 8.9 us, 13.1 us here; at K = 128 12.8 and 13.4, at 300 26.6 and 12.4)
     if (p.K <= 96 && int64_t(p.M) * p.N <= (1 << 17)) { pl.why = "too small for the odd-size variant"; return pl; }
-    if (p.K > (1 << 23) || p.N > (1 << 30)) { pl.why = "the odd-size variant needs K <= 2^23 and N <= 2^30"; return pl; }
-    pl.Kx = pl.pre ? (p.K + 7) / 8 * 8 : p.K;            // 64 rows of X stay below 2^31 bytes
+    if (p.K > (1 << 23) || p.N > (1 << 30)) { pl.why = "the odd-size variant needs K <= 2^23 and N <= 2^30"; return pl; }     // (64 rows of X below 2^31 bytes)
     pl.ldp = (p.N + 3) / 4 * 4;
     pl.n_tiles = (p.N + kOddTile - 1) / kOddTile;
     pl.RB = int((int64_t(p.M) + 63) / 64);
@@ -380,21 +404,17 @@ static OddPlan odd_plan(const Problem& p)
     const int64_t blocks = int64_t(pl.n_tiles) * pl.RB;
     // byte offsets into a slab of W are 32-bit; the ring runs up to 2048 rows past its end
     auto slab_fits = [&](int s) { return (int64_t(64) * ((runs + s - 1) / s) + 2048) * p.N * 2 < (int64_t(1) << 31); };
-    // workspace: padded X, padded g, partial tiles
-    auto up = [](size_t b) { return (b + 255) / 256 * 256; };
-    pl.gp = pl.pre ? up(size_t(p.M) * pl.Kx * 2) : 0;
-    pl.partial = pl.gp + (pl.pre ? up(size_t(pl.Kx) * 2) : 0);
     auto partial_bytes = [&](int s) { return s > 1 ? size_t(pl.RB) * s * Mb * pl.ldp * 4 : size_t(0); };
     // a split needs one run per wave, room for counters and sums of squares, and partials that fit the smallest
-    // workspace there is, so that every entry point takes the same one
+    // workspace there is, so that every entry point takes the same one; k_split = 1 is the launch that needs none
     auto may_split = [&](int s) {
         return int64_t(s) * kOddWaves <= runs && blocks <= kMaxCounters && blocks * s * kSumsqStride <= kMaxSumsqFloats &&
-               pl.partial + partial_bytes(s) <= kScratchBytes - kHeadBytes;
+               partial_bytes(s) <= kScratchBytes - kHeadBytes;
     };
     // slabs: the skinny kernel's cost model (see skinny_plan, where its constants come from)
     double best = 0.;
     for (int s = 1; s <= 16; ++s) {
-        if (!slab_fits(s) || (s > 1 && !may_split(s))) continue;
+        if (!slab_fits(s) || (s > 1 && (!may_split(s) || p.k_split == 1))) continue;
         const double wgs = double(blocks) * s;
         const double wg_bytes = 64.0 * ((runs + s - 1) / s) * (kOddTile * 2.0 + Mb * 2.0);
         const double hbm_us = double(p.K) * p.N * 2.0 / 6.5e6;
@@ -406,7 +426,7 @@ static OddPlan odd_plan(const Problem& p)
     if (pl.S == 0) { pl.why = "the odd-size variant cannot address a slab of this W"; return pl; }
     if (blocks * pl.S >= (int64_t(1) << 31)) { pl.why = "too many workgroups"; return pl; }
     pl.lds = size_t(kOddWaves) * 16 * pl.MB * 128 * 4;
-    pl.bytes = pl.partial + partial_bytes(pl.S);
+    pl.bytes = partial_bytes(pl.S);
     pl.ok = true;
     return pl;
 }
@@ -417,34 +437,34 @@ size_t odd_workspace_bytes(const Problem& p)
     return pl.ok ? pl.bytes : 0;
 }
 
-template <typename T, int MB, bool ODDN, bool PRE>
-static hipError_t odd_go(const Problem& p, const OddPlan& pl, const u16* X, const u16* g, const OddCold& c, hipStream_t s)
+template <typename T, int MB, bool ODDN, bool SHIFT>
+static hipError_t odd_go(const Problem& p, const OddPlan& pl, const OddCold& c, hipStream_t s)
 {
     static LdsOnce once;                                 // 128 KiB of dynamic LDS at MB = 4
-    hipError_t e = raise_lds_once(once, {(const void*)odd_kernel<T, MB, ODDN, PRE>}, 144 * 1024);
+    hipError_t e = raise_lds_once(once, {(const void*)odd_kernel<T, MB, ODDN, SHIFT>}, 144 * 1024);
     if (e != hipSuccess) return e;
     dim3 grid(unsigned(pl.n_tiles * pl.S * pl.RB));
-    odd_kernel<T, MB, ODDN, PRE><<<grid, 64 * kOddWaves, pl.lds, s>>>((const u16*)p.W, X, g, p.M, p.K, pl.Kx, p.N, pl.S, pl.n_tiles,
-                                                                      pl.RB, c);
+    odd_kernel<T, MB, ODDN, SHIFT><<<grid, 64 * kOddWaves, pl.lds, s>>>((const u16*)p.W, (const u16*)p.X, (const u16*)p.g, p.M, p.K, p.N,
+                                                                        pl.S, pl.n_tiles, pl.RB, c);
     return hipGetLastError();
 }
 
-template <typename T, bool ODDN, bool PRE>
-static hipError_t odd_mb(const Problem& p, const OddPlan& pl, const u16* X, const u16* g, const OddCold& c, hipStream_t s)
+template <typename T, bool ODDN, bool SHIFT>
+static hipError_t odd_mb(const Problem& p, const OddPlan& pl, const OddCold& c, hipStream_t s)
 {
     switch (pl.MB) {
-    case 1:  return odd_go<T, 1, ODDN, PRE>(p, pl, X, g, c, s);
-    case 2:  return odd_go<T, 2, ODDN, PRE>(p, pl, X, g, c, s);
-    case 3:  return odd_go<T, 3, ODDN, PRE>(p, pl, X, g, c, s);
-    default: return odd_go<T, 4, ODDN, PRE>(p, pl, X, g, c, s);
+    case 1:  return odd_go<T, 1, ODDN, SHIFT>(p, pl, c, s);
+    case 2:  return odd_go<T, 2, ODDN, SHIFT>(p, pl, c, s);
+    case 3:  return odd_go<T, 3, ODDN, SHIFT>(p, pl, c, s);
+    default: return odd_go<T, 4, ODDN, SHIFT>(p, pl, c, s);
     }
 }
 
 template <typename T>
-static hipError_t odd_types(const Problem& p, const OddPlan& pl, bool odd_n, const u16* X, const u16* g, const OddCold& c, hipStream_t s)
+static hipError_t odd_types(const Problem& p, const OddPlan& pl, bool odd_n, const OddCold& c, hipStream_t s)
 {
-    if (pl.pre) return odd_n ? odd_mb<T, true, true>(p, pl, X, g, c, s) : odd_mb<T, false, true>(p, pl, X, g, c, s);
-    return odd_n ? odd_mb<T, true, false>(p, pl, X, g, c, s) : odd_mb<T, false, false>(p, pl, X, g, c, s);
+    if (p.K % 8) return odd_n ? odd_mb<T, true, true>(p, pl, c, s) : odd_mb<T, false, true>(p, pl, c, s);
+    return odd_n ? odd_mb<T, true, false>(p, pl, c, s) : odd_mb<T, false, false>(p, pl, c, s);
 }
 
 hipError_t launch_odd(const Problem& p, hipStream_t s, const char** why)
@@ -452,22 +472,11 @@ hipError_t launch_odd(const Problem& p, hipStream_t s, const char** why)
     OddPlan pl = odd_plan(p);
     if (!pl.ok) { if (why) *why = pl.why; return hipErrorInvalidValue; }
     if (pl.bytes && !p.ws_partial) { if (why) *why = "the odd-size variant needs the workspace"; return hipErrorInvalidValue; }
-    char* ws = reinterpret_cast<char*>(p.ws_partial);
-    const u16* X = (const u16*)p.X;
-    const u16* g = (const u16*)p.g;
-    const float inv_K = 1.0f / float(p.K);
-    OddCold c{(u16*)p.Y, p.eps, inv_K, pl.ldp, pl.S > 1 ? reinterpret_cast<float*>(ws + pl.partial) : nullptr, p.ws_sumsq, p.ws_counter};
-    if (pl.pre) {
-        u16* gp = reinterpret_cast<u16*>(ws + pl.gp);
-        odd_rows_kernel<<<p.M + 1, kRowThreads, 0, s>>>(X, g, (u16*)ws, gp, p.M, p.K, pl.Kx);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        X = (const u16*)ws; g = gp;
-    }
+    const OddCold c{(u16*)p.Y, p.eps, 1.0f / float(p.K), pl.ldp, p.ws_partial, p.ws_sumsq, p.ws_counter};
     if (p.plan) { p.plan[0] = kOddTile; p.plan[1] = pl.S; p.plan[2] = pl.n_tiles * pl.S * pl.RB; }
     const bool odd_n = (p.N & 1) != 0;
-    if (p.dt == F16) return odd_types<Fp16>(p, pl, odd_n, X, g, c, s);
-    return odd_types<Bf16>(p, pl, odd_n, X, g, c, s);
+    if (p.dt == F16) return odd_types<Fp16>(p, pl, odd_n, c, s);
+    return odd_types<Bf16>(p, pl, odd_n, c, s);
 }
 
 }  // namespace rmsnl

@@ -129,18 +129,18 @@ def test_special_values(rl, dtype, K):
     assert torch.isnan(Y[4]).all()
 
 
-def test_no_room_falls_back(rl):
-    """With a lent workspace too small for the first kernel's copies the plain kernel runs, as before."""
+def test_no_room_runs_unsplit(rl):
+    """With a lent workspace too small for the partial sums of a split the same kernel runs without one."""
     import torch
     w = workloads.make(40, 4001, 65, "bf16", 1e-5, 93)
     X, g, W = upload(w)
+    Z = oracle.rmsnorm_linear(w.X, w.g, w.W, w.dtype, w.eps)
     small = torch.zeros(1280 * 1024 + 4096, dtype=torch.uint8, device="cuda")
     rl.rl_set_workspace(small)
     try:
         Y = rl.rmsnorm_linear(X, g, W, w.eps)
         torch.cuda.synchronize()
-        assert rl.rl_last_launch()[:2] == ("naive", 0)
+        assert rl.rl_last_launch()[1:3] == (128, 1)
     finally:
         rl.rl_set_workspace(None)
-    Z = oracle.rmsnorm_linear(w.X, w.g, w.W, w.dtype, w.eps)
     _check(to_host_f64(Y, "bf16"), Z, "bf16", "no room")

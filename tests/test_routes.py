@@ -1,0 +1,15 @@
+"""Which kernels a call launches and what memory it takes for them, without a GPU (see tests/host/routes.py)."""
+import pytest
+
+from tests.host import routes
+
+
+@pytest.mark.parametrize("M,K,N", [(24, 4096, 32003), (24, 4095, 32003), (8, 4095, 3001), (8, 4096, 3001), (300, 513, 130)])
+@pytest.mark.parametrize("dt", ["F16", "BF16"])
+def test_odd_sizes_under_capture_before_any_other_call(M, K, N, dt):
+    """Nothing may be allocated then; the matrix-core kernel runs all the same, unsplit."""
+    out = routes.run(f"""
+rec.rec_capture(V(7), 1)
+print(linear({M}, {K}, {N}, {dt}, 7), rec.rec_mallocs(), names(), last()[2])
+""")
+    assert out == ["0 0 ['odd_kernel'] 1"]
