@@ -77,8 +77,9 @@ constexpr size_t kMaxOwnWorkspace = size_t(4) << 30;
 // Workspace for the current device: the lent buffer if there is one, else the library's own.  The
 // library's own buffer is replaced by a larger one (at least twice the size) when a call needs
 // more.  The old one is kept until the process ends: a graph captured earlier still points into
-// it.  Nothing is allocated while `stream` is being captured.
-rl_status get_workspace(size_t need, hipStream_t stream, Workspace* out)
+// it.  Nothing is allocated while `stream` is being captured.  *no_memory: the allocation failed; HIP's last error
+// is then taken back, so that the launch of a kernel that needs none does not find it.
+rl_status get_workspace(size_t need, hipStream_t stream, Workspace* out, bool* no_memory = nullptr)
 {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -102,7 +103,11 @@ rl_status get_workspace(size_t need, hipStream_t stream, Workspace* out)
             return fail(RL_ERR_WORKSPACE, "the workspace cannot grow during stream capture: run the shape once before, or lend a workspace");
         void* p = nullptr;
         e = hipMalloc(&p, want);
-        if (e != hipSuccess) return fail(RL_ERR_HIP, "hipMalloc(workspace): %s", hipGetErrorString(e));
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            if (no_memory) *no_memory = true;
+            return fail(RL_ERR_HIP, "hipMalloc(workspace): %s", hipGetErrorString(e));
+        }
         e = hipMemset(p, 0, kCounterBytes);              // synchronous, once per allocation
         if (e != hipSuccess) { (void)hipFree(p); return fail(RL_ERR_HIP, "hipMemset(workspace): %s", hipGetErrorString(e)); }
         g_ws[dev] = Workspace{p, want, true};            // (a smaller predecessor stays allocated)
@@ -197,7 +202,8 @@ bool prefers_mid_tiles(const Problem& p)
     return p.M > 64 && mid_plan(p, &cols, &S, &k_slab);
 }
 
-// one attempt at one variant; hipErrorInvalidValue = the variant cannot run the shape
+// one attempt at one variant; hipErrorInvalidValue = the variant cannot run the shape; with *ws_status set, hipErrorOutOfMemory = no
+// workspace because there was no room in the one there is or no memory for one
 // fixed: the one workspace this call may use (nothing is allocated), or null for the library's own or the lent one
 hipError_t launch_variant(rl_variant v, Problem& p, hipStream_t s, const char** why, rl_status* ws_status,
                           const Workspace* fixed = nullptr)
@@ -217,9 +223,11 @@ hipError_t launch_variant(rl_variant v, Problem& p, hipStream_t s, const char** 
             *ws_status = ws.bytes >= need + kHeadBytes ? RL_OK
                 : fail(RL_ERR_WORKSPACE, "the shape needs more workspace than this call's buffer holds (the scratch array of rmsnorm_linear_noalloc: 8 MiB in all)");
         } else {
-            *ws_status = get_workspace(need, s, &ws);
+            bool no_memory = false;
+            *ws_status = get_workspace(need, s, &ws, &no_memory);
+            if (no_memory) return hipErrorOutOfMemory;
         }
-        if (*ws_status != RL_OK) return hipErrorUnknown;
+        if (*ws_status != RL_OK) return *ws_status == RL_ERR_WORKSPACE ? hipErrorOutOfMemory : hipErrorUnknown;
         carve(ws, p);
     }
     switch (v) {
@@ -286,11 +294,10 @@ rl_status run(Problem& p, void* stream, const Workspace* fixed = nullptr, const 
         hipError_t e = launch_variant(v, p, s, &why, &ws_status, fixed);
         if (ws_status != RL_OK) {
             // the two-kernel form is an optimisation: without room for it the fused kernel runs; a
-            // tuned launch shape likewise gives way to the built-in one, and the odd-size kernel, for
-            // whatever reason it has no workspace, to itself without a split
-            if (v == kOddSizes) continue;
-            if (forced == RL_AUTO && ws_status == RL_ERR_WORKSPACE &&
-                (v == RL_MFMA_TILE_PRE || (i == 0 && tuned.variant != RL_AUTO))) continue;
+            // tuned launch shape likewise gives way to the built-in one, and the odd-size kernel to
+            // itself without a split
+            if (forced == RL_AUTO && e == hipErrorOutOfMemory &&
+                (v == RL_MFMA_TILE_PRE || v == kOddSizes || (i == 0 && tuned.variant != RL_AUTO))) continue;
             return ws_status;
         }
         if (e == hipSuccess) { tl_last_variant = public_variant(v); return RL_OK; }

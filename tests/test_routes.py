@@ -13,3 +13,16 @@ rec.rec_capture(V(7), 1)
 print(linear({M}, {K}, {N}, {dt}, 7), rec.rec_mallocs(), names(), last()[2])
 """)
     assert out == ["0 0 ['odd_kernel'] 1"]
+
+
+def test_failed_allocation():
+    """Calls that have a form without a workspace run it, and HIP's last error does not stay behind to be taken for theirs;
+    the others say what failed."""
+    out = routes.run("""
+rec.rec_fail_mallocs(100)
+print(linear(8, 4096, 3001), names(), last()[2])                 # a split over K gives way to none
+print(linear(300, 1024, 10000), names())                         # X-hat in the workspace to row blocks
+print(linear(1, 4096, 4096), names(), b"hipMalloc" in lib.rl_last_error())
+print(rec.hipGetLastError())
+""")
+    assert out == ["0 ['odd_kernel'] 1", "0 ['skinny_kernel']", "3 [] True", "0"]
