@@ -62,6 +62,7 @@ hipError_t launch_tile_pre(const Problem& p, hipStream_t s, const char** why);
 size_t tile_pre_workspace_bytes(const Problem& p);
 // the product of that form on 128-row tiles: which problems, and the launch
 bool mid_plan(const Problem& p, int* cols, int* S, int* k_slab);
+bool mid_fused(const Problem& p, int cols, int S);       // that launch forms X-hat itself: one kernel, no workspace
 double tile_pre_us(const Problem& p);        // the model's time of the form with 256 x 256 tiles
 // the skinny kernel's row blocks (64 < M): better than 256 x 256 tiles? and the model's time
 bool skinny_row_blocks(const Problem& p);

@@ -13,6 +13,12 @@
 // Both operands go from memory straight into LDS (direct loads), NS tiles ahead.  Iteration t: wait for the wave's own loads
 // of tile t + 1, barrier, ask for tile t + NS (into the buffer of tile t, whose fragments every wave holds in registers by
 // now), read the fragments of tile t + 1 into the other register set, matrix instructions on tile t.
+//
+// Unsplit, the kernel can form X-hat itself (FUSED): it multiplies the A fragments by g, which it keeps in LDS, and takes
+// the squares from them.  One launch, no workspace, and the same product bit for bit; only the squares are summed in another order.
+// It costs vector instructions in the K loop, at 128 columns twice (two waves hold the same rows): in fp16, which has packed
+// products, it is ahead nearly everywhere (34 shapes with M 89 to 2341, geometric mean 0.83; worst 1.00), in bf16 at 64
+// columns (0.74 to 1.06), but not at 128 (0.94 to 1.34: 563 x 3008 x 6336 33.5 and 43.6 us), where X-hat stays a kernel of its own.
 #include <algorithm>
 #include <cmath>
 #include "common.hpp"
@@ -26,6 +32,9 @@ constexpr unsigned kMidOut = 0x80000000u;    // beyond every resource (sizes bel
 // K tiles in LDS; with 64 columns two workgroups share a compute unit (72 KiB and 128 registers each), with 128 one (128 KiB)
 constexpr int mid_stages(int BN) { return BN == 64 ? 3 : 4; }
 constexpr size_t mid_lds(int BN) { return size_t(mid_stages(BN)) * (kMidM + BN) * kMidK * 2; }
+// FUSED: g in LDS besides, with room for as many workgroups as before (64 columns: K <= 4096; 128: K <= 16384)
+constexpr size_t kMidLdsMost = 160 * 1024;
+constexpr size_t mid_gain_lds(int K) { return size_t((K + kMidK - 1) / kMidK) * kMidK * 2; }
 
 struct MidArgs {
     const u16* X; const u16* W; u16* Y; const float* rscale;
@@ -33,6 +42,7 @@ struct MidArgs {
     int tiles_m, tiles_n, k_slab;
     int H, G;                                // gated block: outputs (N = 2 H) and the layout of W, see gated_col()
     float* part;                             // SPLIT: fp32 tiles [slab][M][N]
+    const u16* g; float eps, inv_K;          // FUSED: X is not X-hat yet
 };
 
 template <typename T> struct MfmaMid;
@@ -47,6 +57,27 @@ template <> struct MfmaMid<Fp16> {
     }
 };
 
+// FUSED: a pair of X times a pair of g, rounded once to the storage type, and the sum of a pair's squares, in as few vector
+// instructions as there are (the K loop is bound by them).  fp16 has a packed product, which rounds the exact one once, and
+// a dot product; bf16's dot product issues at a fraction of the rate (products from it: 46 us for 44 at 563 x 3008 x 6336).
+template <typename T> struct MidPair {
+    static __device__ __forceinline__ uint32_t mul(uint32_t x, uint32_t g) {
+        return Elem<T>::pack(Elem<T>::lo(x) * Elem<T>::lo(g), Elem<T>::hi(x) * Elem<T>::hi(g));
+    }
+    static __device__ __forceinline__ float squares(uint32_t x, float s) {
+        return __fmaf_rn(Elem<T>::hi(x), Elem<T>::hi(x), __fmaf_rn(Elem<T>::lo(x), Elem<T>::lo(x), s));
+    }
+};
+template <> struct MidPair<Fp16> {
+    static __device__ __forceinline__ uint32_t mul(uint32_t x, uint32_t g) {
+        return __builtin_bit_cast(uint32_t, __builtin_bit_cast(f16x2_t, x) * __builtin_bit_cast(f16x2_t, g));
+    }
+    static __device__ __forceinline__ float squares(uint32_t x, float s) {
+        const f16x2_t v = __builtin_bit_cast(f16x2_t, x);
+        return __builtin_amdgcn_fdot2(v, v, s, false);
+    }
+};
+
 typedef __attribute__((ext_vector_type(4))) short mid_short4_t;
 typedef __attribute__((address_space(3))) mid_short4_t* mid_lds_ptr;
 __device__ __forceinline__ uint2_t mid_read_tr(const u16* p) {
@@ -55,18 +86,20 @@ __device__ __forceinline__ uint2_t mid_read_tr(const u16* p) {
 
 #define RL_MID_WAIT_VM(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (((n) >> 4) << 14) | (7 << 4) | (15 << 8))
 
-template <typename T, int BN, bool GATED, bool SPLIT>
+template <typename T, int BN, bool GATED, bool SPLIT, bool FUSED>
 __global__ __launch_bounds__(512, BN == 64 ? 4 : 2) void mid_kernel(MidArgs a)
 {
     constexpr int BM = kMidM, BK = kMidK, NS = mid_stages(BN);
     constexpr int WN = BN / 64, WM = 4 / WN;             // waves of a group along N and M
     constexpr int TM = BM / WM / 32, TN = 2;             // matrix tiles per wave
+    static_assert(TM == WN, "a row block's squares for each wave along N");
     constexpr int BL = BN / 64;                          // direct loads of W per wave and K tile (two of X)
     constexpr int RPL = 512 / BN;                        // rows of W in one load of 1 KiB
     constexpr int NLOAD = 2 + BL;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     u16* As = (u16*)lds_raw;                             // [NS][BM][BK]
     u16* Bs = As + NS * BM * BK;                         // [NS][BK][BN]
+    u16* gs = Bs + NS * BK * BN;                         // FUSED: g, in whole K tiles
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -141,8 +174,13 @@ __global__ __launch_bounds__(512, BN == 64 ? 4 : 2) void mid_kernel(MidArgs a)
         b_off[j] = (32 * kg + b_row) * BN + ((wn * 64 + j * 32 + 16 * (blk & 1)) ^ (32 * (BN == 64 ? (b_row >> 1) & 1 : b_row & 3))) +
                    4 * (jj & 3);
     uint4_t af[2][2][TM], bf[2][2][TN];                  // [set][step]
-    auto read_frags = [&](auto set, int buf) {
+    uint4_t gf[2][2];
+    const int nk = (klen + BK - 1) / BK;
+    auto read_frags = [&](auto set, int t, int buf) {
         constexpr int st = decltype(set)::value;
+        if (FUSED)
+#pragma unroll
+            for (int s = 0; s < 2; ++s) gf[st][s] = *(const uint4_t*)(gs + min(t, nk - 1) * BK + 8 * (2 * (2 * kg + s) + (lane >> 5)));
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
             const u16* Ab = As + buf * BM * BK + a_off[s];
@@ -164,26 +202,54 @@ __global__ __launch_bounds__(512, BN == 64 ? 4 : 2) void mid_kernel(MidArgs a)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-    const int nk = (klen + BK - 1) / BK;
+    // FUSED: the fragments become X-hat (rounded once, as the first kernel of the other form rounds it) on their way into the
+    // matrix instructions; of the WN waves that hold the same rows each takes the squares of row block wn
+    float ss = 0.f;
+    auto squares = [&](const uint4_t& x) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ss = MidPair<T>::squares(x[e], ss);
+    };
+    auto x_hat = [&](uint4_t x, const uint4_t& gv) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = MidPair<T>::mul(x[e], gv[e]);
+        return x;
+    };
+    if (FUSED) {
+        const uint4_t* g8 = (const uint4_t*)a.g;
+        for (int c = tid; c < nk * (BK / 8); c += 512) ((uint4_t*)gs)[c] = 8 * c < klen ? g8[c] : uint4_t{0, 0, 0, 0};
+    }
 #pragma unroll
     for (int t = 0; t < NS; ++t) load_tile(t, t);
     RL_MID_WAIT_VM((NS - 1) * NLOAD);
     __syncthreads();
-    read_frags(std::integral_constant<int, 0>{}, 0);
+    read_frags(std::integral_constant<int, 0>{}, 0, 0);
     auto iteration = [&](auto set, int t) {
         constexpr int st = decltype(set)::value;
         RL_MID_WAIT_VM((NS - 2) * NLOAD);                // this wave's loads of tile t + 1 have landed
         __syncthreads();                                 // everybody's have, and everybody holds tile t in registers
         __builtin_amdgcn_sched_barrier(0);
-        read_frags(std::integral_constant<int, st ^ 1>{}, (t + 1) % NS);
+        read_frags(std::integral_constant<int, st ^ 1>{}, t + 1, (t + 1) % NS);
         load_tile(t + NS, t % NS);
         __builtin_amdgcn_sched_barrier(0);
+        if (FUSED) {
+            if (TM == 1 || wn == 0) {        // (a branch: the compiler would compute both and select)
+#pragma unroll
+                for (int s = 0; s < 2; ++s) squares(af[st][s][0]);
+                asm volatile("");
+            } else {
+#pragma unroll
+                for (int s = 0; s < 2; ++s) squares(af[st][s][TM - 1]);
+                asm volatile("");
+            }
+        }
 #pragma unroll
         for (int s = 0; s < 2; ++s)
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
+            for (int i = 0; i < TM; ++i) {
+                const uint4_t x = FUSED ? x_hat(af[st][s][i], gf[st][s]) : af[st][s][i];
 #pragma unroll
-                for (int j = 0; j < TN; ++j) acc[i][j] = MfmaMid<T>::run(af[st][s][i], bf[st][s][j], acc[i][j]);
+                for (int j = 0; j < TN; ++j) acc[i][j] = MfmaMid<T>::run(x, bf[st][s][j], acc[i][j]);
+            }
         __builtin_amdgcn_sched_barrier(0);
     };
     int t = 0;
@@ -198,6 +264,7 @@ __global__ __launch_bounds__(512, BN == 64 ? 4 : 2) void mid_kernel(MidArgs a)
     // ---- the groups' sums: group 0 finishes accumulator registers 0 .. 7, group 1 registers 8 .. 15
     float* mine = (float*)lds_raw + (wave * TM * TN * 8) * 64 + lane;
     const float* other = (const float*)lds_raw + ((wave ^ 4) * TM * TN * 8) * 64 + lane;
+    float* s_ss = (float*)lds_raw + 8 * TM * TN * 8 * 64;            // [2][BM], behind them; [0] then the rows' factors
     const int col = lane & 31, rowq = 4 * (lane >> 5);
     auto give = [&](auto first) {            // the eight registers the other group keeps
         constexpr int r0 = decltype(first)::value;
@@ -235,7 +302,9 @@ __global__ __launch_bounds__(512, BN == 64 ? 4 : 2) void mid_kernel(MidArgs a)
 #pragma unroll
                 for (int r = 0; r < 8; r += 2) {
                     const int ra = row0 + 8 * (r >> 2) + (r & 3), row = ra + (odd ? 1 : 0);
-                    const float s0 = ra < a.M ? a.rscale[ra] : 0.f, s1 = ra + 1 < a.M ? a.rscale[ra + 1] : 0.f;
+                    float s0, s1;
+                    if (FUSED) { s0 = s_ss[ra - m0]; s1 = s_ss[ra - m0 + 1]; }
+                    else { s0 = ra < a.M ? a.rscale[ra] : 0.f; s1 = ra + 1 < a.M ? a.rscale[ra + 1] : 0.f; }
                     constexpr int NO = GATED ? 1 : TN;
 #pragma unroll
                     for (int j = 0; j < NO; ++j) {
@@ -254,25 +323,38 @@ __global__ __launch_bounds__(512, BN == 64 ? 4 : 2) void mid_kernel(MidArgs a)
     const std::integral_constant<int, 0> low;
     const std::integral_constant<int, 8> high;
     if (kg == 0) give(high); else give(low);
+    if (FUSED) {
+        ss += __shfl_xor(ss, 32, 64);
+        if (lane < 32) s_ss[kg * BM + wm * (BM / WM) + wn * 32 + lane] = ss;         // (TM = WN row blocks of 32)
+        __syncthreads();
+        if (tid < BM) s_ss[tid] = row_scale(s_ss[tid] + s_ss[BM + tid], a.inv_K, a.eps);
+    }
     __syncthreads();
     if (kg == 0) finish(low); else finish(high);
 }
 
-template <typename T, int BN, bool GATED, bool SPLIT>
+template <typename T, int BN, bool GATED, bool SPLIT, bool FUSED>
 static hipError_t mid_go(const MidArgs& a, int S, hipStream_t s)
 {
     static LdsOnce once;
-    hipError_t e = raise_lds_once(once, {(const void*)mid_kernel<T, BN, GATED, SPLIT>}, int(mid_lds(BN)));
+    hipError_t e = raise_lds_once(once, {(const void*)mid_kernel<T, BN, GATED, SPLIT, FUSED>}, int(FUSED ? kMidLdsMost : mid_lds(BN)));
     if (e != hipSuccess) return e;
-    mid_kernel<T, BN, GATED, SPLIT><<<dim3(unsigned(a.tiles_m * a.tiles_n * S)), 512, mid_lds(BN), s>>>(a);
+    const size_t lds = mid_lds(BN) + (FUSED ? mid_gain_lds(a.K) : 0);
+    mid_kernel<T, BN, GATED, SPLIT, FUSED><<<dim3(unsigned(a.tiles_m * a.tiles_n * S)), 512, lds, s>>>(a);
     return hipGetLastError();
 }
 
 template <typename T, int BN>
 static hipError_t mid_t(const MidArgs& a, bool gated, int S, hipStream_t s)
 {
-    if (S > 1) return mid_go<T, BN, false, true>(a, S, s);
-    return gated ? mid_go<T, BN, true, false>(a, S, s) : mid_go<T, BN, false, false>(a, S, s);
+    if (S > 1) return mid_go<T, BN, false, true, false>(a, S, s);
+    if (a.g) return gated ? mid_go<T, BN, true, false, true>(a, S, s) : mid_go<T, BN, false, false, true>(a, S, s);
+    return gated ? mid_go<T, BN, true, false, false>(a, S, s) : mid_go<T, BN, false, false, false>(a, S, s);
+}
+
+bool mid_fused(const Problem& p, int cols, int S)
+{
+    return p.fused && S == 1 && (p.dt == F16 || cols == 64) && mid_lds(cols) + mid_gain_lds(p.K) <= kMidLdsMost / (cols == 64 ? 2 : 1);
 }
 
 // The tile width and the split over K for the product of this problem; false: another form is the better choice, or the
@@ -281,7 +363,7 @@ static hipError_t mid_t(const MidArgs& a, bool gated, int S, hipStream_t s)
 // The choice is a cost model, fitted (log least squares) to 153 shapes with M 65 to 8000, plain and gated, W from memory, the
 // chip warm (884 timings at both widths and 1 to 8 slabs; 9 % rms): microseconds for the first kernel, for a round of
 // workgroups over the chip (one per compute unit at 128 columns, two at 64) with its K tiles, for W from memory at
-// least, and for writing and adding the partial tiles.  The other forms' models (tile_pre_us, skinny_us) are of the same
+// least, and for writing and adding the partial tiles (all with X-hat as a kernel of its own).  The other forms' models (tile_pre_us, skinny_us) are of the same
 // fit.  The margins are there for the models' errors: on those shapes nothing became more than 4 % slower, 48 changed, and all
 // 153 take 8 % less time (geometric mean) (300 x 1024 x 10000 30 -> 19 us, 654 x 2392 x 4352 50 -> 29 us, 1024 x 4096 x 4096 57 -> 50 us).
 bool mid_plan(const Problem& p, int* cols, int* S, int* k_slab)
@@ -333,6 +415,7 @@ hipError_t launch_mid(const Problem& q, int cols, int S, int k_slab, float* part
     a.tiles_m = (q.M + kMidM - 1) / kMidM;
     a.tiles_n = gated ? (a.H + cols / 2 - 1) / (cols / 2) : (q.N + cols - 1) / cols;
     a.k_slab = k_slab; a.part = part;
+    a.g = q.fused ? (const u16*)q.g : nullptr; a.eps = q.eps; a.inv_K = 1.0f / float(q.K);
     if (cols == 64) return q.dt == F16 ? mid_t<Fp16, 64>(a, gated, S, s) : mid_t<Bf16, 64>(a, gated, S, s);
     return q.dt == F16 ? mid_t<Fp16, 128>(a, gated, S, s) : mid_t<Bf16, 128>(a, gated, S, s);
 }

@@ -831,7 +831,7 @@ size_t tile_pre_workspace_bytes(const Problem& p)
 {
     int S, k_slab, cols;
     if (mid_plan(p, &cols, &S, &k_slab))
-        return xhat_bytes(p) + rscale_bytes(p) + (S > 1 ? size_t(S) * p.M * p.N * 4 : 0);
+        return mid_fused(p, cols, S) ? 0 : xhat_bytes(p) + rscale_bytes(p) + (S > 1 ? size_t(S) * p.M * p.N * 4 : 0);
     tile_pre_split(p, &S, &k_slab);
     int full, rem, RS, rks;
     tile_rem_plan(p, &full, &rem, &RS, &rks);
@@ -858,6 +858,9 @@ hipError_t launch_tile_pre(const Problem& p, hipStream_t s, const char** why)
         int full, rem, RS, rks;
         tile_rem_plan(p, &full, &rem, &RS, &rks);
         if (rem && !p.ws_partial) { if (why) *why = "two-kernel tile variant needs the workspace"; return hipErrorInvalidValue; }
+    } else {
+        if (p.plan) { p.plan[0] = cols; p.plan[1] = S; p.plan[2] = ((p.M + 127) / 128) * ((p.N + cols - 1) / cols) * S; }
+        if (mid_fused(p, cols, S)) return launch_mid(p, cols, S, k_slab, nullptr, s);
     }
     if ((p.fused || S > 1) && !p.ws_partial) { if (why) *why = "two-kernel tile variant needs the workspace"; return hipErrorInvalidValue; }
     Problem q = p;                           // the product, scaled per row if it is the fused block's
@@ -875,7 +878,6 @@ hipError_t launch_tile_pre(const Problem& p, hipStream_t s, const char** why)
         q.rscale = nullptr;                  // the plain product (matmul): no first kernel, only the split
     }
     if (mid) {
-        if (p.plan) { p.plan[0] = cols; p.plan[1] = S; p.plan[2] = ((p.M + 127) / 128) * ((p.N + cols - 1) / cols) * S; }
         hipError_t e = launch_mid(q, cols, S, k_slab, part, s);
         return e == hipSuccess && S > 1 ? launch_tile_reduce(q, S, part, s) : e;
     }
