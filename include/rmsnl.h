@@ -98,10 +98,11 @@ rl_status rmsnorm_linear(const void* X, const void* g, const void* W, float eps,
  * ignores rl_set_workspace.  The first call on a device looks the array's address up and enqueues a
  * small kernel on `stream` that zeroes the counters.
  * A shape whose split-K partials do not fit returns RL_ERR_WORKSPACE ("fixed scratch buffer") and
- * launches nothing; the two-kernel tile form, which would need 2 M K bytes, gives way to the one fused
- * tile kernel, which needs none.
- * All calls on a device share that device's array: calls that overlap in time on one device (different
- * streams, or a graph replayed beside another call) race on it and must be ordered by the caller.
+ * launches nothing.  Where rmsnorm_linear runs 128-row tiles in place of the skinny kernel's row blocks (up to 1024 rows), their X (.) g
+ * and partial tiles lie in a second such array (48 MiB); for larger shapes the two-kernel tile form, which would need
+ * 2 M K bytes, gives way to the one fused tile kernel, which needs none.
+ * All calls on a device share that device's arrays: calls that overlap in time on one device (different
+ * streams, or a graph replayed beside another call) race on them and must be ordered by the caller.
  */
 rl_status rmsnorm_linear_noalloc(const void* X, const void* g, const void* W, float eps, void* Y,
                                  int64_t M, int64_t K, int64_t N, rl_dtype dt, void* stream);

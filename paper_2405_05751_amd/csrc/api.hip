@@ -131,8 +131,10 @@ void carve(const Workspace& ws, Problem& p)
 // device.  Same layout as every other workspace (see carve()).
 }  // namespace
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+static __device__ __align__(256) unsigned char row_scratch[kRowScratchBytes];    // (X-hat and partial tiles: no counters in use)
 namespace {
-void* g_scratch[kMaxDevices] = {};       // device address of the current device's copy, once looked up
+void* g_scratch[kMaxDevices] = {};       // device addresses of the current device's copies, once looked up
+void* g_row_scratch[kMaxDevices] = {};
 
 __global__ void scratch_clear_kernel(unsigned* p, int n)
 {
@@ -140,7 +142,7 @@ __global__ void scratch_clear_kernel(unsigned* p, int n)
     if (i < n) p[i] = 0u;
 }
 
-rl_status get_scratch(hipStream_t s, Workspace* out)
+rl_status get_scratch(hipStream_t s, Workspace* out, Workspace* rows)
 {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -149,7 +151,8 @@ rl_status get_scratch(hipStream_t s, Workspace* out)
     std::lock_guard<std::mutex> lk(g_mu);
     if (!g_scratch[dev]) {
         void* ptr = nullptr;
-        e = hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch));
+        e = hipGetSymbolAddress(&g_row_scratch[dev], HIP_SYMBOL(row_scratch));
+        if (e == hipSuccess) e = hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch));
         if (e != hipSuccess || !ptr) return fail(RL_ERR_HIP, "hipGetSymbolAddress(scratch): %s", hipGetErrorString(e));
         // the arrival counters must start at zero (the kernels leave them at zero after every call); a
         // fill kernel, not a memset, so that a caller may capture this first call into a graph
@@ -160,6 +163,7 @@ rl_status get_scratch(hipStream_t s, Workspace* out)
         g_scratch[dev] = ptr;
     }
     *out = Workspace{g_scratch[dev], kScratchBytes, false};
+    *rows = Workspace{g_row_scratch[dev], kRowScratchBytes, false};
     return RL_OK;
 }
 
@@ -204,9 +208,10 @@ bool prefers_mid_tiles(const Problem& p)
 
 // one attempt at one variant; hipErrorInvalidValue = the variant cannot run the shape; with *ws_status set, hipErrorOutOfMemory = no
 // workspace because there was no room in the one there is or no memory for one
-// fixed: the one workspace this call may use (nothing is allocated), or null for the library's own or the lent one
+// fixed: the one workspace this call may use (nothing is allocated), or null for the library's own or the lent one; fixed_rows:
+// a second one, for 128-row tiles in place of row blocks
 hipError_t launch_variant(rl_variant v, Problem& p, hipStream_t s, const char** why, rl_status* ws_status,
-                          const Workspace* fixed = nullptr)
+                          const Workspace* fixed = nullptr, const Workspace* fixed_rows = nullptr)
 {
     *ws_status = RL_OK;
     size_t need = 0;
@@ -219,7 +224,7 @@ hipError_t launch_variant(rl_variant v, Problem& p, hipStream_t s, const char** 
     if (need) {
         Workspace ws;
         if (fixed) {
-            ws = *fixed;
+            ws = fixed_rows && v == RL_MFMA_TILE_PRE && skinny_row_blocks(p) ? *fixed_rows : *fixed;
             *ws_status = ws.bytes >= need + kHeadBytes ? RL_OK
                 : fail(RL_ERR_WORKSPACE, "the shape needs more workspace than this call's buffer holds (the scratch array of rmsnorm_linear_noalloc: 8 MiB in all)");
         } else {
@@ -245,7 +250,8 @@ hipError_t launch_variant(rl_variant v, Problem& p, hipStream_t s, const char** 
 // opts: this call's variant and launch shape instead of the process-wide settings (or null)
 struct CallOpts { rl_variant variant; int n_tile, k_split; };
 
-rl_status run(Problem& p, void* stream, const Workspace* fixed = nullptr, const CallOpts* opts = nullptr)
+rl_status run(Problem& p, void* stream, const Workspace* fixed = nullptr, const CallOpts* opts = nullptr,
+              const Workspace* fixed_rows = nullptr)
 {
     rl_variant forced;
     Tuned tuned{RL_AUTO, 0, 0};
@@ -291,7 +297,7 @@ rl_status run(Problem& p, void* stream, const Workspace* fixed = nullptr, const 
         p.n_tile = order[i].n_tile;
         p.k_split = order[i].k_split;
         rl_status ws_status;
-        hipError_t e = launch_variant(v, p, s, &why, &ws_status, fixed);
+        hipError_t e = launch_variant(v, p, s, &why, &ws_status, fixed, fixed_rows);
         if (ws_status != RL_OK) {
             // the two-kernel form is an optimisation: without room for it the fused kernel runs; a
             // tuned launch shape likewise gives way to the built-in one, and the odd-size kernel to
@@ -334,13 +340,13 @@ rl_status rmsnorm_linear_noalloc(const void* X, const void* g, const void* W, fl
     if (!std::isfinite(eps) || eps < 0.f) return fail(RL_ERR_INVALID_ARG, "eps must be finite and >= 0");
     if (!aligned16(X) || !aligned16(g) || !aligned16(W) || !aligned16(Y))
         return fail(RL_ERR_INVALID_ARG, "pointers must be 16-byte aligned");
-    Workspace ws;
-    if (rl_status st = get_scratch(static_cast<hipStream_t>(stream), &ws)) return st;
+    Workspace ws, rows;
+    if (rl_status st = get_scratch(static_cast<hipStream_t>(stream), &ws, &rows)) return st;
     Problem p{};
     p.X = X; p.g = g; p.W = W; p.Y = Y;
     p.M = int(M); p.K = int(K); p.N = int(N);
     p.eps = eps; p.fused = 1; p.dt = DType(dt);
-    return run(p, stream, &ws);
+    return run(p, stream, &ws, nullptr, &rows);
 }
 
 size_t rl_noalloc_scratch_bytes(void) { return kScratchBytes; }

@@ -63,6 +63,7 @@ size_t tile_pre_workspace_bytes(const Problem& p);
 // the product of that form on 128-row tiles: which problems, and the launch
 bool mid_plan(const Problem& p, int* cols, int* S, int* k_slab);
 bool mid_fused(const Problem& p, int cols, int S);       // that launch forms X-hat itself: one kernel, no workspace
+size_t mid_workspace_bytes(const Problem& p, int S);      // of that launch, where it does not form X-hat itself
 double tile_pre_us(const Problem& p);        // the model's time of the form with 256 x 256 tiles
 // the skinny kernel's row blocks (64 < M): better than 256 x 256 tiles? and the model's time
 bool skinny_row_blocks(const Problem& p);
@@ -130,6 +131,7 @@ constexpr size_t kCounterBytes = 256 * 1024;
 constexpr size_t kSumsqBytes = 1024 * 1024;
 constexpr size_t kHeadBytes = kCounterBytes + kSumsqBytes;
 constexpr size_t kScratchBytes = size_t(8) << 20;          // the workspace of the entry point that allocates nothing
+constexpr size_t kRowScratchBytes = size_t(48) << 20;      // and its workspace for 128-row tiles in place of row blocks
 constexpr int kCounterStride = 32;                         // unsigneds between two counters
 constexpr int kMaxCounters = int(kCounterBytes / sizeof(unsigned)) / kCounterStride;
 constexpr int kMaxSumsqFloats = int(kSumsqBytes / sizeof(float));

@@ -394,6 +394,9 @@ bool mid_plan(const Problem& p, int* cols, int* S, int* k_slab)
         for (int s = 1; s <= 8; ++s) {
             const int ks = slab(s), real = (p.K + ks - 1) / ks;
             if (real != s || (s > 1 && (ks < 192 || double(s) * mn * 4. > 40.)) || !fits(c, s)) continue;
+            // in place of row blocks only with what the entry point that allocates nothing has for it: both then run the
+            // same launches and give the same bits (no shape of 12 000 needs more than 43 MiB)
+            if (skinny && !mid_fused(p, c, s) && mid_workspace_bytes(p, s) > kRowScratchBytes - kHeadBytes) continue;
             const int64_t tiles_n = p.gated && s == 1 ? (p.N / 2 + c / 2 - 1) / (c / 2) : (p.N + c - 1) / c;
             const double rounds = double((tiles_m * tiles_n * s + 255) / 256), kt = double((ks + kMidK - 1) / kMidK);
             const double run = c == 128 ? rounds * (4.1 + 0.62 * kt)

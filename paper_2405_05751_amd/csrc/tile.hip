@@ -827,11 +827,16 @@ double tile_pre_us(const Problem& p)
     return first + double((run + 255) / 256) * (6.4 + (run > 200 ? 1.66 : 1.40) * kt(p.K));
 }
 
+size_t mid_workspace_bytes(const Problem& p, int S)
+{
+    return xhat_bytes(p) + rscale_bytes(p) + (S > 1 ? size_t(S) * p.M * p.N * 4 : 0);
+}
+
 size_t tile_pre_workspace_bytes(const Problem& p)
 {
     int S, k_slab, cols;
     if (mid_plan(p, &cols, &S, &k_slab))
-        return mid_fused(p, cols, S) ? 0 : xhat_bytes(p) + rscale_bytes(p) + (S > 1 ? size_t(S) * p.M * p.N * 4 : 0);
+        return mid_fused(p, cols, S) ? 0 : mid_workspace_bytes(p, S);
     tile_pre_split(p, &S, &k_slab);
     int full, rem, RS, rks;
     tile_rem_plan(p, &full, &rem, &RS, &rks);

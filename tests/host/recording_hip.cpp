@@ -88,7 +88,13 @@ int hipMalloc(void** p, size_t n)
 }
 int hipFree(void*) { return 0; }
 int hipMemset(void*, int, size_t) { return 0; }
-int hipGetSymbolAddress(void** p, const void*) { *p = reinterpret_cast<void*>(uintptr_t(1) << 39); return 0; }
+int hipGetSymbolAddress(void** p, const void* symbol)
+{
+    static std::map<const void*, uintptr_t> at;
+    std::lock_guard<std::recursive_mutex> l(mu);
+    *p = reinterpret_cast<void*>(at.emplace(symbol, (uintptr_t(1) << 39) + at.size() * (uintptr_t(1) << 32)).first->second);
+    return 0;
+}
 int hipStreamIsCapturing(void* s, int* status) { std::lock_guard<std::recursive_mutex> l(mu); *status = capturing.count(s) ? 1 : 0; return 0; }
 int hipEventCreate(void** e) { *e = e; return 0; }
 int hipEventDestroy(void*) { return 0; }

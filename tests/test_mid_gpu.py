@@ -87,3 +87,19 @@ def test_automatic_choice(rl, M, K, N):
         rl.rl_set_workspace(None)
     assert used[0] in ("skinny", "tile")
     compare(to_host_f64(Y[rows], "bf16"), Z, "bf16", f"no room {M}x{K}x{N} {used}")
+
+
+@pytest.mark.parametrize("M,K,N,dtype", [(268, 3584, 3512, "bf16"), (140, 4096, 4096, "f16"), (900, 7272, 520, "bf16"), (245, 992, 2496, "f16")])
+def test_no_alloc_entry_point(rl, M, K, N, dtype):
+    """The same launch and the same bits where X-hat and the partial tiles are larger than the first scratch array."""
+    import torch
+    w = workloads.make(M, K, N, dtype, 1e-5, 9400 + M, n_check_rows=1)
+    X, g, W = upload(w)
+    Y = rl.rmsnorm_linear(X, g, W, w.eps)
+    used = rl.rl_last_launch()
+    assert used[0] == "tile_pre" and used[1] in (64, 128)
+    Y2 = torch.full_like(Y, 99.0)
+    rl.rmsnorm_linear_noalloc(X, g, W, w.eps, Y2)
+    torch.cuda.synchronize()
+    assert rl.rl_last_launch() == used
+    assert torch.equal(Y, Y2)

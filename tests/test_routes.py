@@ -35,3 +35,28 @@ def test_mid_size_products_without_a_workspace(M, K, N, dt):
 print(linear({M}, {K}, {N}, {dt}), rec.rec_mallocs(), names(), lib.rl_workspace_bytes({M}, {K}, {N}, {dt}))
 """)
     assert out == ["0 0 ['mid_kernel'] 0"]
+
+
+def test_row_block_sizes_launch_the_same_through_both_entry_points():
+    """65 to 1024 rows where row blocks are the alternative: what rmsnorm_linear_noalloc runs, rmsnorm_linear runs."""
+    out = routes.run("""
+import math, random
+r = random.Random(3)
+spread = lambda lo, hi: int(math.exp(r.uniform(math.log(lo), math.log(hi))))
+ran = 0
+for n in range(6000):
+    M, K, N, dt = spread(65, 1024), 8 * spread(16, 1024), 8 * spread(16, 2048), r.choice((F16, BF16))
+    blocks = (M + 63) // 64
+    if blocks * K * N > (1.4e8 if N <= 6144 or blocks == 2 else 0.9e8):
+        continue
+    st = linear(M, K, N, dt, 0, "rmsnorm_linear_noalloc")
+    a = [(l.mangled, l.grid) for l in launches() if l.name.startswith(("skinny", "xhat", "mid", "tile"))]
+    if st == 4:                                          # partial sums that the scratch does not hold: refused
+        continue
+    assert st == 0 and linear(M, K, N, dt) == 0
+    b = [(l.mangled, l.grid) for l in launches() if l.name.startswith(("skinny", "xhat", "mid", "tile"))]
+    assert a == b, (M, K, N, dt, a, b)
+    ran += 1
+print(ran > 2000)
+""")
+    assert out == ["True"]
