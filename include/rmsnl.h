@@ -7,7 +7,8 @@
  * (NULL = the default stream).  Every entry point only enqueues work and returns; it
  * performs no host synchronisation, with two exceptions: the first call on a device that needs
  * the library's own workspace (and a later one that needs a larger one) allocates it and clears
- * its counters with a synchronous memset (see rl_set_workspace for how to avoid that), and
+ * its counters with a synchronous memset (see rl_set_workspace for how to avoid that; a stream's first call
+ * that takes a region of its own allocates it, see rmsnorm_linear), and
  * rl_autotune waits for its timing events.  Matrices are dense and row-major:
  *
  *     X [M][K]   activations        g [K]      gain
@@ -82,7 +83,10 @@ typedef enum {
  * eps is added to the mean square under the root (eps = 0 gives Eq. 1 exactly).
  * An all-zero row with eps = 0 yields NaN, as the definition does.
  * May use the library workspace (see rl_set_workspace): calls that overlap in time on
- * different streams of one device must not both use it (rl_workspace_bytes() > 0).
+ * different streams of one device must not both use it (rl_workspace_bytes() > 0).  Some calls of which that is 0 are
+ * faster with memory all the same: they have it in a region of the stream's own (24 MiB, allocated at the first
+ * such call on a stream, for up to 16 streams of a device), and run without where there is none: while the stream
+ * is being captured, while a workspace is lent, beyond the 16 streams.
  */
 rl_status rmsnorm_linear(const void* X, const void* g, const void* W, float eps, void* Y,
                          int64_t M, int64_t K, int64_t N, rl_dtype dt, void* stream);
@@ -291,7 +295,8 @@ void rl_autotune_clear(void);
  * in the 16-bit types and D % 4 == 0 up to 128 in fp32 (keys read once, their mean,
  * variance and dot product from the same registers, online softmax, the sequence split over workgroups); any
  * other D (<= 4096), and keys of 2 GiB or more per head, run a slow plain kernel.  May use the library workspace like
- * rmsnorm_linear.  Pointers 16-byte aligned; O must not overlap the inputs.
+ * rmsnorm_linear; with 256 heads and samples or more, or fewer than 512 positions, the fast path does not (a region of
+ * the stream's own, or one split), unless a number of splits is forced or remembered.  Pointers 16-byte aligned; O must not overlap the inputs.
  */
 rl_status rl_qknorm_attention(const void* Q, const void* K, const void* V, const void* gq, const void* bq,
                               const void* gk, const void* bk, float eps, void* O,
@@ -364,7 +369,8 @@ rl_status rl_ff_pairs(const void* X, const void* g, const void* W, void* Y, int6
  * NULL returns to the library's own buffer.  With a lent buffer too small for a call, the split-K variants
  * return RL_ERR_WORKSPACE; the two-kernel tile form is then skipped by RL_AUTO (the fused tile kernel runs), and
  * the kernel for K or N not a multiple of 8 runs unsplit.
- * rl_workspace_bytes gives the bytes an rmsnorm_linear call of that shape would like (0 if none).
+ * rl_workspace_bytes gives the bytes of it an rmsnorm_linear call of that shape would like (0 if none, also where the
+ * call has them in its stream's region).
  */
 rl_status rl_set_workspace(void* dev_ptr, size_t bytes);
 size_t rl_workspace_bytes(int64_t M, int64_t K, int64_t N, rl_dtype dt);

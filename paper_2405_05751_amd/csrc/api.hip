@@ -167,6 +167,53 @@ rl_status get_scratch(hipStream_t s, Workspace* out, Workspace* rows)
     return RL_OK;
 }
 
+// ---- regions of a stream's own, for forms that are faster with a workspace than the form without one behind them.  A call that can
+// do without must not share memory with one on another stream (rl_workspace_bytes() says 0 of it), so it takes what
+// it needs from its stream's region, or does without: under capture (the graph may be replayed beside anything), while a buffer
+// is lent (the lender wants no allocations), and for streams beyond the first kMaxRegions that asked.  (A shape that does without
+// where rmsnorm_linear_noalloc does not may differ from it in the last bit.)  A handle can come back for a new
+// stream only when the runtime has freed the old one, whose work is done by then.
+constexpr int kMaxRegions = 16;
+struct Region { hipStream_t stream; void* ptr; };
+Region g_region[kMaxDevices][kMaxRegions];
+int g_regions[kMaxDevices] = {};
+
+rl_status get_region(hipStream_t s, Workspace* out, bool* no_memory)
+{
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return fail(RL_ERR_HIP, "hipGetDevice: %s", hipGetErrorString(e));
+    if (dev < 0 || dev >= kMaxDevices) return fail(RL_ERR_UNSUPPORTED, "device index out of range");
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    e = hipStreamIsCapturing(s, &cap);
+    if (e != hipSuccess) return fail(RL_ERR_HIP, "hipStreamIsCapturing: %s", hipGetErrorString(e));
+    if (cap != hipStreamCaptureStatusNone || s == hipStreamPerThread)    // (that handle is another stream in every thread)
+        return fail(RL_ERR_WORKSPACE, "no region for this stream");
+    std::lock_guard<std::mutex> lk(g_mu);
+    if (g_lent[dev].ptr) return fail(RL_ERR_WORKSPACE, "no region while a workspace is lent");
+    for (int i = 0; i < g_regions[dev]; ++i)
+        if (g_region[dev][i].stream == s) { *out = Workspace{g_region[dev][i].ptr, kRegionBytes, true}; return RL_OK; }
+    if (g_regions[dev] == kMaxRegions) return fail(RL_ERR_WORKSPACE, "no region left");
+    void* p = nullptr;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;             // another thread may be capturing a stream of its own
+    e = hipThreadExchangeStreamCaptureMode(&mode);
+    if (e != hipSuccess) return fail(RL_ERR_HIP, "hipThreadExchangeStreamCaptureMode: %s", hipGetErrorString(e));
+    e = hipMalloc(&p, kRegionBytes);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        *no_memory = true;
+        return fail(RL_ERR_HIP, "hipMalloc(region): %s", hipGetErrorString(e));
+    }
+    const int n = int(kCounterBytes / sizeof(unsigned));                 // arrival counters start at zero
+    scratch_clear_kernel<<<(n + 255) / 256, 256, 0, s>>>(static_cast<unsigned*>(p), n);
+    e = hipGetLastError();
+    if (e != hipSuccess) { (void)hipFree(p); return fail(RL_ERR_HIP, "clearing a region's counters: %s", hipGetErrorString(e)); }
+    g_region[dev][g_regions[dev]++] = Region{s, p};
+    *out = Workspace{p, kRegionBytes, true};
+    return RL_OK;
+}
+
 // The matrix-core kernel for sizes that are no multiple of eight: not a choice of the caller's but what RL_AUTO
 // runs in place of the plain kernel where it can.  Reported as RL_NAIVE, which is what a caller may force there.
 constexpr rl_variant kOddSizes = rl_variant(7);
@@ -206,12 +253,19 @@ bool prefers_mid_tiles(const Problem& p)
     return p.M > 64 && mid_plan(p, &cols, &S, &k_slab);
 }
 
+// Is the automatic choice of v a form that the call could do without a workspace (get_region)?  The odd-size kernel runs unsplit,
+// 128-row tiles in place of row blocks that are not split either.
+bool spares_workspace(rl_variant v, const Problem& p)
+{
+    return v == kOddSizes || (v == RL_MFMA_TILE_PRE && skinny_row_blocks(p) && skinny_workspace_bytes(p) == 0);
+}
+
 // one attempt at one variant; hipErrorInvalidValue = the variant cannot run the shape; with *ws_status set, hipErrorOutOfMemory = no
 // workspace because there was no room in the one there is or no memory for one
-// fixed: the one workspace this call may use (nothing is allocated), or null for the library's own or the lent one; fixed_rows:
-// a second one, for 128-row tiles in place of row blocks
+// fixed: the one workspace this call may use (nothing is allocated), or null for the library's own or the lent one, or with own
+// the stream's region; fixed_rows: a second one, for 128-row tiles in place of row blocks
 hipError_t launch_variant(rl_variant v, Problem& p, hipStream_t s, const char** why, rl_status* ws_status,
-                          const Workspace* fixed = nullptr, const Workspace* fixed_rows = nullptr)
+                          const Workspace* fixed = nullptr, const Workspace* fixed_rows = nullptr, bool own = false)
 {
     *ws_status = RL_OK;
     size_t need = 0;
@@ -221,6 +275,7 @@ hipError_t launch_variant(rl_variant v, Problem& p, hipStream_t s, const char** 
     else if (v == RL_MFMA_F32) need = f32_workspace_bytes(p);
     else if (v == kOddSizes) need = odd_workspace_bytes(p);
     p.ws_partial = nullptr; p.ws_sumsq = nullptr; p.ws_counter = nullptr;
+    if (need && p.no_ws) return hipErrorInvalidValue;    // no such form
     if (need) {
         Workspace ws;
         if (fixed) {
@@ -229,7 +284,9 @@ hipError_t launch_variant(rl_variant v, Problem& p, hipStream_t s, const char** 
                 : fail(RL_ERR_WORKSPACE, "the shape needs more workspace than this call's buffer holds (the scratch array of rmsnorm_linear_noalloc: 8 MiB in all)");
         } else {
             bool no_memory = false;
-            *ws_status = get_workspace(need, s, &ws, &no_memory);
+            *ws_status = !own ? get_workspace(need, s, &ws, &no_memory)
+                       : need + kHeadBytes > kRegionBytes ? fail(RL_ERR_WORKSPACE, "the shape needs more than a stream's region")
+                       : get_region(s, &ws, &no_memory);
             if (no_memory) return hipErrorOutOfMemory;
         }
         if (*ws_status != RL_OK) return *ws_status == RL_ERR_WORKSPACE ? hipErrorOutOfMemory : hipErrorUnknown;
@@ -271,21 +328,23 @@ rl_status run(Problem& p, void* stream, const Workspace* fixed = nullptr, const 
     hipStream_t s = static_cast<hipStream_t>(stream);
     tl_last_plan[0] = tl_last_plan[1] = tl_last_plan[2] = 0;
     p.plan = tl_last_plan;
-    Tuned order[8];                        // what is tried, one after the other: variant and launch shape
+    struct Step { rl_variant variant; int n_tile, k_split; bool own, without; };
+    Step order[9];                         // what is tried, one after the other; without = only in a form that needs no workspace
     int n_order = 0;
-    auto then = [&](rl_variant v, int k_split = 0) { order[n_order++] = Tuned{v, 0, k_split}; };
+    auto then = [&](rl_variant v) {
+        const bool spares = spares_workspace(v, p);
+        order[n_order++] = Step{v, 0, 0, spares, false};
+        if (spares) order[n_order++] = Step{v, 0, 0, false, true};
+    };
     if (forced != RL_AUTO) {
-        order[n_order++] = Tuned{forced, p.n_tile, p.k_split};
+        order[n_order++] = Step{forced, p.n_tile, p.k_split, false, false};
     } else {
         p.n_tile = 0;                      // tuning overrides apply to a forced variant only
         p.k_split = 0;
-        if (tuned.variant != RL_AUTO) order[n_order++] = tuned;
+        if (tuned.variant != RL_AUTO) order[n_order++] = Step{tuned.variant, tuned.n_tile, tuned.k_split, tuned.variant == kOddSizes, false};
         rl_variant first = choose_auto(p);
         if ((first == RL_MFMA_TILE && prefers_two_kernels(p)) || prefers_mid_tiles(p)) then(RL_MFMA_TILE_PRE);
-        if (first == RL_NAIVE) {
-            then(kOddSizes);
-            then(kOddSizes, 1);            // without a split, which needs no workspace
-        }
+        if (first == RL_NAIVE) then(kOddSizes);
         then(first);
         if (first == RL_MFMA_SKINNY && p.M > 64) then(RL_MFMA_TILE);   // e.g. no room for the split
         if (first != RL_NAIVE) then(RL_NAIVE);
@@ -296,8 +355,9 @@ rl_status run(Problem& p, void* stream, const Workspace* fixed = nullptr, const 
         why = "variant cannot run this shape";
         p.n_tile = order[i].n_tile;
         p.k_split = order[i].k_split;
+        p.no_ws = order[i].without;
         rl_status ws_status;
-        hipError_t e = launch_variant(v, p, s, &why, &ws_status, fixed, fixed_rows);
+        hipError_t e = launch_variant(v, p, s, &why, &ws_status, fixed, fixed_rows, order[i].own);
         if (ws_status != RL_OK) {
             // the two-kernel form is an optimisation: without room for it the fused kernel runs; a
             // tuned launch shape likewise gives way to the built-in one, and the odd-size kernel to
@@ -581,7 +641,7 @@ static rl_status autotune_core(const void* X, const void* g, const void* const* 
             if (i == 2) he = hipEventRecord(e0, s);
             p.W = Ws[i % n_w];
             plan[0] = plan[1] = plan[2] = 0;
-            hipError_t le = launch_variant(c.v, p, s, &why, &ws_status);
+            hipError_t le = launch_variant(c.v, p, s, &why, &ws_status, nullptr, nullptr, c.v == kOddSizes);
             if (ws_status != RL_OK || le == hipErrorInvalidValue) { (void)hipGetLastError(); ok = false; break; }
             if (le != hipSuccess) { result = fail(RL_ERR_HIP, "kernel launch: %s", hipGetErrorString(le)); ok = false; }
             if (i == 0) {                                           // the same launch as an earlier candidate: once is enough
@@ -680,10 +740,20 @@ static rl_status qknorm_launch(const void* Q, const void* K, const void* V, cons
 {
     float* ws = nullptr;
     unsigned* counters = nullptr;
-    const size_t need = qkattn_workspace_bytes(B, H, S, D, DType(dt), splits);
-    if (need) {
-        Workspace w;
+    size_t need = qkattn_workspace_bytes(B, H, S, D, DType(dt), splits);
+    // With a workgroup per compute unit from the heads alone, or a sequence this short, one split is a fair choice and
+    // needs no workspace: the better one takes a region of the stream's own or gives way (see get_region)
+    const bool spares = splits == 0 && need && qkattn_splits(B, H, S, D, DType(dt), 0) > 1 && (B * H >= 256 || S < 512);
+    Workspace w;
+    if (spares) {
+        bool no_memory = false;
+        rl_status st = need + kHeadBytes > kRegionBytes ? RL_ERR_WORKSPACE : get_region(s, &w, &no_memory);
+        if (st != RL_OK && st != RL_ERR_WORKSPACE && !no_memory) return st;
+        if (st != RL_OK) { splits = 1; need = 0; }
+    } else if (need) {
         if (rl_status st = get_workspace(need, s, &w)) return st;
+    }
+    if (need) {
         counters = static_cast<unsigned*>(w.ptr);
         ws = reinterpret_cast<float*>(static_cast<char*>(w.ptr) + kHeadBytes);
     }
@@ -916,7 +986,6 @@ size_t rl_workspace_bytes(int64_t M, int64_t K, int64_t N, rl_dtype dt)
         if (var == RL_MFMA_SKINNY) return skinny_workspace_bytes(q);
         if (var == RL_MFMA_TILE_PRE) return tile_pre_workspace_bytes(q);
         if (var == RL_MFMA_F32) return f32_workspace_bytes(q);
-        if (var == kOddSizes) return odd_workspace_bytes(q);
         return 0;
     };
     size_t need = 0;
@@ -924,7 +993,7 @@ size_t rl_workspace_bytes(int64_t M, int64_t K, int64_t N, rl_dtype dt)
         v = choose_auto(p);
         if (v == RL_NAIVE) v = kOddSizes;
         if ((v == RL_MFMA_TILE && prefers_two_kernels(p)) || prefers_mid_tiles(p)) v = RL_MFMA_TILE_PRE;   // optional: without it the fused kernel runs
-        need = need_of(v, p);
+        need = spares_workspace(v, p) ? 0 : need_of(v, p);
         if (tuned.variant != RL_AUTO) {        // a shape found by rl_autotune runs first: room for whichever needs more
             Problem q = p;
             q.n_tile = tuned.n_tile; q.k_split = tuned.k_split;

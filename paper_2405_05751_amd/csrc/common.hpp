@@ -20,6 +20,7 @@ struct Problem {
     const void* W;        // [K][N]
     void* Y;              // [M][N]
     int M, K, N;
+    int no_ws;            // 1: no workspace, whatever form that leaves (automatic choice)
     int ldx;              // elements from one row of X to the next; 0 = K (more only for the X-hat of the two-kernel form)
     float eps;
     int fused;            // 1: RMSNorm prologue + row scaling, 0: plain product
@@ -131,6 +132,7 @@ constexpr size_t kCounterBytes = 256 * 1024;
 constexpr size_t kSumsqBytes = 1024 * 1024;
 constexpr size_t kHeadBytes = kCounterBytes + kSumsqBytes;
 constexpr size_t kScratchBytes = size_t(8) << 20;          // the workspace of the entry point that allocates nothing
+constexpr size_t kRegionBytes = size_t(24) << 20;          // a stream's own region
 constexpr size_t kRowScratchBytes = size_t(48) << 20;      // and its workspace for 128-row tiles in place of row blocks
 constexpr int kCounterStride = 32;                         // unsigneds between two counters
 constexpr int kMaxCounters = int(kCounterBytes / sizeof(unsigned)) / kCounterStride;

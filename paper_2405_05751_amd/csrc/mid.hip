@@ -354,7 +354,7 @@ static hipError_t mid_t(const MidArgs& a, bool gated, int S, hipStream_t s)
 
 bool mid_fused(const Problem& p, int cols, int S)
 {
-    return p.fused && S == 1 && (p.dt == F16 || cols == 64) && mid_lds(cols) + mid_gain_lds(p.K) <= kMidLdsMost / (cols == 64 ? 2 : 1);
+    return p.fused && S == 1 && (p.dt == F16 || cols == 64 || p.no_ws) && mid_lds(cols) + mid_gain_lds(p.K) <= kMidLdsMost / (cols == 64 ? 2 : 1);
 }
 
 // The tile width and the split over K for the product of this problem; false: another form is the better choice, or the
@@ -388,15 +388,17 @@ bool mid_plan(const Problem& p, int* cols, int* S, int* k_slab)
     const bool skinny = skinny_row_blocks(p);    // the choice without this kernel; shorter calls than that are the host's time
     const double other = skinny ? skinny_us(p) : tile_pre_us(p);
     if (skinny && other < 16.) return false;
+    const bool split = skinny && skinny_workspace_bytes(p) != 0;
     double best = skinny ? std::min(0.87 * other, tile_pre_us(p)) : 0.85 * other;
     *cols = 0;
     for (int c = 64; c <= 128; c += 64)
         for (int s = 1; s <= 8; ++s) {
             const int ks = slab(s), real = (p.K + ks - 1) / ks;
-            if (real != s || (s > 1 && (ks < 192 || double(s) * mn * 4. > 40.)) || !fits(c, s)) continue;
+            if (real != s || (p.no_ws && !mid_fused(p, c, s)) || (s > 1 && (ks < 192 || double(s) * mn * 4. > 40.)) || !fits(c, s)) continue;
             // in place of row blocks only with what the entry point that allocates nothing has for it: both then run the
-            // same launches and give the same bits (no shape of 12 000 needs more than 43 MiB)
-            if (skinny && !mid_fused(p, c, s) && mid_workspace_bytes(p, s) > kRowScratchBytes - kHeadBytes) continue;
+            // same launches and give the same bits (no shape of 12 000 needs more than 43 MiB); where the row blocks are not
+            // split, and so need no workspace, with what a stream's region holds (none needs more than 23 MiB)
+            if (skinny && !mid_fused(p, c, s) && mid_workspace_bytes(p, s) + kHeadBytes > (split ? kRowScratchBytes : kRegionBytes)) continue;
             const int64_t tiles_n = p.gated && s == 1 ? (p.N / 2 + c / 2 - 1) / (c / 2) : (p.N + c - 1) / c;
             const double rounds = double((tiles_m * tiles_n * s + 255) / 256), kt = double((ks + kMidK - 1) / kMidK);
             const double run = c == 128 ? rounds * (4.1 + 0.62 * kt)

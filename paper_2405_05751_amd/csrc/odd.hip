@@ -406,7 +406,7 @@ static OddPlan odd_plan(const Problem& p)
     auto slab_fits = [&](int s) { return (int64_t(64) * ((runs + s - 1) / s) + 2048) * p.N * 2 < (int64_t(1) << 31); };
     auto partial_bytes = [&](int s) { return s > 1 ? size_t(pl.RB) * s * Mb * pl.ldp * 4 : size_t(0); };
     // a split needs one run per wave, room for counters and sums of squares, and partials that fit the smallest
-    // workspace there is, so that every entry point takes the same one; k_split = 1 is the launch that needs none
+    // workspace there is, so that every entry point takes the same one
     auto may_split = [&](int s) {
         return int64_t(s) * kOddWaves <= runs && blocks <= kMaxCounters && blocks * s * kSumsqStride <= kMaxSumsqFloats &&
                partial_bytes(s) <= kScratchBytes - kHeadBytes;
@@ -414,7 +414,7 @@ static OddPlan odd_plan(const Problem& p)
     // slabs: the skinny kernel's cost model (see skinny_plan, where its constants come from)
     double best = 0.;
     for (int s = 1; s <= 16; ++s) {
-        if (!slab_fits(s) || (s > 1 && (!may_split(s) || p.k_split == 1))) continue;
+        if (!slab_fits(s) || (s > 1 && (!may_split(s) || p.no_ws))) continue;
         const double wgs = double(blocks) * s;
         const double wg_bytes = 64.0 * ((runs + s - 1) / s) * (kOddTile * 2.0 + Mb * 2.0);
         const double hbm_us = double(p.K) * p.N * 2.0 / 6.5e6;

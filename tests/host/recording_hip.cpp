@@ -96,6 +96,7 @@ int hipGetSymbolAddress(void** p, const void* symbol)
     return 0;
 }
 int hipStreamIsCapturing(void* s, int* status) { std::lock_guard<std::recursive_mutex> l(mu); *status = capturing.count(s) ? 1 : 0; return 0; }
+int hipThreadExchangeStreamCaptureMode(int* mode) { static thread_local int now = 0; const int was = now; now = *mode; *mode = was; return 0; }
 int hipEventCreate(void** e) { *e = e; return 0; }
 int hipEventDestroy(void*) { return 0; }
 int hipEventRecord(void*, void*) { return 0; }

@@ -21,11 +21,11 @@ def test_failed_allocation():
     out = routes.run("""
 rec.rec_fail_mallocs(100)
 print(linear(8, 4096, 3001), names(), last()[2])                 # a split over K gives way to none
-print(linear(300, 1024, 10000), names())                         # X-hat in the workspace to row blocks
+print(linear(300, 1024, 10000), names())                         # X-hat in the workspace to tiles that form it themselves
 print(linear(1, 4096, 4096), names(), b"hipMalloc" in lib.rl_last_error())
 print(rec.hipGetLastError())
 """)
-    assert out == ["0 ['odd_kernel'] 1", "0 ['skinny_kernel']", "3 [] True", "0"]
+    assert out == ["0 ['odd_kernel'] 1", "0 ['mid_kernel']", "3 [] True", "0"]
 
 
 @pytest.mark.parametrize("M,K,N,dt", [(300, 1024, 10000, "F16"), (89, 1280, 12712, "BF16"), (1914, 664, 624, "BF16"), (654, 2392, 4352, "F16")])
@@ -60,3 +60,48 @@ for n in range(6000):
 print(ran > 2000)
 """)
     assert out == ["True"]
+
+
+# calls that could do without a workspace and are faster with one: (call, kernel, which word of its argument is the workspace)
+SPARING = {
+    "odd sizes, split": ("linear(8, 4095, 3001, BF16, {s})", "odd_kernel", (9, 32, 3), "lib.rl_workspace_bytes(8, 4095, 3001, BF16)"),
+    "X-hat": ("linear(300, 1024, 10000, BF16, {s})", "xhat_rows_kernel", (2, 8, 0), "lib.rl_workspace_bytes(300, 1024, 10000, BF16)"),
+    "attention, many heads": ("qknorm(8, 40, 4096, 128, BF16, {s})", "qkattn_kernel", (0, 72, 8), "0"),
+    "attention, short sequence": ("qknorm(1, 32, 300, 128, BF16, {s})", "qkattn_kernel", (0, 72, 8), "0"),
+}
+
+
+@pytest.mark.parametrize("what", SPARING)
+def test_streams_share_nothing(what):
+    """Every stream has memory of its own for them, apart from the shared workspace too; without any (under capture, while a
+    buffer is lent, too many streams, the handle that means another stream in every thread) the form that needs none runs."""
+    call, kernel, (arg, size, word), query = SPARING[what]
+    out = routes.run(f"""
+rec.rec_watch(b"{kernel}", {arg}, {size})
+def place(s):
+    st = {call.format(s="s")}
+    assert st == 0, lib.rl_last_error()
+    got = [l for l in launches() if l.name == "{kernel}"]
+    return got[0].words[{word}] if got and got[0].words[{word}] else 0
+linear(1, 4096, 4096, BF16, 0)
+shared_mallocs, shared_bytes = rec.rec_mallocs(), rec.rec_malloc_bytes()
+at = [place(s) for s in (0, 5, 6, 5, 0)]
+print(0 in at, at[3] == at[1], at[4] == at[0], len(set(at)) == 3, min(abs(a - b) for a in at for b in at if a != b) >= 4 << 20)
+shared = (1 << 40, (1 << 40) + shared_bytes)
+print([shared[0] <= a < shared[1] for a in at])
+rec.rec_capture(V(5), 1)
+print(place(5) != 0, rec.rec_mallocs() - shared_mallocs)
+rec.rec_capture(V(5), 0)
+print(place(2))
+many = [place(100 + i) for i in range(40)]
+print(len(set(many)), many[-1], rec.rec_malloc_bytes() - shared_bytes <= 16 * (24 << 20), place(6) == at[2])
+lib.rl_set_workspace(V(1 << 43), 1 << 28)
+print(place(6), place(7))
+print({query})
+""")
+    assert out[:2] == ["False True True True True", "[False, False, False, False, False]"]
+    assert out[2] == "False 3"
+    assert out[3] == "0"
+    assert out[4] == "14 0 True True"                    # 13 regions were left; the rest goes without
+    assert out[5] == "0 0"
+    assert out[6] == "0"
