@@ -24,6 +24,9 @@ thread_local rl_variant tl_last_variant = RL_AUTO;
 thread_local int tl_last_plan[3] = {0, 0, 0};
 
 std::mutex g_mu;
+// Held while the kernels of a call that pass data through a workspace are enqueued: another thread's call on the same
+// stream, with the same workspace, must not come in between (one kernel by itself is in order there)
+std::mutex g_enqueue;
 bool g_env_read = false;
 rl_variant g_variant = RL_AUTO;
 int g_n_tile = 0, g_k_split = 0;
@@ -292,6 +295,8 @@ hipError_t launch_variant(rl_variant v, Problem& p, hipStream_t s, const char** 
         if (*ws_status != RL_OK) return *ws_status == RL_ERR_WORKSPACE ? hipErrorOutOfMemory : hipErrorUnknown;
         carve(ws, p);
     }
+    std::unique_lock<std::mutex> several(g_enqueue, std::defer_lock);
+    if (need && v == RL_MFMA_TILE_PRE) several.lock();
     switch (v) {
     case RL_GEMV_SPLITK: return launch_gemv(p, s, why);
     case RL_MFMA_SKINNY: return launch_skinny(p, s, why);
@@ -757,6 +762,8 @@ static rl_status qknorm_launch(const void* Q, const void* K, const void* V, cons
         counters = static_cast<unsigned*>(w.ptr);
         ws = reinterpret_cast<float*>(static_cast<char*>(w.ptr) + kHeadBytes);
     }
+    std::unique_lock<std::mutex> several(g_enqueue, std::defer_lock);
+    if (need) several.lock();                            // (a second kernel merges the splits of more heads than there are counters)
     hipError_t e = launch_qkattn(Q, K, V, gq, bq, gk, bk, eps, O, B, H, S, D, DType(dt), ws, counters, splits, s);
     if (e != hipSuccess) return fail(RL_ERR_HIP, "kernel launch: %s", hipGetErrorString(e));
     return RL_OK;

@@ -4,6 +4,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
+#include <unistd.h>
 #include <map>
 #include <mutex>
 #include <set>
@@ -20,7 +21,7 @@ std::set<void*> capturing;
 std::vector<Watch> watched;
 std::string log_text;
 uintptr_t next_address = uintptr_t(1) << 40;
-int fail_mallocs = 0, mallocs = 0;
+int fail_mallocs = 0, mallocs = 0, launch_pause_us = 0;
 size_t malloc_bytes = 0;
 thread_local std::vector<Config> configs;
 thread_local int last_error = 0;
@@ -30,6 +31,7 @@ int error(int e) { if (e) last_error = e; return e; }
 extern "C" {
 // ---- what a test sets and reads
 void rec_capture(void* stream, int on) { std::lock_guard<std::recursive_mutex> l(mu); if (on) capturing.insert(stream); else capturing.erase(stream); }
+void rec_launch_pause(int us) { launch_pause_us = us; }
 void rec_fail_mallocs(int n) { fail_mallocs = n; }
 int rec_mallocs() { return mallocs; }
 size_t rec_malloc_bytes() { return malloc_bytes; }
@@ -55,6 +57,7 @@ int __hipPopCallConfiguration(Dim* grid, Dim* block, size_t* lds, void** stream)
 }
 int hipLaunchKernel(const void* fn, Dim grid, Dim block, void** args, size_t lds, void* stream)
 {
+    if (launch_pause_us) usleep(launch_pause_us);        // (outside the lock: other threads' launches may come in between)
     if (uint64_t(grid.x) * block.x >= (uint64_t(1) << 32) || block.x > 1024 || grid.x == 0) return error(9);
     std::lock_guard<std::recursive_mutex> l(mu);
     const std::string& n = names()[fn];

@@ -105,3 +105,26 @@ print({query})
     assert out[4] == "14 0 True True"                    # 13 regions were left; the rest goes without
     assert out[5] == "0 0"
     assert out[6] == "0"
+
+
+@pytest.mark.parametrize("call,kernels", [
+    ("linear(300, 1024, 10000, BF16, 5)", ["xhat_rows_kernel", "mid_kernel"]),
+    ("linear(245, 992, 2496, BF16, 5)", ["xhat_rows_kernel", "mid_kernel", "tile_reduce_kernel"]),
+    ("linear(4096, 4096, 4096, BF16, 5)", ["xhat_rows_kernel", "tile_kernel"]),
+    ("linear(300, 1024, 10000, BF16, 5, 'rmsnorm_linear_noalloc')", ["xhat_rows_kernel", "mid_kernel"]),
+])
+def test_two_threads_on_one_stream(call, kernels):
+    """The kernels of a call that pass data through a workspace are enqueued together."""
+    out = routes.run(f"""
+{call}
+rec.rec_take()
+rec.rec_launch_pause(300)
+def work():
+    for i in range(30):
+        assert {call} == 0
+threads = [threading.Thread(target=work) for i in range(3)]
+for t in threads: t.start()
+for t in threads: t.join()
+print(names() == {kernels} * 90)
+""")
+    assert out == ["True"]
