@@ -372,8 +372,8 @@ bool mid_plan(const Problem& p, int* cols, int* S, int* k_slab)
     if (int64_t(kMidM) * (int64_t(p.K) + 64) * 2 >= (int64_t(1) << 31) || p.N >= (1 << 22)) return false;
     const int64_t tiles_m = (int64_t(p.M) + kMidM - 1) / kMidM;
     auto slab = [&](int s) { return ((p.K + s - 1) / s + kMidK - 1) / kMidK * kMidK; };
-    auto fits = [&](int c, int s) {              // byte offsets into a slab of W; the grid
-        return (int64_t(slab(s)) + 512) * p.N * 2 < (int64_t(1) << 31) && tiles_m * ((p.N + c - 1) / c + 1) * s < (int64_t(1) << 31);
+    auto fits = [&](int c, int s) {              // byte offsets into a slab of W; a grid holds fewer than 2^32 threads, 512 to a tile
+        return (int64_t(slab(s)) + 512) * p.N * 2 < (int64_t(1) << 31) && tiles_m * ((p.N + c - 1) / c + 1) * s < (int64_t(1) << 23);
     };
     if (p.n_tile == 64 || p.n_tile == 128) {
         const int s = p.k_split >= 1 && p.k_split <= 16 ? p.k_split : 1;

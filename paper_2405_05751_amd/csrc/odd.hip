@@ -424,7 +424,7 @@ static OddPlan odd_plan(const Problem& p)
         if (pl.S == 0 || t < best) { best = t; pl.S = s; }
     }
     if (pl.S == 0) { pl.why = "the odd-size variant cannot address a slab of this W"; return pl; }
-    if (blocks * pl.S >= (int64_t(1) << 31)) { pl.why = "too many workgroups"; return pl; }
+    if (blocks * pl.S >= (int64_t(1) << 24)) { pl.why = "too many workgroups"; return pl; }     // (a grid holds fewer than 2^32 threads)
     pl.lds = size_t(kOddWaves) * 16 * pl.MB * 128 * 4;
     pl.bytes = partial_bytes(pl.S);
     pl.ok = true;

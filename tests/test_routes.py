@@ -128,3 +128,12 @@ for t in threads: t.join()
 print(names() == {kernels} * 90)
 """)
     assert out == ["True"]
+
+
+@pytest.mark.parametrize("M,K,N,dt", [(1443343563, 8, 16, "F16"), (1177524770, 24, 32, "F16"), (2056937954, 16, 56, "BF16")])
+def test_most_rows(M, K, N, dt):
+    """No launch of more threads than a grid may hold (the recorder refuses those, as HIP does)."""
+    out = routes.run(f"""
+print(linear({M}, {K}, {N}, {dt}), len(launches()) > 0)
+""")
+    assert out == ["0 True"]
