@@ -310,8 +310,7 @@ rl_status rl_qknorm_attention(const void* Q, const void* K, const void* V, const
  * through n_copies DEVICE copies of K and V (host arrays of device pointers; one copy times the cache-warm
  * case).  The fastest is remembered for (B H, S, D, dt) and used by later rl_qknorm_attention calls of that
  * shape unless rl_set_tuning forces a count; rl_autotune_clear forgets it.  *best_splits (may be NULL)
- * receives the number of splits chosen, *best_us its time per launch.  Shapes that run the plain kernel, and
- * sequences of fewer than 128 positions at a D other than 64, 128 and 256, have
+ * receives the number of splits chosen, *best_us its time per launch.  Shapes that run the plain kernel have
  * nothing to search: RL_OK, *best_splits = 0.  O is overwritten by every candidate.  Synchronises with the
  * stream (it waits on its events).
  */

@@ -800,8 +800,6 @@ rl_status rl_autotune_qknorm(const void* Q, const void* const* K_copies, const v
     if (best_us) *best_us = 0.f;
     const int automatic = qkattn_splits(B, H, S, D, DType(dt), 0);
     if (automatic == 0) return RL_OK;                    // the plain kernel has no launch shape to search
-    // (nor has a sequence too short for a second split; D = 64, 128, 256 are timed all the same and report their one)
-    if (S < 128 && D != 64 && D != 128 && D != 256) return RL_OK;
     // every split count that leaves at least 64 positions to a split; counts that round to the same
     // number of splits are launched once; the library's own rule goes first and wins ties
     std::vector<int> cands{0};

@@ -117,10 +117,15 @@ def test_split_tuner(rl):
         finally:
             rl.rl_autotune_clear()
         _check(rl, c, "bf16", 1e-5, f"after forgetting, D = {D}")
-    c = workloads.make_attention(1, 2, 100, 80, "f16", 9810)
-    dev = {k: to_device(v, "f16") for k, v in c.items()}
-    O = torch.empty_like(dev["Q"])
-    assert rl.rl_autotune_qknorm(dev["Q"], [dev["K"]], [dev["V"]], dev["gq"], dev["bq"], dev["gk"], dev["bk"], 1e-5, O)[0] == 0
+    for D, splits in ((80, 1), (64, 1), (81, 0)):         # too short for a second split; and the plain kernel
+        c = workloads.make_attention(1, 2, 100, D, "f16", 9810)
+        dev = {k: to_device(v, "f16") for k, v in c.items()}
+        O = torch.empty_like(dev["Q"])
+        args = dev["Q"], [dev["K"]], [dev["V"]], dev["gq"], dev["bq"], dev["gk"], dev["bk"], 1e-5, O
+        try:
+            assert rl.rl_autotune_qknorm(*args)[0] == splits, D
+        finally:
+            rl.rl_autotune_clear()
     with pytest.raises(rl.RmsnlError):
         rl.rl_autotune_qknorm(dev["Q"], [dev["K"]], [dev["V"]], dev["gq"], dev["bq"], dev["gk"], dev["bk"], 1e-5, O, reps=0)
 
