@@ -45,9 +45,8 @@ typedef enum { RL_F16 = 0, RL_BF16 = 1, RL_F32 = 2 } rl_dtype;
 
 typedef enum {
     RL_AUTO = 0,          /* pick by shape: fp32: its matrix-core kernel, or the plain kernel for what that one does not run.  K or N not
-                             a multiple of 8: the skinny kernel's form for any sizes (reported as RL_NAIVE, with 128 columns
-                             by rl_last_launch; without room for its partial sums it is not split; the plain kernel for K <= 96 with M N <= 131072, for
-                             matmul, and for the gated block, there also with N not a multiple of 16).  Else GEMV
+                             a multiple of 8: RL_NAIVE's form with 128 columns (without room for its partial sums it is not split; the
+                             plain kernel for K <= 96 with M N <= 131072, for matmul, and for the gated block, there also with N not a multiple of 16).  Else GEMV
                              for M = 1 and N < 10240, and for M <= 4 while K N <= 6e6; M <= 64 skinny, and up to M = 1024 while
                              ceil(M / 64) K N <= 1.4e8 (0.9e8 for N > 6144 and M > 128); else the two-kernel tile form (above 64 rows also where
                              its 128-row tiles are estimated to be clearly ahead), or the
@@ -61,7 +60,10 @@ typedef enum {
     RL_MFMA_TILE = 3,     /* 16-bit types, large M: 256x256 (or 128x512) output tiles on matrix cores, one fused kernel; K < 2^22,
                              N < 2^25; a W of 2 GiB or more is addressed row by row */
     RL_NAIVE = 4,         /* any shape and type, slow (no matrix cores, no split over workgroups): fp32 arithmetic for the
-                             16-bit types, fp64 accumulation for fp32 */
+                             16-bit types, fp64 accumulation for fp32.  With 128 columns (rl_set_tuning, rl_launch_opts; so reported by
+                             rl_last_launch and rl_autotune_get): the fused block in the 16-bit types at any K and N on the matrix
+                             cores, the skinny kernel's form for rows that start at any element; K <= 2^23, W of a slab below
+                             2 GiB, K split over the waves and into 1 to 16 slabs over workgroups */
     RL_MFMA_TILE_PRE = 5, /* M > 64: X (.) g and 1/rms written once by a first kernel (workspace of 2 M K + 4 M bytes, rows of K
                              rounded up to 64), then the tile kernel as a product scaled per row; with few 256x256 tiles the product
                              is split over K into fp32 partials (up to 64 MiB more) that a third kernel adds up, or runs on tiles
@@ -69,7 +71,8 @@ typedef enum {
                              64 columns, 16384 at 128; bf16: K <= 4096 at 64), without a first kernel and without a workspace */
     RL_MFMA_F32 = 6       /* fp32 only, any M, K % 4 == 0 and N % 4 == 0, W below 4 GiB: matrix cores on fp32 operands
                              (fp32 products and sums, two levels of accumulators), 64 rows x 64 columns per workgroup,
-                             K split over its waves and into 1 to 16 slabs over workgroups */
+                             K split over its waves and into 1 to 16 slabs over workgroups; where they fill the chip and K is 192 to
+                             4096, 128 x 128 tiles through LDS instead (rl_last_launch: 128 columns), unless a shape is forced */
 } rl_variant;
 
 /*
@@ -123,8 +126,9 @@ size_t rl_noalloc_scratch_bytes(void);
  *   struct_size    sizeof(rl_launch_opts), checked
  *   variant        RL_AUTO or a forced variant (then no fallback, as with rl_set_variant)
  *   columns        GEMV: columns of W per workgroup, 64, 128, 256 or 512; skinny: a multiple of 8 up to 128; fp32: 64;
- *                  fused tile kernel: 256 (256 x 256 tiles) or 512 (128 x 512 tiles)
- *   slabs          K slabs: GEMV, skinny and fp32 (1..16), and the product of the two-kernel tile form (1 = unsplit)
+ *                  fused tile kernel: 256 (256 x 256 tiles) or 512 (128 x 512 tiles); two-kernel tile form: 64 or 128 for
+ *                  tiles of 128 rows (others: 256 x 256); RL_NAIVE: 128 for its matrix-core form
+ *   slabs          K slabs: GEMV, skinny, fp32 and RL_NAIVE's matrix-core form (1..16), and the product of the two-kernel tile form (1 = unsplit)
  *   waves          fused tile kernel: waves per workgroup, 4 or 8
  *   rem_slabs      two-kernel tile form: K slabs for the tiles left over after the last full round of 256
  *   workspace      DEVICE buffer of workspace_bytes for this call alone (16-byte aligned, its first 256 KiB
@@ -222,7 +226,9 @@ rl_variant rl_last_variant(void);
  *           the waves per workgroup (4 or 8); for the two-kernel tile variant n_tile = 1 makes k_split
  *           (1 to 16) the number of K slabs of its product (1 = no split; otherwise the library splits
  *           when the 256x256 tiles are too few to fill the chip), and n_tile = 2 makes k_split the number
- *           of slabs for the tiles left over after the last full round of 256 (1 = no such split).
+ *           of slabs for the tiles left over after the last full round of 256 (1 = no such split); n_tile = 64 or 128 asks for
+ *           tiles of 128 rows and that many columns, in k_split (0 to 16; 0 = 1) slabs; for RL_NAIVE n_tile = 128 asks for its
+ *           matrix-core form, in k_split slabs (0 to 16).
  *           For rl_qknorm_attention k_split is the number of splits of the sequence (at least 64 positions each).
  * Values a variant cannot honour give RL_ERR_UNSUPPORTED at the next call.
  */
@@ -249,7 +255,8 @@ rl_status rl_ntrans(const void* X, const void* H, const void* alpha, float eps, 
  * rl_autotune runs every launch shape the library has for the call, generated from the shape
  * (variant x columns per workgroup x every K slab count that leaves each lane group a batch of rows,
  * launches that come out the same timed once; tile shape x waves per workgroup for the tile
- * variant; the two-kernel form with and without its K split) on the caller's own device
+ * variant; the two-kernel form with and without its K split, and on 128-row tiles of either width in 1 to 8 slabs;
+ * RL_NAIVE's matrix-core form in every number of slabs where K or N is no multiple of 8) on the caller's own device
  * buffers: two warm-up launches, then `reps` (1..1000) timed ones between HIP events on `stream`.
  * The fastest is remembered for (M, K, N, dt, gated) and used by later RL_AUTO calls of exactly
  * that shape; forced variants are not affected; a tuned shape that finds no room in the workspace

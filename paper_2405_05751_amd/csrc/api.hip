@@ -217,10 +217,15 @@ rl_status get_region(hipStream_t s, Workspace* out, bool* no_memory)
     return RL_OK;
 }
 
-// The matrix-core kernel for sizes that are no multiple of eight: not a choice of the caller's but what RL_AUTO
-// runs in place of the plain kernel where it can.  Reported as RL_NAIVE, which is what a caller may force there.
+// The matrix-core kernel for sizes that are no multiple of eight: what RL_AUTO runs there in place of the plain kernel.  To the
+// caller it is the form of RL_NAIVE with 128 columns: reported as that, and asked for as that.
 constexpr rl_variant kOddSizes = rl_variant(7);
+constexpr int kOddColumns = 128;
 rl_variant public_variant(rl_variant v) { return v == kOddSizes ? RL_NAIVE : v; }
+rl_variant with_columns(rl_variant v, const Problem& p)
+{
+    return v == RL_NAIVE && p.n_tile == kOddColumns && p.fused && !p.gated && p.dt != F32 ? kOddSizes : v;
+}
 
 rl_variant choose_auto(const Problem& p)
 {
@@ -342,7 +347,7 @@ rl_status run(Problem& p, void* stream, const Workspace* fixed = nullptr, const 
         if (spares) order[n_order++] = Step{v, 0, 0, false, true};
     };
     if (forced != RL_AUTO) {
-        order[n_order++] = Step{forced, p.n_tile, p.k_split, false, false};
+        order[n_order++] = Step{with_columns(forced, p), p.n_tile, p.k_split, false, false};
     } else {
         p.n_tile = 0;                      // tuning overrides apply to a forced variant only
         p.k_split = 0;
@@ -361,6 +366,7 @@ rl_status run(Problem& p, void* stream, const Workspace* fixed = nullptr, const 
         p.n_tile = order[i].n_tile;
         p.k_split = order[i].k_split;
         p.no_ws = order[i].without;
+        p.forced = forced != RL_AUTO;
         rl_status ws_status;
         hipError_t e = launch_variant(v, p, s, &why, &ws_status, fixed, fixed_rows, order[i].own);
         if (ws_status != RL_OK) {
@@ -428,10 +434,11 @@ static rl_status translate_opts(const rl_launch_opts* o, CallOpts* c, Workspace*
         return fail(RL_ERR_INVALID_ARG, "launch options must be >= 0");
     c->variant = o->variant;
     switch (o->variant) {
-    case RL_GEMV_SPLITK: case RL_MFMA_SKINNY: case RL_MFMA_F32: c->n_tile = o->columns; c->k_split = o->slabs; break;
+    case RL_GEMV_SPLITK: case RL_MFMA_SKINNY: case RL_MFMA_F32: case RL_NAIVE: c->n_tile = o->columns; c->k_split = o->slabs; break;
     case RL_MFMA_TILE: c->n_tile = o->columns; c->k_split = o->waves; break;
     case RL_MFMA_TILE_PRE:
-        if (o->slabs) { c->n_tile = 1; c->k_split = o->slabs; }
+        if (o->columns == 64 || o->columns == 128) { c->n_tile = o->columns; c->k_split = o->slabs; }     // 128-row tiles
+        else if (o->slabs) { c->n_tile = 1; c->k_split = o->slabs; }
         else if (o->rem_slabs) { c->n_tile = 2; c->k_split = o->rem_slabs; }
         break;
     default: break;
@@ -615,10 +622,14 @@ static rl_status autotune_core(const void* X, const void* g, const void* const* 
                 for (int nw : {4, 8}) cands.push_back({RL_MFMA_TILE, shape, nw});
         if (M > 64)                        // two-kernel form: the library's own K split, none, 2 to 16 slabs
             for (int ks : {0, 1, 2, 4, 8, 16}) cands.push_back({RL_MFMA_TILE_PRE, ks ? 1 : 0, ks});
+        if (M > 64)                        // and on 128-row tiles
+            for (int nt : {64, 128})
+                for (int ks = 1; ks <= 8; ++ks) cands.push_back({RL_MFMA_TILE_PRE, nt, ks});
+        if (K % 8 || N % 8)
+            for (int ks = 0; ks <= 16; ++ks) cands.push_back({kOddSizes, kOddColumns, ks});
     }
     if (dt == RL_F32)
         for (int ks = 0; ks <= 16; ++ks) cands.push_back({RL_MFMA_F32, 0, ks});
-    cands.push_back({kOddSizes, 0, 0});
     cands.push_back({RL_NAIVE, 0, 0});
 
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -991,6 +1002,7 @@ size_t rl_workspace_bytes(int64_t M, int64_t K, int64_t N, rl_dtype dt)
         if (var == RL_MFMA_SKINNY) return skinny_workspace_bytes(q);
         if (var == RL_MFMA_TILE_PRE) return tile_pre_workspace_bytes(q);
         if (var == RL_MFMA_F32) return f32_workspace_bytes(q);
+        if (var == kOddSizes) return odd_workspace_bytes(q);
         return 0;
     };
     size_t need = 0;
@@ -1002,10 +1014,10 @@ size_t rl_workspace_bytes(int64_t M, int64_t K, int64_t N, rl_dtype dt)
         if (tuned.variant != RL_AUTO) {        // a shape found by rl_autotune runs first: room for whichever needs more
             Problem q = p;
             q.n_tile = tuned.n_tile; q.k_split = tuned.k_split;
-            need = std::max(need, need_of(tuned.variant, q));
+            if (tuned.variant != kOddSizes) need = std::max(need, need_of(tuned.variant, q));    // (that one: its stream's region)
         }
     } else {
-        need = need_of(v, p);
+        need = need_of(with_columns(v, p), p);
     }
     return need ? need + kHeadBytes : 0;
 }

@@ -20,6 +20,7 @@ struct Problem {
     const void* W;        // [K][N]
     void* Y;              // [M][N]
     int M, K, N;
+    int forced;           // 1: the caller asked for this variant
     int no_ws;            // 1: no workspace, whatever form that leaves (automatic choice)
     int ldx;              // elements from one row of X to the next; 0 = K (more only for the X-hat of the two-kernel form)
     float eps;

@@ -376,7 +376,8 @@ bool mid_plan(const Problem& p, int* cols, int* S, int* k_slab)
         return (int64_t(slab(s)) + 512) * p.N * 2 < (int64_t(1) << 31) && tiles_m * ((p.N + c - 1) / c + 1) * s < (int64_t(1) << 23);
     };
     if (p.n_tile == 64 || p.n_tile == 128) {
-        const int s = p.k_split >= 1 && p.k_split <= 16 ? p.k_split : 1;
+        const int s = std::max(p.k_split, 1);
+        if (s > 16) return false;
         *cols = p.n_tile;
         *k_slab = slab(s);
         *S = (p.K + *k_slab - 1) / *k_slab;

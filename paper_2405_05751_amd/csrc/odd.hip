@@ -393,7 +393,7 @@ static OddPlan odd_plan(const Problem& p)
     if (p.dt == F32 || !p.fused || p.gated) { pl.why = "the odd-size variant runs the fused block in the 16-bit types only"; return pl; }
     // a few dozen k and at most one plain workgroup to a place on the chip: nothing to stream, and the plain kernel's
     // single launch is ahead (1 x 64 x 1001 fp16: 8.9 us, 13.1 us here; at K = 128 12.8 and 13.4, at 300 26.6 and 12.4)
-    if (p.K <= 96 && int64_t(p.M) * p.N <= (1 << 17)) { pl.why = "too small for the odd-size variant"; return pl; }
+    if (!p.forced && p.K <= 96 && int64_t(p.M) * p.N <= (1 << 17)) { pl.why = "too small for the odd-size variant"; return pl; }
     if (p.K > (1 << 23) || p.N > (1 << 30)) { pl.why = "the odd-size variant needs K <= 2^23 and N <= 2^30"; return pl; }     // (64 rows of X below 2^31 bytes)
     pl.ldp = (p.N + 3) / 4 * 4;
     pl.n_tiles = (p.N + kOddTile - 1) / kOddTile;
@@ -412,8 +412,10 @@ static OddPlan odd_plan(const Problem& p)
                partial_bytes(s) <= kScratchBytes - kHeadBytes;
     };
     // slabs: the skinny kernel's cost model (see skinny_plan, where its constants come from)
+    if (p.n_tile != 0 && p.n_tile != kOddTile) { pl.why = "odd-size variant: tiles of 128 columns"; return pl; }
+    if (p.k_split > 16) { pl.why = "odd-size variant: 1 to 16 slabs"; return pl; }
     double best = 0.;
-    for (int s = 1; s <= 16; ++s) {
+    for (int s = std::max(1, p.k_split); s <= (p.k_split ? p.k_split : 16); ++s) {
         if (!slab_fits(s) || (s > 1 && (!may_split(s) || p.no_ws))) continue;
         const double wgs = double(blocks) * s;
         const double wg_bytes = 64.0 * ((runs + s - 1) / s) * (kOddTile * 2.0 + Mb * 2.0);
@@ -423,7 +425,7 @@ static OddPlan odd_plan(const Problem& p)
         const double t = std::max(hbm_us, unit_us) + 0.15 * std::min(hbm_us, unit_us) + tail_us;
         if (pl.S == 0 || t < best) { best = t; pl.S = s; }
     }
-    if (pl.S == 0) { pl.why = "the odd-size variant cannot address a slab of this W"; return pl; }
+    if (pl.S == 0) { pl.why = "the odd-size variant cannot split this W so, or not address a slab of it"; return pl; }
     if (blocks * pl.S >= (int64_t(1) << 24)) { pl.why = "too many workgroups"; return pl; }     // (a grid holds fewer than 2^32 threads)
     pl.lds = size_t(kOddWaves) * 16 * pl.MB * 128 * 4;
     pl.bytes = partial_bytes(pl.S);

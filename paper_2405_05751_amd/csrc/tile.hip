@@ -858,6 +858,10 @@ hipError_t launch_tile_pre(const Problem& p, hipStream_t s, const char** why)
     }
     int S, k_slab, cols = 0;
     const bool mid = mid_plan(p, &cols, &S, &k_slab);
+    if (p.fused && (p.n_tile == 64 || p.n_tile == 128) && !mid) {
+        if (why) *why = "128-row tiles: 1 to 16 slabs, K < 2^23, N < 2^22, and a slab of W below 2 GiB";
+        return hipErrorInvalidValue;
+    }
     if (!mid) {
         tile_pre_split(p, &S, &k_slab);
         int full, rem, RS, rks;

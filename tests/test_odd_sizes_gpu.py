@@ -144,3 +144,19 @@ def test_no_room_runs_unsplit(rl):
     finally:
         rl.rl_set_workspace(None)
     _check(to_host_f64(Y, "bf16"), Z, "bf16", "no room")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("M,K,N,slabs", [(1, 1, 3, 0), (2, 3, 2, 0), (9, 7, 250, 1), (65, 64, 127, 0), (5, 96, 64, 0), (8, 512, 512, 2), (70, 1032, 264, 4),
+                                         (24, 2051, 1001, 8)])
+def test_asked_for(rl, M, K, N, slabs, dtype):
+    """Asked for by its columns: also at sizes where the automatic choice is another, and in a given number of slabs."""
+    import torch
+    w = workloads.make(M, K, N, dtype, 1e-5, 5600 + M + K + N)
+    X, g, W = upload(w)
+    Y = rl.rmsnorm_linear_ex(X, g, W, w.eps, variant="naive", columns=128, slabs=slabs)
+    torch.cuda.synchronize()
+    used = rl.rl_last_launch()
+    assert used[:2] == ("naive", 128) and (slabs == 0 or used[2] == slabs)
+    Z = oracle.rmsnorm_linear(w.X, w.g, w.W, w.dtype, w.eps)
+    _check(to_host_f64(Y, dtype), Z, dtype, f"{M}x{K}x{N} {dtype} in {slabs} slabs")

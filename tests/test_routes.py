@@ -137,3 +137,57 @@ def test_most_rows(M, K, N, dt):
 print(linear({M}, {K}, {N}, {dt}), len(launches()) > 0)
 """)
     assert out == ["0 True"]
+
+
+def test_odd_size_kernel_can_be_asked_for():
+    """RL_NAIVE with 128 columns: so it is reported, so it runs when it is asked for (aligned and tiny sizes too, in a given number of
+    slabs), and a choice of the tuner's that is played back is the launch that was timed."""
+    out = routes.run("""
+NAIVE = 4
+print(linear(24, 4096, 32003), last()[:2])
+lib.rl_set_variant(NAIVE)
+lib.rl_set_tuning(128, 3)
+print(linear(8, 4096, 3000), last()[:3], linear(2, 64, 100), linear(8, 4096, 3001, F32), last()[:2])
+lib.rl_set_tuning(128, 17)
+print(linear(8, 4096, 3001))
+lib.rl_set_tuning(0, 0)
+print(linear(8, 4096, 3001), last()[:2])
+lib.rl_set_variant(0)
+lib.rl_set_tuning(0, 0)
+lib.rl_autotune.argtypes = [V, V, V, F, V, L, L, L, I, I, I, V, V]
+rec.rec_take()
+assert lib.rl_autotune(P[0], P[1], P[2], 1e-5, P[3], 8, 4095, 3001, BF16, 0, 1, None, None) == 0
+tried = {l.grid for l in launches() if l.name == "odd_kernel"}
+print(sorted(g // 24 for g in tried) == list(range(1, 17)))
+v, nt, ks = I(), I(), I()
+lib.rl_autotune_get.argtypes = [L, L, L, I, I, V, V, V]
+lib.rl_autotune_get(8, 4095, 3001, BF16, 0, *[ctypes.byref(x) for x in (v, nt, ks)])
+linear(8, 4095, 3001)
+tuned = [(l.name, l.grid) for l in launches()][-1]
+lib.rl_autotune_clear()
+lib.rl_set_variant(v.value)
+lib.rl_set_tuning(nt.value, ks.value)
+linear(8, 4095, 3001)
+print((v.value, nt.value), tuned[0], tuned == [(l.name, l.grid) for l in launches()][-1])
+""")
+    assert out == ["0 (4, 128)", "0 (4, 128, 3) 2 0 (4, 0)", "2", "0 (4, 0)", "True", "(4, 128) odd_kernel True"]
+
+
+def test_widths_of_128_row_tiles():
+    """The tuner tries both in 1 to 8 slabs; a call's own options name them; what does not fit is refused."""
+    out = routes.run("""
+class Opts(ctypes.Structure):
+    _fields_ = [("struct_size", Z), ("variant", I), ("columns", I), ("slabs", I), ("waves", I), ("rem_slabs", I), ("workspace", V), ("bytes", Z)]
+lib.rl_autotune.argtypes = [V, V, V, F, V, L, L, L, I, I, I, V, V]
+lib.rmsnorm_linear_ex.argtypes = [V, V, V, F, V, L, L, L, I, V, V]
+assert lib.rl_autotune(P[0], P[1], P[2], 1e-5, P[3], 256, 4096, 1024, BF16, 0, 1, None, None) == 0
+print(sorted({(l.grid, "Li64" in l.mangled) for l in launches() if l.name == "mid_kernel"}) ==
+      sorted([(32 * s, True) for s in range(1, 9)] + [(16 * s, False) for s in range(1, 9)]))
+def ex(columns, slabs, M=256, K=4096, N=1024):
+    o = Opts(ctypes.sizeof(Opts), 5, columns, slabs, 0, 0, None, 0)
+    return lib.rmsnorm_linear_ex(P[0], P[1], P[2], 1e-5, P[3], M, K, N, BF16, ctypes.byref(o), None)
+print(ex(64, 3), last(), ex(128, 0), last(), ex(256, 2), last()[1:3])
+print(ex(128, 17), ex(64, 1, 256, 4096, 1 << 22), lib.rl_last_error())
+""")
+    assert out == ["True", "0 (5, 64, 3, 96) 0 (5, 128, 1, 16) 0 (256, 2)",
+                   "2 2 b'128-row tiles: 1 to 16 slabs, K < 2^23, N < 2^22, and a slab of W below 2 GiB'"]
