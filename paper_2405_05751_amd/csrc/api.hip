@@ -759,7 +759,7 @@ static rl_status qknorm_launch(const void* Q, const void* K, const void* V, cons
     size_t need = qkattn_workspace_bytes(B, H, S, D, DType(dt), splits);
     // With a workgroup per compute unit from the heads alone, or a sequence this short, one split is a fair choice and
     // needs no workspace: the better one takes a region of the stream's own or gives way (see get_region)
-    const bool spares = splits == 0 && need && qkattn_splits(B, H, S, D, DType(dt), 0) > 1 && (B * H >= 256 || S < 512);
+    const bool spares = splits == 0 && need && (B * H >= 256 || S < 512) && qkattn_splits(B, H, S, D, DType(dt), 0) > 1;
     Workspace w;
     if (spares) {
         bool no_memory = false;

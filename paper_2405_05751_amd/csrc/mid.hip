@@ -386,7 +386,8 @@ bool mid_plan(const Problem& p, int* cols, int* S, int* k_slab)
     if (p.n_tile != 0 || p.M <= 64) return false;
     const double mk = double(p.M) * p.K * 1e-6, mn = double(p.M) * p.N * 1e-6;
     const double w_us = double(p.K) * p.N * 2e-6 / 3.45;
-    const bool skinny = skinny_row_blocks(p);    // the choice without this kernel; shorter calls than that are the host's time
+    // the choice without this kernel; below 16 us it stays: issued one by one such calls take the host as long (not compared in graphs)
+    const bool skinny = skinny_row_blocks(p);
     const double other = skinny ? skinny_us(p) : tile_pre_us(p);
     if (skinny && other < 16.) return false;
     const bool split = skinny && skinny_workspace_bytes(p) != 0;

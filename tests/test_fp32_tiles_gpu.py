@@ -30,3 +30,27 @@ def test_tiles(M, K, N):
     # the fp32 bar is 1e-5; the first kernel's tests hold it to 2e-6, and so does this one's summation order
     ratio, _ = compare(got, Z, "f32", f"{M}x{K}x{N}")
     assert ratio <= 2e-6, ratio
+
+
+@pytest.mark.parametrize("M,K,N", [(1921, 292, 1924), (1023, 1000, 4092)])
+def test_special_values(M, K, N):
+    """Infinities in W keep sign and column, NaN and infinity in X keep to their rows, a zero row gives zeros."""
+    import torch
+    import paper_2405_05751_amd as rl
+    w = workloads.make(M, K, N, "f32", 1e-5, 9450, n_check_rows=8)
+    X, g, W = upload(w)
+    X[:, K - 1] = torch.where(torch.arange(M, device="cuda") % 2 == 0, 1.0, -1.0)
+    clean = rl.rmsnorm_linear(X, g, W, w.eps)
+    W[K - 1, 130] = float("inf")
+    X[M - 1] = 0.0
+    X[127, 3] = float("nan")
+    X[128, K - 2] = float("inf")
+    Y = rl.rmsnorm_linear(X, g, W, w.eps)
+    torch.cuda.synchronize()
+    assert rl.rl_last_launch()[:3] == ("f32", 128, 1)
+    plain = torch.tensor([r for r in range(M) if r not in (127, 128, M - 1)], device="cuda")
+    others = torch.tensor([n for n in range(N) if n != 130], device="cuda")
+    assert torch.equal(Y[plain, 130], X[plain, K - 1] * float("inf"))
+    assert torch.equal(Y[plain][:, others], clean[plain][:, others])
+    assert torch.isnan(Y[127]).all() and torch.isnan(Y[128]).all()
+    assert (Y[M - 1, others] == 0).all() and torch.isnan(Y[M - 1, 130])

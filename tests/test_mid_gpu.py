@@ -105,3 +105,49 @@ def test_no_alloc_entry_point(rl, M, K, N, dtype):
     torch.cuda.synchronize()
     assert rl.rl_last_launch() == used
     assert torch.equal(Y, Y2)
+
+
+@pytest.mark.parametrize("cols", [64, 128])
+@pytest.mark.parametrize("M,K,H", [(129, 136, 24), (200, 520, 192), (66, 1000, 320)])
+def test_gated_f16(rl, M, K, H, cols):
+    w = workloads.make(M, K, 2 * H, "f16", 1e-5, 9200 + M + K + H)
+    X, g, W = upload(w)
+    Z = oracle.rmsnorm_linear(w.X, w.g, w.W, w.dtype, w.eps)
+    for slabs in (1, 3):
+        Y, used = _run(rl, lambda: rl.rmsnorm_gated_mlp(X, g, W, w.eps), "tile_pre", cols, slabs)
+        assert used[1] == cols
+        compare_gated(to_host_f64(Y, "f16"), Z, "f16", f"gated {M}x{K}x{H} {used}")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("cols,slabs", [(64, 1), (128, 1), (64, 2), (128, 5)])
+@pytest.mark.parametrize("M,K,N", [(129, 456, 136), (257, 1000, 648)])
+def test_special_values_and_edges(rl, M, K, N, cols, slabs, dtype):
+    """An infinity in the last row of W keeps its sign and its column, NaN and infinity in X keep to their rows, a zero row gives
+    zeros; nothing outside Y is written; the launch has the slabs that whole K tiles of 64 make of those asked for."""
+    import torch
+    w = workloads.make(M, K, N, dtype, 1e-5, 9500 + M)
+    X, g, W = upload(w)
+    X[:, K - 1] = torch.where(torch.arange(M, device="cuda") % 2 == 0, 1.0, -1.0).to(X.dtype)
+    W[K - 1, 7] = float("inf")
+    X[M - 1] = 0.0
+    X[M - 2, 3] = float("nan")
+    X[5, K - 2] = float("inf")
+    pad = 512
+    buf = torch.full((pad + M * N + pad,), 99.0, dtype=X.dtype, device="cuda")
+    Y = buf[pad:pad + M * N].view(M, N)
+    _, used = _run(rl, lambda: rl.rmsnorm_linear(X, g, W, w.eps, Y), "tile_pre", cols, slabs)
+    slab = -(-(-(-K // slabs)) // 64) * 64
+    assert used[:3] == ("tile_pre", cols, -(-K // slab))
+    assert torch.all(buf[:pad] == 99.0) and torch.all(buf[pad + M * N:] == 99.0)
+    plain = [r for r in range(M) if r not in (5, M - 2, M - 1)]
+    assert torch.equal(Y[plain, 7].float(), X[plain, K - 1].float() * float("inf"))
+    others = [n for n in range(N) if n != 7]
+    assert torch.isfinite(Y[plain][:, others]).all()
+    assert torch.isnan(Y[5]).all() and torch.isnan(Y[M - 2]).all()
+    assert (Y[M - 1, others] == 0).all() and torch.isnan(Y[M - 1, 7])
+    W[K - 1, 7] = 0.0
+    X[M - 2, 3] = X[5, K - 2] = 1.0                      # (rows that are not compared)
+    xs, ws = X.cpu().double(), W.cpu().double()
+    Z = (xs * g.cpu().double()) @ ws / torch.sqrt((xs ** 2).mean(1, keepdim=True) + w.eps)
+    compare(to_host_f64(Y[plain][:, others], dtype), Z[plain][:, others].numpy(), dtype, f"{M}x{K}x{N} {used}")

@@ -39,3 +39,20 @@ def test_row_lengths(D, dtype):
     bound = half_ulp * 1.001 * np.abs(want) + 1e-6 * np.abs(want) + 2e-6 * rms + 2.0 ** -25
     worst = float((np.abs(to_host_f64(Y, dtype) - want) / bound).max())
     assert worst <= 1.0, f"{M}x{D} {dtype}: |err| / bound = {worst:.3f}"
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("D", [1, 7, 63, 513, 2047, 3001, 10241])
+def test_special_values_keep_to_their_row(D, dtype):
+    """Rows that share a chunk with one of NaN or infinities, or of the type's largest values, are what they are without."""
+    import torch
+    import paper_2405_05751_amd as rl
+    M = 11
+    X, H, A = (to_device(t, dtype) for t in _make(M, D, dtype, 8400 + D))
+    clean = rl.rl_ntrans(X, H, A, 1e-6)
+    X[2], H[5], X[8], H[8] = float("nan"), float("inf"), float("-inf"), torch.finfo(X.dtype).max
+    Y = rl.rl_ntrans(X, H, A, 1e-6)
+    torch.cuda.synchronize()
+    keep = [0, 1, 3, 4, 6, 7, 9, 10]
+    assert torch.equal(Y[keep], clean[keep])
+    assert torch.isnan(Y[[2, 5, 8]]).all()

@@ -160,3 +160,24 @@ def test_asked_for(rl, M, K, N, slabs, dtype):
     assert used[:2] == ("naive", 128) and (slabs == 0 or used[2] == slabs)
     Z = oracle.rmsnorm_linear(w.X, w.g, w.W, w.dtype, w.eps)
     _check(to_host_f64(Y, dtype), Z, dtype, f"{M}x{K}x{N} {dtype} in {slabs} slabs")
+
+
+def test_w_of_two_gib(rl):
+    """W beyond 2^31 bytes: slabs that are addressed one by one.  Columns at the ends of tiles, of the first and the last."""
+    import torch
+    M, K, N = 3, 8200, 131075
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    X = torch.randn((M, K), generator=gen, device="cuda").to(torch.bfloat16)
+    g = torch.rand((K,), generator=gen, device="cuda").add_(0.5).to(torch.bfloat16)
+    W = torch.empty((K, N), dtype=torch.bfloat16, device="cuda")
+    assert W.numel() * 2 > 1 << 31
+    for k in range(0, K, 1025):
+        W[k:k + 1025] = torch.randn((min(1025, K - k), N), generator=gen, device="cuda").mul_(K ** -0.5)
+    Y = rl.rmsnorm_linear(X, g, W, 1e-5)
+    torch.cuda.synchronize()
+    used = rl.rl_last_launch()
+    assert used[1] == 128 and used[2] > 1
+    cols = torch.tensor([0, 1, 126, 127, 128, 129, 255, 256, 65535, 65536, N - 132, N - 131, N - 130, N - 4, N - 3, N - 2, N - 1], device="cuda")
+    x = X.double()
+    Z = (x * g.double()) @ W[:, cols].double() / torch.sqrt((x ** 2).mean(1, keepdim=True) + 1e-5)
+    _check(Y[:, cols].double().cpu().numpy(), Z.cpu().numpy(), "bf16", f"{M}x{K}x{N} {used}")

@@ -76,7 +76,8 @@ def test_fast_path_forced_splits(rl, D):
         rl.rl_set_tuning(0, 0)
 
 
-@pytest.mark.parametrize("dtype,D", [("f32", 128), ("f32", 64), ("bf16", 96), ("f16", 80), ("bf16", 512), ("f32", 7)])
+@pytest.mark.parametrize("dtype,D", [("f32", 128), ("f32", 64), ("bf16", 96), ("f16", 80), ("bf16", 512), ("f32", 7),
+                                     ("f32", 130), ("f32", 132), ("bf16", 100), ("f16", 77), ("f16", 264)])
 @pytest.mark.parametrize("B,H,S", [(1, 1, 1), (2, 3, 300), (1, 2, 1025)])
 def test_plain_path(rl, B, H, S, D, dtype):
     c = workloads.make_attention(B, H, S, D, dtype, 9300 + B + H + S + D)
@@ -97,6 +98,31 @@ def test_fast_path_partial_lane_groups(rl, B, H, S, splits, dtype, D):
     finally:
         rl.rl_set_tuning(0, 0)
     print(f"{B}x{H}x{S}x{D} {dtype}: max|err|/rms = {worst:.3e}")
+
+
+@pytest.mark.parametrize("dtype,D,splits", [("f16", 96, 0), ("bf16", 72, 5), ("f32", 36, 3), ("bf16", 128, 4)])
+def test_special_values(rl, dtype, D, splits):
+    """NaN in a key, or in a value, keeps to its head (a value's to its dimension), an infinite value gives an infinity there,
+    and the other heads' outputs are, bit for bit, what they are without."""
+    import torch
+    B, H, S = 2, 5, 701
+    c = workloads.make_attention(B, H, S, D, dtype, 9700 + D)
+    dev = {k: to_device(v, dtype) for k, v in c.items()}
+    call = lambda: rl.rl_qknorm_attention(dev["Q"], dev["K"], dev["V"], dev["gq"], dev["bq"], dev["gk"], dev["bk"], 1e-5)
+    try:
+        rl.rl_set_tuning(0, splits)
+        clean = call()
+        dev["K"][0, 1, S - 1, D - 1] = float("nan")
+        dev["V"][1, 2, 333, 5] = float("nan")
+        dev["V"][1, 4, 0, D - 1] = float("-inf")
+        got = call()
+        torch.cuda.synchronize()
+    finally:
+        rl.rl_set_tuning(0, 0)
+    assert torch.isnan(got[0, 1]).all()
+    assert torch.isnan(got[1, 2, 5]) and got[1, 4, D - 1] == float("-inf")
+    got[0, 1], got[1, 2, 5], got[1, 4, D - 1] = clean[0, 1], clean[1, 2, 5], clean[1, 4, D - 1]
+    assert torch.equal(got, clean)
 
 
 def test_split_tuner(rl):
