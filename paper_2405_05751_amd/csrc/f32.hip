@@ -1,11 +1,13 @@
-// The fp32 path of the fused block on the matrix cores (v_mfma_f32_16x16x4_f32: fp32 products, fp32
-// sums), for every M: the case study's Fig. 2b again -- A_i = sum_k X_ik^2 and B_in = sum_k (X_ik g_k)
-// W_kn in one K loop, the division by the root mean square after it -- on 4-byte elements.
+// The fp32 path of the fused block on the matrix cores (fp32 products, fp32
+// sums): the case study's Fig. 2b again -- A_i = sum_k X_ik^2 and B_in = sum_k (X_ik g_k)
+// W_kn in one K loop, the division by the root mean square after it -- on 4-byte elements.  Two kernels: the one
+// described here (v_mfma_f32_16x16x4_f32), which runs every M, and further down one on 128 x 128 tiles through LDS for
+// large problems with K from 192 to 4096 (f32_tiles() has the rule).
 //
 // A workgroup (4 waves) owns 16 MB rows (MB = 1..4) x 64 columns of Y over one K slab; its waves
 // take the slab's 16-row runs of W in turn.  fp32 matrix instructions are slow enough (64 flops
-// per clock and SIMD) that operands straight from the caches keep them fed: nothing is staged
-// through LDS in the K loop.
+// per clock and SIMD) that operands straight from the caches keep them fed two thirds of the time: nothing is
+// staged through LDS in this kernel's K loop.
 //   W: lane (c, q) = (lane % 16, lane / 16) loads rows k + 4 q + t, t = 0..3, columns n0 + 4 c .. + 3:
 //      four loads of 4 rows x 256 contiguous bytes;
 //   X: the same lane loads row 16 mb + c, elements k + 4 q .. + 3 (and g's), 16 bytes;
