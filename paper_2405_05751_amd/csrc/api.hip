@@ -189,7 +189,10 @@ rl_status get_region(hipStream_t s, Workspace* out, bool* no_memory)
     if (dev < 0 || dev >= kMaxDevices) return fail(RL_ERR_UNSUPPORTED, "device index out of range");
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     e = hipStreamIsCapturing(s, &cap);
-    if (e != hipSuccess) return fail(RL_ERR_HIP, "hipStreamIsCapturing: %s", hipGetErrorString(e));
+    if (e != hipSuccess) {                   // (the default stream while another one is captured: the query is refused)
+        (void)hipGetLastError();
+        return fail(RL_ERR_WORKSPACE, "hipStreamIsCapturing: %s", hipGetErrorString(e));
+    }
     if (cap != hipStreamCaptureStatusNone || s == hipStreamPerThread)    // (that handle is another stream in every thread)
         return fail(RL_ERR_WORKSPACE, "no region for this stream");
     std::lock_guard<std::mutex> lk(g_mu);

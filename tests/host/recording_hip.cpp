@@ -98,7 +98,13 @@ int hipGetSymbolAddress(void** p, const void* symbol)
     *p = reinterpret_cast<void*>(at.emplace(symbol, (uintptr_t(1) << 39) + at.size() * (uintptr_t(1) << 32)).first->second);
     return 0;
 }
-int hipStreamIsCapturing(void* s, int* status) { std::lock_guard<std::recursive_mutex> l(mu); *status = capturing.count(s) ? 1 : 0; return 0; }
+int hipStreamIsCapturing(void* s, int* status)
+{
+    std::lock_guard<std::recursive_mutex> l(mu);
+    if (!s && !capturing.empty()) return error(906);     // hipErrorStreamCaptureImplicit
+    *status = capturing.count(s) ? 1 : 0;
+    return 0;
+}
 int hipThreadExchangeStreamCaptureMode(int* mode) { static thread_local int now = 0; const int was = now; now = *mode; *mode = was; return 0; }
 int hipEventCreate(void** e) { *e = e; return 0; }
 int hipEventDestroy(void*) { return 0; }

@@ -107,6 +107,15 @@ print({query})
     assert out[6] == "0"
 
 
+def test_default_stream_while_another_is_captured():
+    """Whether the default stream is captured cannot be asked then: the calls that could do without a workspace do."""
+    out = routes.run("""
+rec.rec_capture(V(5), 1)
+print(linear(8, 4095, 3001), names(), linear(300, 1024, 10000), names(), qknorm(1, 32, 300, 128), len(names()), rec.hipGetLastError())
+""")
+    assert out == ["0 ['odd_kernel'] 0 ['mid_kernel'] 0 1 0"]
+
+
 @pytest.mark.parametrize("call,kernels", [
     ("linear(300, 1024, 10000, BF16, 5)", ["xhat_rows_kernel", "mid_kernel"]),
     ("linear(245, 992, 2496, BF16, 5)", ["xhat_rows_kernel", "mid_kernel", "tile_reduce_kernel"]),
