@@ -68,7 +68,7 @@ typedef enum {
                              rounded up to 64), then the tile kernel as a product scaled per row; with few 256x256 tiles the product
                              is split over K into fp32 partials (up to 64 MiB more) that a third kernel adds up, or runs on tiles
                              of 128 rows x 64 or 128 columns, split or not; unsplit these form X (.) g themselves (fp16: K <= 4096 at
-                             64 columns, 16384 at 128; bf16: K <= 4096 at 64), without a first kernel and without a workspace */
+                             64 columns, 16384 at 128; bf16: N <= 3 M and K <= 4096 at 64), without a first kernel and without a workspace */
     RL_MFMA_F32 = 6       /* fp32 only, any M, K % 4 == 0 and N % 4 == 0, W below 4 GiB: matrix cores on fp32 operands
                              (fp32 products and sums, two levels of accumulators), 64 rows x 64 columns per workgroup,
                              K split over its waves and into 1 to 16 slabs over workgroups; where they fill the chip and K is 192 to

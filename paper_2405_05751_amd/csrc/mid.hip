@@ -18,7 +18,8 @@
 // the squares from them.  One launch, no workspace, and the same product bit for bit; only the squares are summed in another order.
 // It costs vector instructions in the K loop, at 128 columns twice (two waves hold the same rows): in fp16, which has packed
 // products, it is ahead nearly everywhere (34 shapes with M 89 to 2341, geometric mean 0.83; worst 1.00), in bf16 at 64
-// columns (0.74 to 1.06), but not at 128 (0.94 to 1.34: 563 x 3008 x 6336 33.5 and 43.6 us), where X-hat stays a kernel of its own.
+// columns where X-hat's kernel is a fair part of the call, N up to 3 M (32 shapes: 0.72 to 0.99, one 1.05; beyond that 0.98 to
+// 1.10 over 29), but not at 128 (0.94 to 1.34: 563 x 3008 x 6336 33.5 and 43.6 us).  There X-hat stays a kernel of its own.
 #include <algorithm>
 #include <cmath>
 #include "common.hpp"
@@ -354,7 +355,7 @@ static hipError_t mid_t(const MidArgs& a, bool gated, int S, hipStream_t s)
 
 bool mid_fused(const Problem& p, int cols, int S)
 {
-    return p.fused && S == 1 && (p.dt == F16 || cols == 64 || p.no_ws) && mid_lds(cols) + mid_gain_lds(p.K) <= kMidLdsMost / (cols == 64 ? 2 : 1);
+    return p.fused && S == 1 && (p.dt == F16 || (cols == 64 && p.N <= 3 * int64_t(p.M)) || p.no_ws) && mid_lds(cols) + mid_gain_lds(p.K) <= kMidLdsMost / (cols == 64 ? 2 : 1);
 }
 
 // The tile width and the split over K for the product of this problem; false: another form is the better choice, or the
