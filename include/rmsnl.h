@@ -135,7 +135,8 @@ size_t rl_noalloc_scratch_bytes(void);
  *                  zero before the first call that uses it; the kernels leave them zero), or NULL for the
  *                  library's own or the lent one.  Calls that run at the same time on different streams of one
  *                  device must each bring their own.  Too small for the call: RL_ERR_WORKSPACE, except
- *                  that RL_AUTO gives up the two-kernel tile form for the fused tile kernel.
+ *                  that RL_AUTO gives up the two-kernel tile form for the fused tile kernel, and a split of RL_NAIVE's
+ *                  matrix-core form.
  *
  * rmsnorm_gated_mlp_ex: interleaved != 0 reads W as rmsnorm_gated_mlp_interleaved does.
  * rl_last_launch reports what the most recent successful call on this thread launched: variant, columns

@@ -322,6 +322,17 @@ __device__ __forceinline__ float2_t ld_dev2(const float* p) {
     return __builtin_bit_cast(float2_t, u);
 }
 
+// A direct load to LDS: lane l's 16 bytes at byte offset v of the resource (zeros beyond it) go to byte dst + 16 l.  In assembly:
+// as a builtin, the compiler takes every later LDS read for a possible reader of the bytes in flight and waits for all
+// loads first.  So the waits for these are placed by hand.
+__device__ __forceinline__ void load_lds(const uint4_t& rsrc, uint32_t dst, unsigned v) {
+    const uint4_t desc = rsrc;
+    uint32_t keep;                           // M0 carries the LDS address; whatever it held is put back
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
+                 "buffer_load_dwordx4 %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
+                 : "=&s"(keep) : "s"(dst), "v"(v), "s"(desc) : "memory");
+}
+
 // Workgroup b of n: consecutive workgroups go to the 8 XCDs in turn, so XCD x holds those with b % 8 == x.  The
 // number returned runs through 0 .. n - 1 so that each XCD gets a run of consecutive ones (shares
 // differ by one at most), and what neighbours share, it finds in its own L2.

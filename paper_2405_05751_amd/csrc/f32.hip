@@ -230,13 +230,6 @@ __global__ __launch_bounds__(512, 2) void f32_tile_kernel(const float* X, const 
     const uint64_t xbase = uint64_t(uintptr_t(X + size_t(m0) * K)), wbase = uint64_t(uintptr_t(W));
     const uint4_t xdesc = {uint32_t(xbase), uint32_t(xbase >> 32), uint32_t(min(BM, M - m0) * K * 4), uint32_t(kF32Flags)};
     const uint4_t wdesc = {uint32_t(wbase), uint32_t(wbase >> 32), uint32_t(K * N * 4), uint32_t(kF32Flags)};
-    auto load_lds = [&](const uint4_t& rsrc, uint32_t dst, unsigned v) {
-        const uint4_t desc = rsrc;
-        uint32_t keep;                       // M0 carries the LDS address; whatever it held is put back
-        asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
-                     "buffer_load_dwordx4 %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
-                     : "=&s"(keep) : "s"(dst), "v"(v), "s"(desc) : "memory");
-    };
     // a load of X: 8 rows of 128 bytes, lane (r, c) fetches the chunk that belongs in slot c of row r; of W: 2 rows of 512
     const int xr = lane >> 3, xc = ((lane & 7) ^ (4 * (wave & 1) + (xr >> 1))) * 4;
     const int wcol = n0 + 4 * (lane & 31);

@@ -125,13 +125,6 @@ __global__ __launch_bounds__(512, BN == 64 ? 4 : 2) void mid_kernel(MidArgs a)
     const uint64_t xbase = uint64_t(uintptr_t(a.X + size_t(m0) * a.ldx + kb)), wbase = uint64_t(uintptr_t(a.W + size_t(kb) * a.N));
     const uint4_t xdesc = {uint32_t(xbase), uint32_t(xbase >> 32), uint32_t((min(BM, a.M - m0) * a.ldx - kb) * 2), uint32_t(kMidFlags)};
     const uint4_t wdesc = {uint32_t(wbase), uint32_t(wbase >> 32), uint32_t(klen * a.N * 2), uint32_t(kMidFlags)};
-    auto load_lds = [&](const uint4_t& rsrc, uint32_t dst, unsigned v) {
-        const uint4_t desc = rsrc;
-        uint32_t keep;                                   // M0 carries the LDS address; whatever it held is put back
-        asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
-                     "buffer_load_dwordx4 %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
-                     : "=&s"(keep) : "s"(dst), "v"(v), "s"(desc) : "memory");
-    };
     const int xr = lane >> 3, xc = ((lane & 7) ^ (4 * (wave & 1) + (xr >> 1))) * 8;          // row in the load, first k
     unsigned xoff[2];
 #pragma unroll

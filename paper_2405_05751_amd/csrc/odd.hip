@@ -128,13 +128,6 @@ __global__ __launch_bounds__(64 * kOddWaves) void odd_kernel(
     const uint32_t stage_lds = __builtin_amdgcn_readfirstlane(uint32_t(uintptr_t(stage)));
     const uint4_t xdesc = {uint32_t(uintptr_t(Xb)), uint32_t(uintptr_t(Xb) >> 32), uint32_t((Mh * K * 2 + 3) & ~3), uint32_t(kOddFlags)};
     const uint4_t gdesc = {uint32_t(uintptr_t(g)), uint32_t(uintptr_t(g) >> 32), uint32_t((K * 2 + 3) & ~3), uint32_t(kOddFlags)};
-    auto load_lds = [&](const uint4_t& rsrc, uint32_t dst, int v) {
-        const uint4_t desc = rsrc;
-        uint32_t keep;                       // M0 carries the LDS address; whatever it held is put back
-        asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
-                     "buffer_load_dwordx4 %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
-                     : "=&s"(keep) : "s"(dst), "v"(v), "s"(desc) : "memory");
-    };
     // the dword of column n0 + 128 of odd rows: lane l takes row 2l + 1 of the run
     const uint4_t wdesc = {uint32_t(uintptr_t(W + size_t(k0) * N)), uint32_t(uintptr_t(W + size_t(k0) * N) >> 32),
                            uint32_t((klen * N * 2 + 3) & ~3), uint32_t(kOddFlags)};

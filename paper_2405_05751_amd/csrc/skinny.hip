@@ -181,13 +181,6 @@ __global__ __launch_bounds__(64 * skinny_waves(MB)) void skinny_kernel(
     const uint4_t xdesc = {uint32_t(uintptr_t(Xb)), uint32_t(uintptr_t(Xb) >> 32), uint32_t(Mh * a.K * 2), uint32_t(kSkFlags)};
     const uint4_t gdesc = {uint32_t(uintptr_t(FUSED ? a.g : a.X)), uint32_t(uintptr_t(FUSED ? a.g : a.X) >> 32),
                            uint32_t(a.K * 2), uint32_t(kSkFlags)};
-    auto load_lds = [&](const uint4_t& rsrc, uint32_t dst, int v) {
-        const uint4_t desc = rsrc;
-        uint32_t keep;                       // M0 carries the LDS address; whatever it held is put back
-        asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
-                     "buffer_load_dwordx4 %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
-                     : "=&s"(keep) : "s"(dst), "v"(v), "s"(desc) : "memory");
-    };
 
     uint4_t w[D][8];                         // D steps of W in flight
     uint4_t xr[XLDS ? 1 : 2 * MB], gr;       // register mode: the next run of X (and g), as lines
