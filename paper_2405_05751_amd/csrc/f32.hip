@@ -195,29 +195,68 @@ __global__ __launch_bounds__(256) void f32_kernel(F32Args a)
     splitk_tail<float, MT, kF32Tile, FUSED, 4, GATED>(ta, red, &s_sumsq[0][0], s_rinv, &s_last, tile, slab, n0);
 }
 
-// ---- large problems: 128 x 128 tiles through LDS
-// The kernel above leaves the matrix pipes idle a third of the time: with operands straight from the caches, every 16 x 16 x 4
-// instruction waits on loads of its own wave.  Where 128 x 128 tiles fill the chip, this one keeps four K tiles of 32 in LDS
-// (direct loads of X and W, as in mid.hip, whose scheme it is): 8 waves in two groups, a group takes 16 of the 32 k, a
-// wave 64 x 64 of the tile on v_mfma_f32_32x32x2_f32 (two k: lane halves h, element t of a 16-byte fragment is k 8 s + 4 h + t
-// on both sides).  X (.) g is formed in fp32 on the fragments; the two waves that share 64 rows take the squares of 32 each.
-// Sums: a matrix accumulator takes 32 k of its group (64 of the tile) and is then added into a second one, so that the
-// rounding error stays below that of the kernel above for K from 192 to 4096 (K / 2 terms in two levels of 32 against K / 4
-// in two levels of 128; relative error against fp64 1.27e-7 and 1.43e-7 at K = 192, 1.44e-7 and 2.14e-7 at 1000, 1.92e-7 and
-// 2.22e-7 at 4096, but 1.23e-7 and 1.01e-7 at 64), which is where it is used.  2048 x 4096 x 4096: 672 -> 593 us, 116 TFLOP/s, 74 % of the fp32 matrix peak
-// (the second level costs 3 %; loads asked for earlier or later, and a third or fourth K tile in LDS: 1 %).
-constexpr int kFtM = 128, kFtN = 128, kFtK = 32, kFtStages = 4, kFtMinK = 192, kFtMaxK = 4096;
+// ---- large problems: tiles of 128 columns on the bf16 matrix cores
+// The fp32 matrix instructions run at 1/16 of the bf16 rate (and the kernel above keeps them busy 65 % of the time).  A finite
+// fp32 number is the sum of three bf16 numbers, its value rounded to bf16, the remainder rounded, and what is left, each exact; the
+// product of two such sums is nine products, exact in fp32, of which the three smallest (together below 2^-26 of the product) are
+// left out.  Six v_mfma_f32_32x32x16_bf16 then stand for eight v_mfma_f32_32x32x2_f32 of four times the time each.
+// What must hold for that: the remainders are no denormals (both operands are scaled by 2^24, the sums back, so that this
+// holds down to the smallest fp32 numbers), and everything is finite (sums that are not are taken again in fp32, see below).
+//
+// X (.) g (formed in fp32) and W come through registers, two K tiles of 32 ahead: split there, and written to LDS as three bf16
+// planes each, in two buffers.  8 waves in two groups; a group takes 16 of the 32 k, a wave 32 TM x 64 of the tile.  Scaling and
+// splitting is vector work for the next K tile between the matrix instructions of this one.
+// Sums: a matrix accumulator takes 64 k of its group (128 of the tile) and is then added into a second one, by the two waves of
+// a SIMD at different times; of a step's six products the small ones come first.  Relative error against fp64 1.0e-7 at K = 64,
+// 1.2e-7 at 192, 1.4e-7 at 1000, 1.8e-7 at 4096, 2.1e-7 at 8192 (on fp32 instructions, 128 x 128 tiles: 1.3e-7, 1.4e-7, 1.9e-7 from 192
+// to 4096; the kernel above: 1.0e-7 at 64, 2.2e-7 at 1000 and 4096, 2.3e-7 at 8192; adding into the second accumulator twice as often: 1.0e-7 at 192,
+// but 2.0e-7 at 4096).  2048 x 4096 x 4096: 593 -> 375 us, 183 TFLOP/s (fp32 peak: 157).  Of that the matrix instructions and their LDS
+// reads take 295 us, which is what the chip's power allows them; loads 55 (by leaving them out), splitting 49, second accumulator 20.
+constexpr int kFtN = 128, kFtK = 32, kFtMinK = 64, kFtMaxK = 16000;        // (g in LDS)
 constexpr unsigned kFtOut = 0x80000000u;     // beyond every resource (sizes below 2^31), with any tile offset added
+constexpr float kFtScale = 0x1p24f;
+constexpr int ft_buf(int TM) { return 3 * (64 * TM + kFtN) * kFtK; }          // elements of a buffer
 
+typedef __attribute__((ext_vector_type(4))) short f32_short4_t;
+typedef __attribute__((address_space(3))) f32_short4_t* f32_lds_ptr;
+__device__ __forceinline__ uint2_t f32_read_tr(const u16* p) {
+    return __builtin_bit_cast(uint2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((f32_lds_ptr)(p)));
+}
+
+// n times a matrix instruction and v vector instructions behind it
+#define RL_F32_MIX(n, v) \
+    _Pragma("unroll") for (int mix = 0; mix < n; ++mix) { \
+        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0); \
+        __builtin_amdgcn_sched_group_barrier(0x2, v, 0); \
+    }
+
+// four numbers, scaled, as three times four bf16 numbers
+__device__ __forceinline__ void f32_split(float4_t v, uint2_t (&part)[3]) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] *= kFtScale;
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const uint32_t p = Elem<Bf16>::pack(v[2 * e], v[2 * e + 1]);
+            part[q][e] = p;
+            if (q < 2) {
+                v[2 * e] -= Elem<Bf16>::lo(p);
+                v[2 * e + 1] -= Elem<Bf16>::hi(p);
+            }
+        }
+}
+
+// TM: matrix tiles of 32 rows per wave, tiles of 64 TM rows
+template <int TM>
 __global__ __launch_bounds__(512, 2) void f32_tile_kernel(const float* X, const float* g, const float* W, float* Y,
                                                           int M, int K, int N, int tiles_m, int tiles_n, float eps, float inv_K)
 {
-    constexpr int BM = kFtM, BN = kFtN, BK = kFtK, NS = kFtStages, NLOAD = 4;
+    constexpr int BM = 64 * TM, BN = kFtN, BK = kFtK, BUF = ft_buf(TM);
     extern __shared__ __attribute__((aligned(16))) float smem[];
-    float* As = smem;                        // [NS][BM][BK], 16-byte chunk c of row r at c ^ ((r / 2) & 7)
-    float* Bs = As + NS * BM * BK;           // [NS][BK][BN]
-    float* gs = Bs + NS * BK * BN;           // g, K rounded up to a multiple of BK (and one more tile), zeros behind it
-    __shared__ float s_ss[2][BM];
+    u16* planes = (u16*)smem;                // [2]{ X-hat [3][BM][BK], W [3][BK][BN] }, see below
+    float* gs = smem + BUF;               // g, K rounded up to a multiple of 4 BK (and one more tile), zeros behind it
+    __shared__ float s_ss[BM];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kg = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
@@ -227,130 +266,214 @@ __global__ __launch_bounds__(512, 2) void f32_tile_kernel(const float* X, const 
     const int panel = l / (8 * tiles_n), in = l - panel * 8 * tiles_n, rows = min(8, tiles_m - 8 * panel);
     const int m0 = (8 * panel + in % rows) * BM, n0 = in / rows * BN;
 
-    const uint64_t xbase = uint64_t(uintptr_t(X + size_t(m0) * K)), wbase = uint64_t(uintptr_t(W));
-    const uint4_t xdesc = {uint32_t(xbase), uint32_t(xbase >> 32), uint32_t(min(BM, M - m0) * K * 4), uint32_t(kF32Flags)};
-    const uint4_t wdesc = {uint32_t(wbase), uint32_t(wbase >> 32), uint32_t(K * N * 4), uint32_t(kF32Flags)};
-    // a load of X: 8 rows of 128 bytes, lane (r, c) fetches the chunk that belongs in slot c of row r; of W: 2 rows of 512
-    const int xr = lane >> 3, xc = ((lane & 7) ^ (4 * (wave & 1) + (xr >> 1))) * 4;
-    const int wcol = n0 + 4 * (lane & 31);
-    unsigned xoff[2], woff[2];
-#pragma unroll
-    for (int p = 0; p < 2; ++p) {
-        const int row = 8 * (wave + 8 * p) + xr;
-        xoff[p] = m0 + row < M ? unsigned(row * K + xc) * 4u : kFtOut;
-        woff[p] = wcol < N ? unsigned((2 * (wave + 8 * p) + (lane >> 5)) * N + wcol) * 4u : kFtOut;
-    }
-    const uint32_t as_base = uint32_t(uintptr_t(As)) + uint32_t(wave) * 1024, bs_base = uint32_t(uintptr_t(Bs)) + uint32_t(wave) * 1024;
-    auto load_tile = [&](int t, int buf) {   // past K: zeros
-        const int k0 = t * BK;
-        const bool kin = k0 + xc < K;
+    const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(X + size_t(m0) * K), 0, min(BM, M - m0) * K * 4, kF32Flags);
+    const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(W), 0, K * N * 4, kF32Flags);
+    const __amdgpu_buffer_rsrc_t grs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(g), 0, K * 4, kF32Flags);
+    // a wave's load of X is 8 rows of 128 bytes, of W 2 rows of 512
+    // (64 rows, 16 rows further on for the second one)
+    const int xrow = 8 * wave + (lane >> 3), xk = 4 * (lane & 7), wrow = 2 * wave + (lane >> 5), wcol = 4 * (lane & 31);
+    const unsigned xoff = unsigned(xrow * K + xk) * 4u;                  // (rows beyond M lie beyond the resource)
+    const unsigned woff = n0 + wcol < N ? unsigned(wrow * N + n0 + wcol) * 4u : kFtOut;
+    // where they go.  X-hat: rows of 64 bytes, 16-byte chunk c of row r at c ^ ((r / 4) & 3); W: rows of 256 bytes, chunk c of row r at c ^ 4 (r & 3)
+    u16* const xst = planes + xrow * BK + 8 * ((xk >> 3) ^ ((xrow >> 2) & 3)) + (xk & 4);
+    u16* const wst = planes + 3 * BM * BK + wrow * BN + ((wcol & ~7) ^ (32 * (wrow & 3))) + (wcol & 4);
+    float4_t xr[2][TM], wr[2][2];             // [set]: two K tiles on their way
+    auto load_tile = [&](auto set, int t) {  // past K: zeros
+        constexpr int st = decltype(set)::value;
+        const unsigned k0 = unsigned(t * BK);
+        const unsigned xo = int(k0) + xk < K ? xoff + k0 * 4u : kFtOut, wo = woff + k0 * unsigned(N) * 4u;
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
-            load_lds(wdesc, bs_base + uint32_t(buf * BK * BN * 4 + p * 8192), woff[p] + unsigned(k0) * unsigned(N) * 4u);
-            load_lds(xdesc, as_base + uint32_t(buf * BM * BK * 4 + p * 8192), kin ? xoff[p] + unsigned(k0) * 4u : kFtOut);
+            if (p < TM) xr[st][p] = __builtin_bit_cast(float4_t, __builtin_amdgcn_raw_buffer_load_b128(xrs, int(xo + unsigned(p * 64 * K) * 4u), 0, 0));
+            wr[st][p] = __builtin_bit_cast(float4_t, __builtin_amdgcn_raw_buffer_load_b128(wrs, int(wo + unsigned(p * 16 * N) * 4u), 0, 0));
         }
     };
-    const int nk = (K + BK - 1) / BK;
+    float ss[TM] = {}, ss_tot[TM] = {};      // squares of this thread's rows
+    auto store_x = [&](auto set, int buf, int p, float4_t gv) {
+        constexpr int st = decltype(set)::value;
+        const float4_t x = xr[st][p];
 #pragma unroll
-    for (int t = 0; t < NS; ++t) load_tile(t, t);
-    for (int k = tid; k < (nk + 1) * BK; k += 512) gs[k] = k < K ? g[k] : 0.f;
+        for (int e = 0; e < 4; ++e) ss[p] = __fmaf_rn(x[e], x[e], ss[p]);
+        uint2_t part[3];
+        f32_split(x * gv, part);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) *(uint2_t*)(xst + buf * BUF + q * BM * BK + p * 64 * BK) = part[q];
+    };
+    auto store_w = [&](auto set, int buf, int p) {
+        constexpr int st = decltype(set)::value;
+        uint2_t part[3];
+        f32_split(wr[st][p], part);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) *(uint2_t*)(wst + buf * BUF + q * BK * BN + p * 16 * BN) = part[q];
+    };
 
     const int h = lane >> 5, c = lane & 31;
-    const int a_row = wm * 64 + c;
-    int a_off[2];
+    const int a_row = wm * 32 * TM + c, a_off = a_row * BK + 8 * ((2 * kg + h) ^ ((a_row >> 2) & 3));
+    const int blk = lane >> 4, jj = lane & 15, b_row = 16 * kg + 8 * h + (jj >> 2);
+    const int b_off = 3 * BM * BK + b_row * BN + ((wn * 64 + 16 * (blk & 1)) ^ (32 * (b_row & 3))) + 4 * (jj & 3);
+    float16_t acc[TM][2], tot[TM][2];
+    auto clear = [&](float16_t (&v)[TM][2]) {
 #pragma unroll
-    for (int s = 0; s < 2; ++s) a_off[s] = a_row * BK + 4 * ((4 * kg + 2 * s + h) ^ ((a_row >> 1) & 7));
-    const int b_off = (16 * kg + 4 * h) * BN + wn * 64 + 2 * c, g_off = 16 * kg + 4 * h;
-    float4_t af[2][2][2], gf[2][2];          // [set][step][row block]
-    float2_t bf[2][2][4];                    // [set][step][t]: columns 2 c and 2 c + 1
-    auto read_frags = [&](auto set, int t, int buf) {
-        constexpr int st = decltype(set)::value;
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-#pragma unroll
-            for (int i = 0; i < 2; ++i) af[st][s][i] = *(const float4_t*)(As + buf * BM * BK + a_off[s] + i * 32 * BK);
-            gf[st][s] = *(const float4_t*)(gs + t * BK + g_off + 8 * s);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) bf[st][s][e] = *(const float2_t*)(Bs + buf * BK * BN + b_off + (8 * s + e) * BN);
-        }
-    };
-    float16_t acc[2][2], tot[2][2];
-    float ss = 0.f, ss_tot = 0.f;            // squares of row block wn
-    auto clear = [&](float16_t (&v)[2][2]) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < 2; ++j)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) v[i][j][r] = 0.f;
     };
-    clear(acc);
-    clear(tot);
     auto fold = [&]() {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < 2; ++j)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) tot[i][j][r] += acc[i][j][r];
-        clear(acc);
-        ss_tot += ss;
-        ss = 0.f;
     };
-    auto iteration = [&](auto set, int t) {
-        constexpr int st = decltype(set)::value;
-        // this wave's loads of tile t + 1 have landed; after the barrier everybody's have, and everybody holds tile t
-        __builtin_amdgcn_s_waitcnt(((NS - 2) * NLOAD & 15) | (7 << 4) | (15 << 8));
+    const std::integral_constant<int, 0> even;
+    const std::integral_constant<int, 1> odd;
+    // iteration t: products of K tile t out of buffer t % 2, K tile t + 1 into the other one, loads of K tile t + 3
+    auto iteration = [&](auto other, int t, bool first) {
+        constexpr int ob = decltype(other)::value, buf = ob ^ 1;
         __syncthreads();
-        __builtin_amdgcn_sched_barrier(0);
-        read_frags(std::integral_constant<int, st ^ 1>{}, t + 1, (t + 1) % NS);
-        load_tile(t + NS, t % NS);
-        __builtin_amdgcn_sched_barrier(0);
+        const u16* pl = planes + buf * BUF;
+        uint4_t af[3][TM], bf[3][2];
+        auto read_a = [&](int q) {
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            float4_t xh[2];
+            for (int i = 0; i < TM; ++i) af[q][i] = *(const uint4_t*)(pl + q * BM * BK + a_off + i * 32 * BK);
+        };
+        auto read_b = [&](int q) {
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const float4_t x = af[st][s][i];
-                if (wn == i)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) ss = __fmaf_rn(x[e], x[e], ss);
-                xh[i] = x * gf[st][s];
+            for (int j = 0; j < 2; ++j) {
+                const u16* Bb = pl + q * BK * BN + (b_off ^ (32 * j));
+                const uint2_t lo = f32_read_tr(Bb), hi = f32_read_tr(Bb + 4 * BN);
+                bf[q][j] = uint4_t{lo[0], lo[1], hi[0], hi[1]};
             }
+        };
+        auto product = [&](int qa, int qb, bool zero) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, af[qa][i]), __builtin_bit_cast(bf16x8_t, bf[qb][j]),
+                                                                        zero ? float16_t{} : acc[i][j], 0, 0, 0);
+        };
+        // the small products first; the vector work for the next K tile between the matrix instructions
+        __builtin_amdgcn_sched_barrier(0);
+        const float4_t gv = *(const float4_t*)(gs + (t + 1) * BK + xk);
+        read_b(0); read_a(2); read_a(0); read_b(2);
+        __builtin_amdgcn_sched_barrier(0);
+        store_x(other, ob, 0, gv);
+        if (first) product(2, 0, true); else product(2, 0, false);
+        read_a(1); read_b(1);
+        product(0, 2, false);
+        RL_F32_MIX(2 * TM, 8);
+        __builtin_amdgcn_sched_barrier(0);
+        if (TM == 2) store_x(other, ob, TM - 1, gv);
+        product(1, 1, false);
+        RL_F32_MIX(2 * TM, 8);
+        __builtin_amdgcn_sched_barrier(0);
+        store_w(other, ob, 0);
+        product(1, 0, false);
+        RL_F32_MIX(2 * TM, 8);
+        __builtin_amdgcn_sched_barrier(0);
+        store_w(other, ob, 1);
+        product(0, 1, false);
+        RL_F32_MIX(2 * TM, 8);
+        __builtin_amdgcn_sched_barrier(0);
+        load_tile(other, t + 3);
+        product(0, 0, false);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    clear(acc);
+    clear(tot);
+    load_tile(even, 0);
+    load_tile(odd, 1);
+    for (int k = tid; k < (K + 4 * BK - 1) / (4 * BK) * (4 * BK) + BK; k += 512) gs[k] = k < K ? g[k] : 0.f;
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < 2; ++p) { if (p < TM) store_x(even, 0, p, *(const float4_t*)(gs + xk)); store_w(even, 0, p); }
+    load_tile(even, 2);
+    const int nk = (K + BK - 1) / BK;
+    for (int t = 0; t < nk; t += 4) {        // (K tiles past the last one are zeros)
+        iteration(odd, t, kg == 0);
+        iteration(even, t + 1, false);
+        if (kg == 1) fold();                 // (the two waves of a SIMD in turn)
+        iteration(odd, t + 2, kg == 1);
+        iteration(even, t + 3, false);
+        if (kg == 0) fold();
+#pragma unroll
+        for (int p = 0; p < TM; ++p) { ss_tot[p] += ss[p]; ss[p] = 0.f; }
+    }
+    if (kg == 1) fold();
+#pragma unroll
+    for (int p = 0; p < TM; ++p) {
+        float v = ss_tot[p];
+#pragma unroll
+        for (int o = 1; o < 8; o <<= 1) v += __shfl_xor(v, o, 64);
+        if ((lane & 7) == 0) s_ss[8 * (wave + 8 * p) + (lane >> 3)] = v;
+    }
+    // An infinity is no sum of bf16 numbers (its remainder is NaN), and what is scaled may overflow: the sums that are not
+    // finite are taken again, over the same k, on the fp32 matrix instructions, operands straight from memory
+    float nan = 0.f;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) nan = __fmaf_rn(tot[i][j][r], 0.f, nan);
+    const bool again = __syncthreads_or(nan != 0.f);     // (NaN != 0)
+    float16_t sum[TM][2];
+    clear(sum);
+    for (int k0 = 0; again && k0 < K; k0 += 4 * BK) {
+        clear(acc);
+        for (int u = 0; u < 8; ++u) {
+            const int k = k0 + BK * (u >> 1) + 16 * kg + 8 * (u & 1) + 4 * h;
+            const bool kin = k < K;
+            const float4_t gv = *(const float4_t*)(gs + k);
+            float4_t xh[TM];
+            float w[4][2];
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+                xh[i] = __builtin_bit_cast(float4_t, __builtin_amdgcn_raw_buffer_load_b128(
+                    xrs, int(kin ? unsigned((a_row + 32 * i) * K + k) * 4u : kFtOut), 0, 0)) * gv;
 #pragma unroll
             for (int e = 0; e < 4; ++e)
 #pragma unroll
-                for (int i = 0; i < 2; ++i)
+                for (int j = 0; j < 2; ++j) {
+                    const int col = n0 + wn * 64 + j * 32 + c;
+                    w[e][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                        wrs, int(kin && col < N ? unsigned((k + e) * N + col) * 4u : kFtOut), 0, 0));
+                }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
 #pragma unroll
                     for (int j = 0; j < 2; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(xh[i][e], bf[st][s][e][j], acc[i][j], 0, 0, 0);
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(xh[i][e], w[e][j], acc[i][j], 0, 0, 0);
         }
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    __builtin_amdgcn_s_waitcnt(((NS - 1) * NLOAD & 15) | (7 << 4) | (15 << 8));
-    __syncthreads();
-    read_frags(std::integral_constant<int, 0>{}, 0, 0);
-    int t = 0;
-    for (; t + 2 <= nk; t += 2) {
-        iteration(std::integral_constant<int, 0>{}, t);
-        iteration(std::integral_constant<int, 1>{}, t + 1);
-        fold();
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) sum[i][j][r] += acc[i][j][r];
     }
-    if (t < nk) {
-        iteration(std::integral_constant<int, 0>{}, t);
-        fold();
-    }
-    __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8));    // nothing may still be writing LDS past this point
-    ss_tot += __shfl_xor(ss_tot, 32, 64);
-    if (h == 0) s_ss[kg][wm * 64 + wn * 32 + c] = ss_tot;
-    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float v = tot[i][j][r];
+                tot[i][j][r] = !again || v - v == 0.f ? v * (1.f / (kFtScale * kFtScale)) : sum[i][j][r];
+            }
     // the groups' sums meet in LDS: group 0 finishes accumulator registers 0 .. 7, group 1 registers 8 .. 15
-    float* mine = smem + wave * 4 * 8 * 64 + lane;
-    const float* other = smem + (wave ^ 4) * 4 * 8 * 64 + lane;
+    float* mine = smem + wave * 2 * TM * 8 * 64 + lane;
+    const float* theirs = smem + (wave ^ 4) * 2 * TM * 8 * 64 + lane;
     auto give = [&](auto first) {
         constexpr int r0 = decltype(first)::value;
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -359,14 +482,18 @@ __global__ __launch_bounds__(512, 2) void f32_tile_kernel(const float* X, const 
     auto finish = [&](auto first) {
         constexpr int r0 = decltype(first)::value;
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int r = 0; r < 8; ++r) {
-                const int row = wm * 64 + i * 32 + 2 * r0 + 8 * (r >> 2) + 4 * h + (r & 3);
-                const float ri = row_scale(s_ss[0][row] + s_ss[1][row], inv_K, eps);
-                const float2_t y = {(tot[i][0][r0 + r] + other[(i * 16 + r) * 64]) * ri, (tot[i][1][r0 + r] + other[(i * 16 + 8 + r) * 64]) * ri};
-                const int col = n0 + wn * 64 + 2 * c;
-                if (m0 + row < M && col < N) __builtin_nontemporal_store(y, (float2_t*)(Y + size_t(m0 + row) * N + col));
+                // register r is row 8 (r / 4) + 4 (lane / 32) + r % 4, column lane % 32 of its matrix tile
+                const int row = wm * 32 * TM + i * 32 + 2 * r0 + 8 * (r >> 2) + 4 * h + (r & 3);
+                const float ri = row_scale(s_ss[row], inv_K, eps);
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const int col = n0 + wn * 64 + j * 32 + c;
+                    const float y = (tot[i][j][r0 + r] + theirs[((i * 2 + j) * 8 + r) * 64]) * ri;
+                    if (m0 + row < M && col < N) __builtin_nontemporal_store(y, Y + size_t(m0 + row) * N + col);
+                }
             }
     };
     const std::integral_constant<int, 0> low;
@@ -376,10 +503,7 @@ __global__ __launch_bounds__(512, 2) void f32_tile_kernel(const float* X, const 
     if (kg == 0) finish(low); else finish(high);
 }
 
-static size_t f32_tile_lds(int K)
-{
-    return size_t(kFtStages) * (kFtM + kFtN) * kFtK * 4 + size_t((K + kFtK - 1) / kFtK + 1) * kFtK * 4;
-}
+static size_t f32_tile_lds(int TM, int K) { return size_t(2) * ft_buf(TM) * 2 + size_t((K + 4 * kFtK - 1) / (4 * kFtK) * (4 * kFtK) + kFtK) * 4; }     // 96 KiB and g
 
 // ------------------------------------------------------------------------------------------- host
 struct F32Plan { int MB, RB, S, k_slab, n_tiles; size_t lds; bool ok; const char* why; };
@@ -434,20 +558,39 @@ static F32Plan f32_plan(const Problem& p)
     return pl;
 }
 
-// Which problems: by the rounds either kernel needs, K in us (fitted to 12 shapes).  128 x 128 tiles run one to a
-// compute unit; 64 x 64 tiles two, or one in a last round that has no more, and a split over K fills the
-// chip better than larger tiles would: 1024 x 4096 x 4096 338 -> 301 us, 1500 x 500 x 2500 58 -> 44 us, 2000 x 256 x 8192 146 ->
-// 98 us, but 512 x 4096 x 4096 170 us here and 299 on 128 tiles, 1000 x 2000 x 3000 134 and 151 us.
-static bool f32_tiles(const Problem& p, const F32Plan& pl)
+// Which problems, and the tile's rows / 64 (0: the kernel above).  By the rounds of workgroups that each needs, K in us: tiles run
+// one to a compute unit and slow down as the chip fills (power), the 64 x 64 tiles above run two, or one in a last round
+// that has no more, and a split over K fills the chip better than larger tiles would.  Fitted to 13 shapes, 6 % rms.  us above, on
+// 64 and on 128 rows: 512 x 4096 x 4096 171, 119, 157; 1000 x 2000 x 3000 135, 116, 84; 1500 x 256 x 1000 20.4, 12.6, 17.7;
+// 300 x 1000 x 8192 75, 63, 46; 256 x 4096 x 4096 87, 108, 156; 1024^3 26, 30, 44.
+static int f32_tiles(const Problem& p, const F32Plan& pl)
 {
-    if (!pl.ok || pl.S > 1 || !p.fused || p.gated || p.n_tile != 0 || p.k_split != 0 || p.K < kFtMinK || p.K > kFtMaxK) return false;
-    if ((int64_t(p.K) + 512) * p.N * 4 >= (int64_t(1) << 31)) return false;
-    const int64_t tiles = ((int64_t(p.M) + kFtM - 1) / kFtM) * ((p.N + kFtN - 1) / kFtN), small = int64_t(pl.n_tiles) * pl.RB;
-    if (tiles >= (int64_t(1) << 31)) return false;
-    const double here = double((tiles + 255) / 256) * (5.0 + 0.0725 * p.K);
+    if (!pl.ok || pl.S > 1 || !p.fused || p.gated || p.n_tile != 0 || p.k_split != 0 || p.K < kFtMinK || p.K > kFtMaxK) return 0;
+    if ((int64_t(p.K) + 512) * p.N * 4 >= (int64_t(1) << 31)) return 0;
+    const int64_t cols = (p.N + kFtN - 1) / kFtN, small = int64_t(pl.n_tiles) * pl.RB;
+    const int64_t n1 = (int64_t(p.M) + 63) / 64 * cols, n2 = (int64_t(p.M) + 127) / 128 * cols;
+    if (n1 >= (int64_t(1) << 23)) return 0;              // a grid holds fewer than 2^32 threads, 512 to a tile
+    const auto rounds = [](int64_t n, double fixed, double empty, double full) {
+        const double last = double(n % 256);
+        return double(n / 256) * (fixed + empty + full) + (last > 0. ? fixed + empty + full * last / 256. : 0.);
+    };
+    const double t1 = rounds(n1, 5.0, 0.0243 * p.K, 0.0035 * p.K), t2 = rounds(n2, 5.5, 0.0372 * p.K, 0.0085 * p.K);
     const int64_t last = small % 512;
-    const double there = double(small / 512) * (7.0 + 0.041 * p.K) + (last > 256 ? 7.0 + 0.041 * p.K : last ? 4.0 + 0.0255 * p.K : 0.0);
-    return here < 0.93 * there;
+    const double t0 = double(small / 512) * (7.0 + 0.041 * p.K) + (last > 256 ? 7.0 + 0.041 * p.K : last ? 4.0 + 0.0203 * p.K : 0.0);
+    return std::min(t1, t2) >= 0.93 * t0 ? 0 : t1 < t2 ? 1 : 2;
+}
+
+template <int TM>
+static hipError_t f32_tile_go(const Problem& p, hipStream_t s)
+{
+    static LdsOnce once;
+    hipError_t e = raise_lds_once(once, {(const void*)f32_tile_kernel<TM>}, int(f32_tile_lds(TM, kFtMaxK)));
+    if (e != hipSuccess) return e;
+    const int tm = (p.M + 64 * TM - 1) / (64 * TM), tn = (p.N + kFtN - 1) / kFtN;
+    if (p.plan) { p.plan[0] = kFtN; p.plan[1] = 1; p.plan[2] = tm * tn; }
+    f32_tile_kernel<TM><<<tm * tn, 512, f32_tile_lds(TM, p.K), s>>>((const float*)p.X, (const float*)p.g, (const float*)p.W, (float*)p.Y,
+                                                                    p.M, p.K, p.N, tm, tn, p.eps, 1.0f / float(p.K));
+    return hipGetLastError();
 }
 
 size_t f32_workspace_bytes(const Problem& p)
@@ -475,15 +618,9 @@ hipError_t launch_f32(const Problem& p, hipStream_t s, const char** why)
 {
     F32Plan pl = f32_plan(p);
     if (!pl.ok) { if (why) *why = pl.why; return hipErrorInvalidValue; }
-    if (f32_tiles(p, pl)) {
-        static LdsOnce once;
-        hipError_t e = raise_lds_once(once, {(const void*)f32_tile_kernel}, int(f32_tile_lds(kFtMaxK)));
-        if (e != hipSuccess) return e;
-        const int tm = (p.M + kFtM - 1) / kFtM, tn = (p.N + kFtN - 1) / kFtN;
-        if (p.plan) { p.plan[0] = kFtN; p.plan[1] = 1; p.plan[2] = tm * tn; }
-        f32_tile_kernel<<<tm * tn, 512, f32_tile_lds(p.K), s>>>((const float*)p.X, (const float*)p.g, (const float*)p.W, (float*)p.Y,
-                                                                p.M, p.K, p.N, tm, tn, p.eps, 1.0f / float(p.K));
-        return hipGetLastError();
+    switch (f32_tiles(p, pl)) {
+    case 1: return f32_tile_go<1>(p, s);
+    case 2: return f32_tile_go<2>(p, s);
     }
     if (pl.S > 1 && (!p.ws_partial || !p.ws_sumsq || !p.ws_counter)) {
         if (why) *why = "split-K needs the workspace";

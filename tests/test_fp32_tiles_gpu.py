@@ -1,4 +1,4 @@
-"""GPU tests of the fp32 kernel's 128 x 128 tiles, against the fp64 oracle."""
+"""GPU tests of the fp32 kernel's tiles of 128 columns (numbers as sums of three bf16 numbers), against the fp64 oracle."""
 import numpy as np
 import pytest
 
@@ -54,3 +54,31 @@ def test_special_values(M, K, N):
     assert torch.equal(Y[plain][:, others], clean[plain][:, others])
     assert torch.isnan(Y[127]).all() and torch.isnan(Y[128]).all()
     assert (Y[M - 1, others] == 0).all() and torch.isnan(Y[M - 1, 130])
+
+
+# 64-row tiles (the first three) and 128-row ones: one row or column chunk over a tile, the smallest K, K not a multiple of the four
+# K tiles between two folds, sizes of few tiles; W as it is, so small that its third bf16 parts would be denormal unscaled (all powers
+# of two: the same bits), and so large that the scaled sums overflow and are taken again in fp32
+@pytest.mark.parametrize("M,K,N", [(449, 324, 3908), (961, 196, 1540), (130, 2048, 8192), (65, 68, 20000), (129, 64, 20004)])
+def test_three_parts(M, K, N):
+    import torch
+    import paper_2405_05751_amd as rl
+    w = workloads.make(M, K, N, "f32", 1e-5, 9470 + M, n_check_rows=32)
+    X, g, W = upload(w)
+    Y = rl.rmsnorm_linear(X, g, W, w.eps)
+    assert rl.rl_last_launch()[:3] == ("f32", 128, 1)
+    # (without the entries that would be denormal themselves, and so rounded, times 2^-110)
+    W0 = torch.where(W.abs() < 2.0 ** -15, 0.0, W)
+    base, tiny = rl.rmsnorm_linear(X, g, W0, w.eps), rl.rmsnorm_linear(X, g, W0 * 2.0 ** -110, w.eps)
+    huge = rl.rmsnorm_linear(X, g, W * 2.0 ** 100, w.eps)
+    torch.cuda.synchronize()
+    rows = np.unique(np.concatenate([np.asarray(w.check_rows), [0, 31, 32, 63, 64, M - 2, M - 1]]))
+    Z = oracle.rmsnorm_linear(w.X, w.g, w.W, w.dtype, w.eps, rows=rows)
+    at = torch.from_numpy(rows).cuda()
+    # the bar of the tests above: sums of 64 k, then K / 128 of those, in fp32
+    for got in (Y[at], huge[at] * 2.0 ** -100):
+        ratio, _ = compare(to_host_f64(got, "f32"), Z, "f32", f"{M}x{K}x{N}")
+        assert ratio <= 2e-6, ratio
+    # 2^-15 times 2^-110 is a normal number; below, the result is rounded once more
+    normal = base.abs() >= 2.0 ** -15
+    assert torch.equal(tiny[normal], (base * 2.0 ** -110)[normal])
