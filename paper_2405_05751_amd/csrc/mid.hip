@@ -357,9 +357,13 @@ bool mid_fused(const Problem& p, int cols, int S)
 // The choice is a cost model, fitted (log least squares) to 153 shapes with M 65 to 8000, plain and gated, W from memory, the
 // chip warm (884 timings at both widths and 1 to 8 slabs; 9 % rms): microseconds for the first kernel, for a round of
 // workgroups over the chip (one per compute unit at 128 columns, two at 64) with its K tiles, for W from memory at
-// least, and for writing and adding the partial tiles (all with X-hat as a kernel of its own).  The other forms' models (tile_pre_us, skinny_us) are of the same
-// fit.  The margins are there for the models' errors: on those shapes nothing became more than 4 % slower, 48 changed, and all
-// 153 take 8 % less time (geometric mean) (300 x 1024 x 10000 30 -> 19 us, 654 x 2392 x 4352 50 -> 29 us, 1024 x 4096 x 4096 57 -> 50 us).
+// least, and for writing and adding the partial tiles (all with X-hat as a kernel of its own; a launch that forms it itself takes a tenth
+// less, but for the ones that run only where there is no room).  The other forms' models (tile_pre_us, skinny_us) are of the same
+// fit.  In place of 256 x 256 tiles there is a margin for the models' errors: on those shapes nothing became more than 4 % slower, 48
+// changed, and all 153 take 8 % less time (geometric mean) (654 x 2392 x 4352 50 -> 29 us, 1024 x 4096 x 4096 57 -> 50 us).  In place of row blocks
+// the margin is 4 %: it was 13 %, and a call that 256 x 256 tiles would have run faster than either stayed with the row
+// blocks.  Of 188 more shapes, bf16 and fp16, plain and gated, 20 change with that, two of them 3 and 5 % slower, the others up to a third
+// faster (292 x 6536 x 3688 60.5 -> 41 us, 614 x 4208 x 2280 46 -> 35, 113 x 6624 x 9856 56 -> 48, 509 x 4096 x 4160 62.5 -> 42).
 bool mid_plan(const Problem& p, int* cols, int* S, int* k_slab)
 {
     if (!p.fused || p.dt == F32 || p.N % 8 != 0 || p.K % 8 != 0 || (p.gated && p.N % 16 != 0)) return false;
@@ -380,12 +384,12 @@ bool mid_plan(const Problem& p, int* cols, int* S, int* k_slab)
     if (p.n_tile != 0 || p.M <= 64) return false;
     const double mk = double(p.M) * p.K * 1e-6, mn = double(p.M) * p.N * 1e-6;
     const double w_us = double(p.K) * p.N * 2e-6 / 3.45;
-    // the choice without this kernel; below 16 us it stays: issued one by one such calls take the host as long (not compared in graphs)
+    // the choice without this kernel; below 16 us row blocks stay: issued one by one such calls take the host as long
     const bool skinny = skinny_row_blocks(p);
     const double other = skinny ? skinny_us(p) : tile_pre_us(p);
     if (skinny && other < 16.) return false;
     const bool split = skinny && skinny_workspace_bytes(p) != 0;
-    double best = skinny ? std::min(0.87 * other, tile_pre_us(p)) : 0.85 * other;
+    double best = !skinny ? 0.85 * other : p.no_ws ? std::min(0.87 * other, tile_pre_us(p)) : 0.96 * other;
     *cols = 0;
     for (int c = 64; c <= 128; c += 64)
         for (int s = 1; s <= 8; ++s) {
@@ -399,7 +403,8 @@ bool mid_plan(const Problem& p, int* cols, int* S, int* k_slab)
             const double rounds = double((tiles_m * tiles_n * s + 255) / 256), kt = double((ks + kMidK - 1) / kMidK);
             const double run = c == 128 ? rounds * (4.1 + 0.62 * kt)
                                         : std::ceil(rounds / 2.) * 3.1 + (rounds > 1. ? 0.445 * rounds : 0.48) * kt;
-            const double us = 3.6 + 0.135 * mk + std::max(run, w_us) + (s > 1 ? 0.9 + 2.2 * s * mn : 0.);
+            const double us = (3.6 + 0.135 * mk + std::max(run, w_us) + (s > 1 ? 0.9 + 2.2 * s * mn : 0.)) * (mid_fused(p, c, s) && !p.no_ws ? 0.9 : 1.);
+            if (skinny && s > 1 && other < 19. && us >= 0.87 * other) continue;          // three launches take the host 18 us
             if (us < best) { best = us; *cols = c; *S = s; *k_slab = ks; }
         }
     return *cols != 0;

@@ -200,3 +200,18 @@ print(ex(128, 17), ex(64, 1, 256, 4096, 1 << 22), lib.rl_last_error())
 """)
     assert out == ["True", "0 (5, 64, 3, 96) 0 (5, 128, 1, 16) 0 (256, 2)",
                    "2 2 b'128-row tiles: 1 to 16 slabs, K < 2^23, N < 2^22, and a slab of W below 2 GiB'"]
+
+
+@pytest.mark.parametrize("M,K,N,dt,kernels", [
+    (509, 4096, 4160, "BF16", ["xhat_rows_kernel", "mid_kernel"]),                           # 264 row blocks, 256 compute units
+    (292, 6536, 3688, "F16", ["xhat_rows_kernel", "mid_kernel", "tile_reduce_kernel"]),      # 256 x 256 tiles would beat the row blocks too
+    (1000, 1000, 1000, "BF16", ["mid_kernel"]),
+    (509, 4096, 4096, "BF16", ["skinny_kernel"]), (128, 2048, 2048, "BF16", ["skinny_kernel"]),
+])
+def test_row_blocks_or_128_row_tiles(M, K, N, dt, kernels):
+    """Row blocks only where they are not the slower form, through either entry point."""
+    out = routes.run(f"""
+print(linear({M}, {K}, {N}, {dt}), names())
+print(linear({M}, {K}, {N}, {dt}, 0, 'rmsnorm_linear_noalloc'), [n for n in names() if "scratch_clear" not in n])
+""")
+    assert out == [f"0 {kernels}"] * 2
