@@ -560,7 +560,7 @@ static F32Plan f32_plan(const Problem& p)
 
 // Which problems, and the tile's rows / 64 (0: the kernel above).  By the rounds of workgroups that each needs, K in us: tiles run
 // one to a compute unit and slow down as the chip fills (power), the 64 x 64 tiles above run two, or one in a last round
-// that has no more, and a split over K fills the chip better than larger tiles would.  Fitted to 13 shapes, 6 % rms.  us above, on
+// that has no more, and a split over K fills the chip better than larger tiles would.  Fitted to 13 shapes, 5 to 8 % rms.  us above, on
 // 64 and on 128 rows: 512 x 4096 x 4096 171, 119, 157; 1000 x 2000 x 3000 135, 116, 84; 1500 x 256 x 1000 20.4, 12.6, 17.7;
 // 300 x 1000 x 8192 75, 63, 46; 256 x 4096 x 4096 87, 108, 156; 1024^3 26, 30, 44.
 static int f32_tiles(const Problem& p, const F32Plan& pl)
