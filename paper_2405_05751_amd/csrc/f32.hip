@@ -210,8 +210,9 @@ __global__ __launch_bounds__(256) void f32_kernel(F32Args a)
 // a SIMD at different times; of a step's six products the small ones come first.  Relative error against fp64 1.0e-7 at K = 64,
 // 1.2e-7 at 192, 1.4e-7 at 1000, 1.8e-7 at 4096, 2.1e-7 at 8192 (on fp32 instructions, 128 x 128 tiles: 1.3e-7, 1.4e-7, 1.9e-7 from 192
 // to 4096; the kernel above: 1.0e-7 at 64, 2.2e-7 at 1000 and 4096, 2.3e-7 at 8192; adding into the second accumulator twice as often: 1.0e-7 at 192,
-// but 2.0e-7 at 4096).  2048 x 4096 x 4096: 593 -> 375 us, 183 TFLOP/s (fp32 peak: 157).  Of that the matrix instructions and their LDS
-// reads take 295 us, which is what the chip's power allows them; loads 55 (by leaving them out), splitting 49, second accumulator 20.
+// but 2.0e-7 at 4096).  2048 x 4096 x 4096: 593 -> 375 us, 183 TFLOP/s (fp32 peak: 157). Parts left out: loads 55 us,
+// splitting 49, second accumulator 20.  Counters: the matrix pipes are busy 49 % of the cycles at 2.0 GHz, and the vector instructions, 89 M
+// of them, would take 44 % by themselves; where they stand between the matrix instructions is worth 1 %.
 constexpr int kFtN = 128, kFtK = 32, kFtMinK = 64, kFtMaxK = 16000;        // (g in LDS)
 constexpr unsigned kFtOut = 0x80000000u;     // beyond every resource (sizes below 2^31), with any tile offset added
 constexpr float kFtScale = 0x1p24f;
