@@ -564,10 +564,16 @@ static F32Plan f32_plan(const Problem& p)
 // that has no more, and a split over K fills the chip better than larger tiles would.  Fitted to 13 shapes, 5 to 8 % rms.  us above, on
 // 64 and on 128 rows: 512 x 4096 x 4096 171, 119, 157; 1000 x 2000 x 3000 135, 116, 84; 1500 x 256 x 1000 20.4, 12.6, 17.7;
 // 300 x 1000 x 8192 75, 63, 46; 256 x 4096 x 4096 87, 108, 156; 1024^3 26, 30, 44.
+// One block of rows: the kernel above then works on 16 MB of them, a tile always on 64, and its time no longer follows the
+// estimate, which is that of 64 rows.  Measured on wide N (16k to 64k, K 64 to 12000), tiles over the kernel above: M 1 to 16 1.3 to 2.5
+// (1 x 152 x 34028 21.6 against 8.7 us, 1 x 1912 x 64532 117 against 86), 17 to 32 0.92 to 1.43, 1.12 in the mean of 76 shapes: not used.
+// 33 to 48 rows: where the estimates are further than a fifth apart 0.71 to 0.88 (71 shapes), closer 0.89 to 1.06 (26): a wider
+// margin.  49 to 64: 0.62 to 0.93 (57).
 static int f32_tiles(const Problem& p, const F32Plan& pl)
 {
     if (!pl.ok || pl.S > 1 || !p.fused || p.gated || p.n_tile != 0 || p.k_split != 0 || p.K < kFtMinK || p.K > kFtMaxK) return 0;
     if ((int64_t(p.K) + 512) * p.N * 4 >= (int64_t(1) << 31)) return 0;
+    if (pl.MB <= 2) return 0;
     const int64_t cols = (p.N + kFtN - 1) / kFtN, small = int64_t(pl.n_tiles) * pl.RB;
     const int64_t n1 = (int64_t(p.M) + 63) / 64 * cols, n2 = (int64_t(p.M) + 127) / 128 * cols;
     if (n1 >= (int64_t(1) << 23)) return 0;              // a grid holds fewer than 2^32 threads, 512 to a tile
@@ -578,7 +584,7 @@ static int f32_tiles(const Problem& p, const F32Plan& pl)
     const double t1 = rounds(n1, 5.0, 0.0243 * p.K, 0.0035 * p.K), t2 = rounds(n2, 5.5, 0.0372 * p.K, 0.0085 * p.K);
     const int64_t last = small % 512;
     const double t0 = double(small / 512) * (7.0 + 0.041 * p.K) + (last > 256 ? 7.0 + 0.041 * p.K : last ? 4.0 + 0.0203 * p.K : 0.0);
-    return std::min(t1, t2) >= 0.93 * t0 ? 0 : t1 < t2 ? 1 : 2;
+    return std::min(t1, t2) >= (pl.MB == 3 ? 0.80 : 0.93) * t0 ? 0 : t1 < t2 ? 1 : 2;
 }
 
 template <int TM>

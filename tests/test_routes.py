@@ -215,3 +215,17 @@ print(linear({M}, {K}, {N}, {dt}), names())
 print(linear({M}, {K}, {N}, {dt}, 0, 'rmsnorm_linear_noalloc'), [n for n in names() if "scratch_clear" not in n])
 """)
     assert out == [f"0 {kernels}"] * 2
+
+
+@pytest.mark.parametrize("M,K,N,kernel", [
+    (1, 152, 34028, "f32_kernel"), (1, 4096, 32000, "f32_kernel"), (4, 2048, 20000, "f32_kernel"), (16, 4164, 55336, "f32_kernel"),
+    (17, 2612, 46528, "f32_kernel"), (32, 5448, 30728, "f32_kernel"),
+    (33, 4392, 37972, "f32_kernel"), (47, 1952, 36224, "f32_kernel"), (33, 224, 23864, "f32_tile_kernel"), (48, 4376, 18748, "f32_tile_kernel"),
+    (49, 2388, 23784, "f32_tile_kernel"), (64, 4096, 28672, "f32_tile_kernel"), (65, 68, 20000, "f32_tile_kernel"),
+])
+def test_fp32_rows_of_one_block(M, K, N, kernel):
+    """Tiles of 64 rows only where they are not the slower form: the kernel for row blocks works on 16 rows at a time."""
+    out = routes.run(f"""
+print(linear({M}, {K}, {N}, F32), names())
+""")
+    assert out == [f"0 ['{kernel}']"]
