@@ -357,13 +357,19 @@ bool mid_fused(const Problem& p, int cols, int S)
 // The choice is a cost model, fitted (log least squares) to 153 shapes with M 65 to 8000, plain and gated, W from memory, the
 // chip warm (884 timings at both widths and 1 to 8 slabs; 9 % rms): microseconds for the first kernel, for a round of
 // workgroups over the chip (one per compute unit at 128 columns, two at 64) with its K tiles, for W from memory at
-// least, and for writing and adding the partial tiles (all with X-hat as a kernel of its own; a launch that forms it itself takes a tenth
-// less, but for the ones that run only where there is no room).  The other forms' models (tile_pre_us, skinny_us) are of the same
-// fit.  In place of 256 x 256 tiles there is a margin for the models' errors: on those shapes nothing became more than 4 % slower, 48
-// changed, and all 153 take 8 % less time (geometric mean) (654 x 2392 x 4352 50 -> 29 us, 1024 x 4096 x 4096 57 -> 50 us).  In place of row blocks
-// the margin is 4 %: it was 13 %, and a call that 256 x 256 tiles would have run faster than either stayed with the row
-// blocks.  Of 188 more shapes, bf16 and fp16, plain and gated, 20 change with that, two of them 3 and 5 % slower, the others up to a third
-// faster (292 x 6536 x 3688 60.5 -> 41 us, 614 x 4208 x 2280 46 -> 35, 113 x 6624 x 9856 56 -> 48, 509 x 4096 x 4160 62.5 -> 42).
+// least, and for writing and adding the partial tiles, all with X-hat as a kernel of its own.  The other forms' models (tile_pre_us,
+// skinny_us) are of the same fit.  In place of 256 x 256 tiles there is a margin for the models' errors (654 x 2392 x 4352 50 -> 29 us,
+// 1024 x 4096 x 4096 57 -> 50 us), in place of row blocks it is 4 %: against a margin of 13 % with which a call that 256 x 256 tiles
+// would have run faster than either stayed with the row blocks, 547 changed shapes take 0.80 of the time (geometric mean: 292 x 6536 x 3688
+// 60.5 -> 41 us, 614 x 4208 x 2280 46 -> 35, 113 x 6624 x 9856 56 -> 48, 509 x 4096 x 4160 62.5 -> 42), 27 of them, splits
+// that take 17 to 24 us, 3 to 16 % more.
+// A launch that forms X-hat itself (but for one that does so because there is no room) is put at a tenth less, since it has no first kernel, where that
+// is so: at 64 columns two workgroups to a unit hide the work of forming it, many rows make the first kernel long, few K tiles the
+// product short; one workgroup to a unit over a long K is slower than a split with the kernel (109 x 2840 x 2*4840 fp16 36 against 25 us,
+// 887 x 3696 x 2*904 40 against 31; with one row of tiles nobody shares W either), and so is, against 256 x 256 tiles, a chip full of 128
+// columns (3414 x 7632 x 2*2584 447 against 366).  Of 1264 shapes whose choice a tenth anywhere or here changes, this rule takes the fastest form measured within
+// 0.3 % (geometric mean), 0.83 of the time with no tenth; 19 are 3 to 16 % slower than without, 149 were (up to 48 %) with it everywhere.
+// (220 shapes not used for the rule: 0.80; 4 of 106 against row blocks and 2 of 114 against the rest are 3 to 11 % slower.)
 bool mid_plan(const Problem& p, int* cols, int* S, int* k_slab)
 {
     if (!p.fused || p.dt == F32 || p.N % 8 != 0 || p.K % 8 != 0 || (p.gated && p.N % 16 != 0)) return false;
@@ -403,7 +409,10 @@ bool mid_plan(const Problem& p, int* cols, int* S, int* k_slab)
             const double rounds = double((tiles_m * tiles_n * s + 255) / 256), kt = double((ks + kMidK - 1) / kMidK);
             const double run = c == 128 ? rounds * (4.1 + 0.62 * kt)
                                         : std::ceil(rounds / 2.) * 3.1 + (rounds > 1. ? 0.445 * rounds : 0.48) * kt;
-            const double us = (3.6 + 0.135 * mk + std::max(run, w_us) + (s > 1 ? 0.9 + 2.2 * s * mn : 0.)) * (mid_fused(p, c, s) && !p.no_ws ? 0.9 : 1.);
+            const bool tenth = mid_fused(p, c, s) && !p.no_ws &&
+                (c == 128 ? tiles_m * tiles_n <= 496 || (tiles_m >= 16 && p.K <= 2500)
+                          : rounds > 1. || tiles_m >= 16 || p.K <= (tiles_m > 1 ? 2500 : 1280));
+            const double us = (3.6 + 0.135 * mk + std::max(run, w_us) + (s > 1 ? 0.9 + 2.2 * s * mn : 0.)) * (tenth ? 0.9 : 1.);
             if (skinny && s > 1 && other < 19. && us >= 0.87 * other) continue;          // three launches take the host 18 us
             if (us < best) { best = us; *cols = c; *S = s; *k_slab = ks; }
         }

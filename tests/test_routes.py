@@ -229,3 +229,25 @@ def test_fp32_rows_of_one_block(M, K, N, kernel):
 print(linear({M}, {K}, {N}, F32), names())
 """)
     assert out == [f"0 ['{kernel}']"]
+
+
+SPLIT, UNSPLIT, WIDE = ["xhat_rows_kernel", "mid_kernel", "tile_reduce_kernel"], ["mid_kernel"], ["xhat_rows_kernel", "tile_kernel"]
+
+
+@pytest.mark.parametrize("fn,M,K,N,dt,kernels", [
+    # a workgroup or less to a unit: long K, one row of tiles and several, up to K = 1280 and 2500
+    ("rmsnorm_gated_mlp", 109, 2840, 4840, "F16", SPLIT), ("rmsnorm_linear", 104, 3256, 9352, "F16", SPLIT),
+    ("rmsnorm_linear", 127, 1528, 5864, "F16", SPLIT), ("rmsnorm_gated_mlp", 887, 3696, 904, "F16", SPLIT), ("rmsnorm_linear", 1036, 2672, 1040, "BF16", SPLIT),
+    ("rmsnorm_linear", 862, 1544, 2136, "BF16", UNSPLIT), ("rmsnorm_linear", 7117, 224, 352, "BF16", UNSPLIT),
+    # many rows
+    ("rmsnorm_linear", 5988, 3808, 192, "F16", UNSPLIT), ("rmsnorm_linear", 4939, 328, 1632, "F16", UNSPLIT), ("rmsnorm_linear", 6126, 448, 832, "F16", UNSPLIT),
+    # a full chip of 128-column tiles
+    ("rmsnorm_gated_mlp", 3414, 7632, 2584, "F16", WIDE), ("rmsnorm_gated_mlp", 1118, 3400, 3560, "F16", WIDE), ("rmsnorm_linear", 731, 768, 10840, "F16", WIDE),
+])
+def test_tiles_that_form_x_hat_themselves(fn, M, K, N, dt, kernels):
+    """128-row tiles without a first kernel only where that is not slower than a split, or 256 x 256 tiles, with one."""
+    out = routes.run(f"""
+lib.rmsnorm_gated_mlp.argtypes = [V, V, V, F, V, L, L, L, I, V]
+print(linear({M}, {K}, {N}, {dt}, 0, {fn!r}), [n for n in names() if "scratch_clear" not in n])
+""")
+    assert out == [f"0 {kernels}"]
