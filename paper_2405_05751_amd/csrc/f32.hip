@@ -257,7 +257,7 @@ __global__ __launch_bounds__(512, 2) void f32_tile_kernel(const float* X, const 
     extern __shared__ __attribute__((aligned(16))) float smem[];
     u16* planes = (u16*)smem;                // [2]{ X-hat [3][BM][BK], W [3][BK][BN] }, see below
     float* gs = smem + BUF;               // g, K rounded up to a multiple of 4 BK (and one more tile), zeros behind it
-    __shared__ float s_ss[BM];
+    __shared__ __attribute__((aligned(16))) float s_ss[BM];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kg = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
@@ -405,52 +405,95 @@ __global__ __launch_bounds__(512, 2) void f32_tile_kernel(const float* X, const 
         for (int p = 0; p < TM; ++p) { ss_tot[p] += ss[p]; ss[p] = 0.f; }
     }
     if (kg == 1) fold();
+    bool inf = false;
 #pragma unroll
     for (int p = 0; p < TM; ++p) {
         float v = ss_tot[p];
 #pragma unroll
         for (int o = 1; o < 8; o <<= 1) v += __shfl_xor(v, o, 64);
         if ((lane & 7) == 0) s_ss[8 * (wave + 8 * p) + (lane >> 3)] = v;
+        inf |= v == INFINITY;
+    }
+    // A row of X with a NaN in it has NaN squares and gives NaN whatever its sums are.  So does one with an infinity (the sums are not
+    // finite, the row's factor is zero), but its squares are infinite, as they are where they overflow: such rows are read again.
+    if (__syncthreads_or(inf)) {
+        for (int r = wave; r < BM; r += 8) {
+            if (s_ss[r] != INFINITY) continue;
+            float nan = 0.f;
+            for (int k = 4 * lane; k < K; k += 256) {
+                const float4_t x = __builtin_bit_cast(float4_t, __builtin_amdgcn_raw_buffer_load_b128(xrs, (r * K + k) * 4, 0, 0));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) nan = __fmaf_rn(x[e], 0.f, nan);
+            }
+            if (__any(nan != 0.f) && lane == 0) s_ss[r] = NAN;
+        }
+        __syncthreads();
     }
     // An infinity is no sum of bf16 numbers (its remainder is NaN), and what is scaled may overflow: the sums that are not
-    // finite are taken again, over the same k, on the fp32 matrix instructions, operands straight from memory
+    // finite, of rows that are, are taken again, over the same k, on the fp32 matrix instructions, operands straight from memory
+    // one step of 16 k ahead (2048 x 1024 x 4096, W of 1e34: 235 us, 323 with every step waiting for its own; a NaN or an infinity in
+    // every 64th row of X 103 and 108, 330 when those rows' sums were taken again too; everything finite 103)
     float nan = 0.f;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int q = 0; q < 4; ++q) {
+            const float4_t ss4 = *(const float4_t*)(s_ss + wm * 32 * TM + i * 32 + 8 * q + 4 * h);
 #pragma unroll
-            for (int r = 0; r < 16; ++r) nan = __fmaf_rn(tot[i][j][r], 0.f, nan);
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) nan = __fmaf_rn(ss4[e] == ss4[e] ? tot[i][j][4 * q + e] : 0.f, 0.f, nan);
+        }
     const bool again = __syncthreads_or(nan != 0.f);     // (NaN != 0)
     float16_t sum[TM][2];
     clear(sum);
-    for (int k0 = 0; again && k0 < K; k0 += 4 * BK) {
-        clear(acc);
-        for (int u = 0; u < 8; ++u) {
-            const int k = k0 + BK * (u >> 1) + 16 * kg + 8 * (u & 1) + 4 * h;
-            const bool kin = k < K;
-            const float4_t gv = *(const float4_t*)(gs + k);
-            float4_t xh[TM];
-            float w[4][2];
+    float4_t xa[2][TM];
+    float wa[2][4][2];
+    unsigned wa_off[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) wa_off[j] = n0 + wn * 64 + j * 32 + c < N ? unsigned(n0 + wn * 64 + j * 32 + c) * 4u : kFtOut;
+    auto fetch = [&](auto set, int n) {      // this group's eight of the 16 k of step n; past K: zeros (W's lie beyond its resource)
+        constexpr int st = decltype(set)::value;
+        const int k = BK * (n >> 1) + 16 * kg + 8 * (n & 1) + 4 * h;
+        const unsigned xo = unsigned(a_row * K + k) * 4u, wo = unsigned(k * N) * 4u;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+            xa[st][i] = __builtin_bit_cast(float4_t, __builtin_amdgcn_raw_buffer_load_b128(
+                xrs, int(k < K ? xo + unsigned(32 * i * K) * 4u : kFtOut), 0, 0));
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                wa[st][e][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                    wrs, int(wa_off[j] + wo + unsigned(e * N) * 4u), 0, 0));
+    };
+    auto step = [&](auto set, int n) {
+        constexpr int st = decltype(set)::value;
+        const float4_t gv = *(const float4_t*)(gs + BK * (n >> 1) + 16 * kg + 8 * (n & 1) + 4 * h);
+        float4_t xh[TM];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) xh[i] = xa[st][i] * gv;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
 #pragma unroll
             for (int i = 0; i < TM; ++i)
-                xh[i] = __builtin_bit_cast(float4_t, __builtin_amdgcn_raw_buffer_load_b128(
-                    xrs, int(kin ? unsigned((a_row + 32 * i) * K + k) * 4u : kFtOut), 0, 0)) * gv;
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    const int col = n0 + wn * 64 + j * 32 + c;
-                    w[e][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
-                        wrs, int(kin && col < N ? unsigned((k + e) * N + col) * 4u : kFtOut), 0, 0));
-                }
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < 2; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(xh[i][e], w[e][j], acc[i][j], 0, 0, 0);
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(xh[i][e], wa[st][e][j], acc[i][j], 0, 0, 0);
+    };
+    if (again) fetch(even, 0);
+    for (int n = 0; again && n < 2 * nk; n += 8) {
+        clear(acc);
+#pragma unroll 1
+        for (int u = n; u < n + 8; u += 2) {
+            fetch(odd, u + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            step(even, u);
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(even, u + 2);
+            __builtin_amdgcn_sched_barrier(0);
+            step(odd, u + 1);
+            __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
         for (int i = 0; i < TM; ++i)

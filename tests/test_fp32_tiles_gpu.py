@@ -32,9 +32,10 @@ def test_tiles(M, K, N):
     assert ratio <= 2e-6, ratio
 
 
-@pytest.mark.parametrize("M,K,N", [(1921, 292, 1924), (1023, 1000, 4092)])
-def test_special_values(M, K, N):
-    """Infinities in W keep sign and column, NaN and infinity in X keep to their rows, a zero row gives zeros."""
+@pytest.mark.parametrize("M,K,N,rows", [(1921, 292, 1924, 128), (1023, 1000, 4092, 128), (449, 324, 3908, 64), (961, 196, 1540, 64)])
+def test_special_values(M, K, N, rows):
+    """Infinities in W keep sign and column, NaN and infinity in X keep to their rows, a zero row gives zeros, and so does one whose
+    squares overflow (its scaled sums do too, beside a row that is not finite and without one)."""
     import torch
     import paper_2405_05751_amd as rl
     w = workloads.make(M, K, N, "f32", 1e-5, 9450, n_check_rows=8)
@@ -45,15 +46,46 @@ def test_special_values(M, K, N):
     X[M - 1] = 0.0
     X[127, 3] = float("nan")
     X[128, K - 2] = float("inf")
+    huge = [5, 130, M - 2]
+    X[huge] *= 1e25
     Y = rl.rmsnorm_linear(X, g, W, w.eps)
     torch.cuda.synchronize()
-    assert rl.rl_last_launch()[:3] == ("f32", 128, 1)
-    plain = torch.tensor([r for r in range(M) if r not in (127, 128, M - 1)], device="cuda")
+    assert rl.rl_last_launch() == ("f32", 128, 1, -(-M // rows) * -(-N // 128))
+    plain = torch.tensor([r for r in range(M) if r not in (127, 128, M - 1, *huge)], device="cuda")
     others = torch.tensor([n for n in range(N) if n != 130], device="cuda")
     assert torch.equal(Y[plain, 130], X[plain, K - 1] * float("inf"))
     assert torch.equal(Y[plain][:, others], clean[plain][:, others])
     assert torch.isnan(Y[127]).all() and torch.isnan(Y[128]).all()
-    assert (Y[M - 1, others] == 0).all() and torch.isnan(Y[M - 1, 130])
+    for r in [M - 1, *huge]:
+        assert (Y[r, others] == 0).all() and torch.isnan(Y[r, 130])
+
+
+@pytest.mark.parametrize("M,K,N", [(2048, 1024, 4096), (512, 4096, 4096)])
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+def test_rows_that_are_not_finite_take_no_longer(M, K, N, value):
+    """They give NaN whatever their sums are, so no sum is taken twice for them (that took two to three times as long)."""
+    import torch
+    import paper_2405_05751_amd as rl
+    w = workloads.make(M, K, N, "f32", 1e-5, 9460, n_check_rows=1)
+    X, g, W = upload(w)
+    bad = X.clone()
+    bad[::64, 7] = value
+    Y = torch.empty(M, N, device="cuda")
+
+    def best(x):
+        start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        us = []
+        for _ in range(6):
+            start.record()
+            for _ in range(20):
+                rl.rmsnorm_linear(x, g, W, w.eps, Y)
+            end.record()
+            torch.cuda.synchronize()
+            us.append(start.elapsed_time(end))
+        return min(us)
+    clean, slow = best(X), best(bad)
+    assert torch.isnan(Y[::64]).all() and not torch.isnan(Y[1::64]).any()
+    assert slow <= 1.5 * clean, (clean, slow)
 
 
 # 64-row tiles (the first three) and 128-row ones: one row or column chunk over a tile, the smallest K, K not a multiple of the four
