@@ -333,6 +333,13 @@ __device__ __forceinline__ void load_lds(const uint4_t& rsrc, uint32_t dst, unsi
                  : "=&s"(keep) : "s"(dst), "v"(v), "s"(desc) : "memory");
 }
 
+// Transposing LDS read of 4 x 16-bit values (the header of tile.hip says which lane gets what).
+typedef __attribute__((ext_vector_type(4))) short short4_t;
+typedef __attribute__((address_space(3))) short4_t* lds_short4_ptr;
+__device__ __forceinline__ uint2_t lds_read_tr(const u16* p) {
+    return __builtin_bit_cast(uint2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(p)));
+}
+
 // Workgroup b of n: consecutive workgroups go to the 8 XCDs in turn, so XCD x holds those with b % 8 == x.  The
 // number returned runs through 0 .. n - 1 so that each XCD gets a run of consecutive ones (shares
 // differ by one at most), and what neighbours share, it finds in its own L2.

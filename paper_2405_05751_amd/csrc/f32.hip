@@ -1,8 +1,8 @@
-// The fp32 path of the fused block on the matrix cores (fp32 products, fp32
-// sums): the case study's Fig. 2b again -- A_i = sum_k X_ik^2 and B_in = sum_k (X_ik g_k)
-// W_kn in one K loop, the division by the root mean square after it -- on 4-byte elements.  Two kernels: the one
-// described here (v_mfma_f32_16x16x4_f32), which runs every M, and further down one on 128 x 128 tiles through LDS for
-// large problems with K from 192 to 4096 (f32_tiles() has the rule).
+// The fp32 path of the fused block on the matrix cores: the case study's Fig. 2b again -- A_i = sum_k X_ik^2 and
+// B_in = sum_k (X_ik g_k) W_kn in one K loop, the division by the root mean square after it -- on 4-byte elements, sums in
+// fp32.  Two kernels: the one described here (v_mfma_f32_16x16x4_f32, fp32 products), which runs every M, and further down one for
+// larger problems with K from 64 to 16000, tiles of 64 or 128 rows x 128 columns through LDS on the bf16 matrix instructions, three
+// bf16 numbers to an fp32 one (f32_tiles() has the rule).
 //
 // A workgroup (4 waves) owns 16 MB rows (MB = 1..4) x 64 columns of Y over one K slab; its waves
 // take the slab's 16-row runs of W in turn.  fp32 matrix instructions are slow enough (64 flops
@@ -198,31 +198,31 @@ __global__ __launch_bounds__(256) void f32_kernel(F32Args a)
 // ---- large problems: tiles of 128 columns on the bf16 matrix cores
 // The fp32 matrix instructions run at 1/16 of the bf16 rate (and the kernel above keeps them busy 65 % of the time).  A finite
 // fp32 number is the sum of three bf16 numbers, its value rounded to bf16, the remainder rounded, and what is left, each exact; the
-// product of two such sums is nine products, exact in fp32, of which the three smallest (together below 2^-26 of the product) are
-// left out.  Six v_mfma_f32_32x32x16_bf16 then stand for eight v_mfma_f32_32x32x2_f32 of four times the time each.
-// What must hold for that: the remainders are no denormals (both operands are scaled by 2^24, the sums back, so that this
+// product of two such sums is nine products, exact in fp32, of which the three smallest are left out (BF16x3 of Henry, Tang and
+// Heinecke, ARITH 2019).  Six v_mfma_f32_32x32x16_bf16 then stand for eight v_mfma_f32_32x32x2_f32 of four times the time each.
+// What is left out is at most 2^-24 of the product, one rounding of it (1 + 2^-8 - 2^-17 times itself), 2^-27.4 in the root mean square of
+// random numbers.  It does not show beside the rounding of the sums: with the two larger ones of the three in, errors are the same
+// within 1 % (2048 x 4096 x 4096, N(0, 1): 1.77e-7 either way) or larger, since each is one more rounding of the sum, at 14 % more time.
+// What must hold: the remainders are no denormals (both operands are scaled by 2^24, the sums back, so that this
 // holds down to the smallest fp32 numbers), and everything is finite (sums that are not are taken again in fp32, see below).
 //
 // X (.) g (formed in fp32) and W come through registers, two K tiles of 32 ahead: split there, and written to LDS as three bf16
 // planes each, in two buffers.  8 waves in two groups; a group takes 16 of the 32 k, a wave 32 TM x 64 of the tile.  Scaling and
 // splitting is vector work for the next K tile between the matrix instructions of this one.
 // Sums: a matrix accumulator takes 64 k of its group (128 of the tile) and is then added into a second one, by the two waves of
-// a SIMD at different times; of a step's six products the small ones come first.  Relative error against fp64 1.0e-7 at K = 64,
+// a SIMD at different times; of a step's six products the small ones come first.  Relative error against fp64 on N(0, 1) 0.93e-7 at K = 64,
 // 1.2e-7 at 192, 1.4e-7 at 1000, 1.8e-7 at 4096, 2.1e-7 at 8192 (on fp32 instructions, 128 x 128 tiles: 1.3e-7, 1.4e-7, 1.9e-7 from 192
 // to 4096; the kernel above: 1.0e-7 at 64, 2.2e-7 at 1000 and 4096, 2.3e-7 at 8192; adding into the second accumulator twice as often: 1.0e-7 at 192,
-// but 2.0e-7 at 4096).  2048 x 4096 x 4096: 593 -> 375 us, 183 TFLOP/s (fp32 peak: 157). Parts left out: loads 55 us,
+// but 2.0e-7 at 4096).  Six roundings of a sum for 16 k and not one a k: less error where terms cancel, more where sums are
+// nearly exact or grow evenly: rows with one entry 6.6e-8 against 6.2e-8; |N(0, 1)| 8.1e-8 against 7.8e-8 at K = 192, but 9.0e-8 against 11.1e-8 at 4096 (the
+// kernel above: 7.4e-8); all entries +-(1 + 2^-8 - 2^-17) times powers of two 1.3e-7 against 0.9e-7.
+// 2048 x 4096 x 4096: 590-612 us on fp32 instructions, 364-378 here, 182-189 TFLOP/s (fp32 peak: 157). Parts left out: loads 55 us,
 // splitting 49, second accumulator 20.  Counters: the matrix pipes are busy 49 % of the cycles at 2.0 GHz, and the vector instructions, 89 M
 // of them, would take 44 % by themselves; where they stand between the matrix instructions is worth 1 %.
 constexpr int kFtN = 128, kFtK = 32, kFtMinK = 64, kFtMaxK = 16000;        // (g in LDS)
 constexpr unsigned kFtOut = 0x80000000u;     // beyond every resource (sizes below 2^31), with any tile offset added
 constexpr float kFtScale = 0x1p24f;
 constexpr int ft_buf(int TM) { return 3 * (64 * TM + kFtN) * kFtK; }          // elements of a buffer
-
-typedef __attribute__((ext_vector_type(4))) short f32_short4_t;
-typedef __attribute__((address_space(3))) f32_short4_t* f32_lds_ptr;
-__device__ __forceinline__ uint2_t f32_read_tr(const u16* p) {
-    return __builtin_bit_cast(uint2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((f32_lds_ptr)(p)));
-}
 
 // n times a matrix instruction and v vector instructions behind it
 #define RL_F32_MIX(n, v) \
@@ -269,7 +269,6 @@ __global__ __launch_bounds__(512, 2) void f32_tile_kernel(const float* X, const 
 
     const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(X + size_t(m0) * K), 0, min(BM, M - m0) * K * 4, kF32Flags);
     const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(W), 0, K * N * 4, kF32Flags);
-    const __amdgpu_buffer_rsrc_t grs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(g), 0, K * 4, kF32Flags);
     // a wave's load of X is 8 rows of 128 bytes, of W 2 rows of 512
     // (64 rows, 16 rows further on for the second one)
     const int xrow = 8 * wave + (lane >> 3), xk = 4 * (lane & 7), wrow = 2 * wave + (lane >> 5), wcol = 4 * (lane & 31);
@@ -345,7 +344,7 @@ __global__ __launch_bounds__(512, 2) void f32_tile_kernel(const float* X, const 
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const u16* Bb = pl + q * BK * BN + (b_off ^ (32 * j));
-                const uint2_t lo = f32_read_tr(Bb), hi = f32_read_tr(Bb + 4 * BN);
+                const uint2_t lo = lds_read_tr(Bb), hi = lds_read_tr(Bb + 4 * BN);
                 bf[q][j] = uint4_t{lo[0], lo[1], hi[0], hi[1]};
             }
         };

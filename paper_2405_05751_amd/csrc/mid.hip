@@ -79,12 +79,6 @@ template <> struct MidPair<Fp16> {
     }
 };
 
-typedef __attribute__((ext_vector_type(4))) short mid_short4_t;
-typedef __attribute__((address_space(3))) mid_short4_t* mid_lds_ptr;
-__device__ __forceinline__ uint2_t mid_read_tr(const u16* p) {
-    return __builtin_bit_cast(uint2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((mid_lds_ptr)(p)));
-}
-
 #define RL_MID_WAIT_VM(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (((n) >> 4) << 14) | (7 << 4) | (15 << 8))
 
 template <typename T, int BN, bool GATED, bool SPLIT, bool FUSED>
@@ -181,7 +175,7 @@ __global__ __launch_bounds__(512, BN == 64 ? 4 : 2) void mid_kernel(MidArgs a)
             const u16* Bb = Bs + buf * BK * BN + s * 16 * BN;
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
-                const uint2_t lo = mid_read_tr(Bb + b_off[j]), hi = mid_read_tr(Bb + b_off[j] + 4 * BN);
+                const uint2_t lo = lds_read_tr(Bb + b_off[j]), hi = lds_read_tr(Bb + b_off[j] + 4 * BN);
                 bf[st][s][j] = uint4_t{lo[0], lo[1], hi[0], hi[1]};
             }
 #pragma unroll

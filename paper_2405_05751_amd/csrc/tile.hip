@@ -111,15 +111,6 @@ template <> struct Mfma32<Fp16> {
     }
 };
 
-typedef __attribute__((ext_vector_type(4))) short short4_t;
-typedef __attribute__((address_space(3))) short4_t* lds_short4_ptr;
-
-// transposing LDS read of 4 x 16-bit values (see the header comment)
-__device__ __forceinline__ uint2_t lds_read_tr(const u16* p) {
-    short4_t v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(p));
-    return __builtin_bit_cast(uint2_t, v);
-}
-
 // sum of the squares of a packed pair of 16-bit values, added to acc (one v_dot2c instead of two
 // unpacks and two fused multiply-adds)
 template <typename T> struct SqPair;
