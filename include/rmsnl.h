@@ -72,8 +72,9 @@ typedef enum {
     RL_MFMA_F32 = 6       /* fp32 only, any M, K % 4 == 0 and N % 4 == 0, W below 4 GiB: matrix cores on fp32 operands
                              (fp32 products and sums, two levels of accumulators), 64 rows x 64 columns per workgroup,
                              K split over its waves and into 1 to 16 slabs over workgroups; where they are faster and K is 64 to
-                             16000, tiles of 64 or 128 rows x 128 columns instead (rl_last_launch: 128 columns), unless a shape is forced:
-                             every number as the sum of three bf16 numbers on the bf16 matrix cores, as close to fp64 */
+                             16000, tiles of 64 or (K to 4096) 128 rows x 128 columns instead (rl_last_launch: 128 columns), unless a shape is
+                             forced: every number as the sum of three bf16 numbers on the bf16 matrix cores, on N(0, 1) entries closer to
+                             fp64 (single products are not: up to 2^-24 of one is left out) */
 } rl_variant;
 
 /*

@@ -210,16 +210,19 @@ __global__ __launch_bounds__(256) void f32_kernel(F32Args a)
 // planes each, in two buffers.  8 waves in two groups; a group takes 16 of the 32 k, a wave 32 TM x 64 of the tile.  Scaling and
 // splitting is vector work for the next K tile between the matrix instructions of this one.
 // Sums: a matrix accumulator takes 64 k of its group (128 of the tile) and is then added into a second one, by the two waves of
-// a SIMD at different times; of a step's six products the small ones come first.  Relative error against fp64 on N(0, 1) 0.93e-7 at K = 64,
-// 1.2e-7 at 192, 1.4e-7 at 1000, 1.8e-7 at 4096, 2.1e-7 at 8192 (on fp32 instructions, 128 x 128 tiles: 1.3e-7, 1.4e-7, 1.9e-7 from 192
-// to 4096; the kernel above: 1.0e-7 at 64, 2.2e-7 at 1000 and 4096, 2.3e-7 at 8192; adding into the second accumulator twice as often: 1.0e-7 at 192,
-// but 2.0e-7 at 4096).  Six roundings of a sum for 16 k and not one a k: less error where terms cancel, more where sums are
-// nearly exact or grow evenly: rows with one entry 6.6e-8 against 6.2e-8; |N(0, 1)| 8.1e-8 against 7.8e-8 at K = 192, but 9.0e-8 against 11.1e-8 at 4096 (the
-// kernel above: 7.4e-8); all entries +-(1 + 2^-8 - 2^-17) times powers of two 1.3e-7 against 0.9e-7.
+// a SIMD at different times; with 64 rows the second one goes into a third after 1024 k of the tile.  128 rows have no registers for
+// that, and so run up to K = 4096 only.  Of a step's six products the small ones come first.  Relative error against fp64
+// on N(0, 1), 2-norm, here (128 rows; 64) and in the kernel above:
+//   K = 64: 0.93e-7, 1.02e-7; 192: 1.21e-7, 1.44e-7; 1000: 1.43e-7, 2.15e-7; 4096: 1.77e-7; 1.58e-7, 2.22e-7; 8192: 1.74e-7, 2.28e-7; 16000: 2.0e-7, 2.40e-7
+// (128 x 128 tiles on fp32 instructions: 1.27e-7 at 192, 1.44e-7 at 1000, 1.92e-7 at 4096; two accumulators at K = 16000: 2.7e-7, the largest
+// error 2.4e-6 of the rms against 1.2e-6 with three and 1.4e-6 above, and 1.4e-7 against 0.8e-7 for sums of positive terms; adding into the second
+// one twice as often: 2.0e-7 at 4096).  Six roundings of a sum for 16 k and not one a k: less error where terms cancel, more where sums
+// are nearly exact: rows with one entry 6.6e-8 against 6.2e-8; |N(0, 1)| 8.1e-8 against 7.8e-8 (128 x 128) at K = 192, 7.2e-8 against 7.5e-8
+// (64 rows) at 4096; all entries +-(1 + 2^-8 - 2^-17) times powers of two 1.3e-7 against 0.9e-7.
 // 2048 x 4096 x 4096: 590-612 us on fp32 instructions, 364-378 here, 182-189 TFLOP/s (fp32 peak: 157). Parts left out: loads 55 us,
 // splitting 49, second accumulator 20.  Counters: the matrix pipes are busy 49 % of the cycles at 2.0 GHz, and the vector instructions, 89 M
 // of them, would take 44 % by themselves; where they stand between the matrix instructions is worth 1 %.
-constexpr int kFtN = 128, kFtK = 32, kFtMinK = 64, kFtMaxK = 16000;        // (g in LDS)
+constexpr int kFtN = 128, kFtK = 32, kFtMinK = 64, kFtMaxK = 16000, kFtMaxK2 = 4096;        // (g in LDS; of 128 rows)
 constexpr unsigned kFtOut = 0x80000000u;     // beyond every resource (sizes below 2^31), with any tile offset added
 constexpr float kFtScale = 0x1p24f;
 constexpr int ft_buf(int TM) { return 3 * (64 * TM + kFtN) * kFtK; }          // elements of a buffer
@@ -328,6 +331,13 @@ __global__ __launch_bounds__(512, 2) void f32_tile_kernel(const float* X, const 
 #pragma unroll
                 for (int r = 0; r < 16; ++r) tot[i][j][r] += acc[i][j][r];
     };
+    float16_t top[2];                        // 64 rows: the third accumulator
+    auto raise = [&]() {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) { top[j][r] += tot[0][j][r]; tot[0][j][r] = 0.f; }
+    };
     const std::integral_constant<int, 0> even;
     const std::integral_constant<int, 1> odd;
     // iteration t: products of K tile t out of buffer t % 2, K tile t + 1 into the other one, loads of K tile t + 3
@@ -385,6 +395,11 @@ __global__ __launch_bounds__(512, 2) void f32_tile_kernel(const float* X, const 
     };
     clear(acc);
     clear(tot);
+    if (TM == 1)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) top[j][r] = 0.f;
     load_tile(even, 0);
     load_tile(odd, 1);
     for (int k = tid; k < (K + 4 * BK - 1) / (4 * BK) * (4 * BK) + BK; k += 512) gs[k] = k < K ? g[k] : 0.f;
@@ -402,8 +417,14 @@ __global__ __launch_bounds__(512, 2) void f32_tile_kernel(const float* X, const 
         if (kg == 0) fold();
 #pragma unroll
         for (int p = 0; p < TM; ++p) { ss_tot[p] += ss[p]; ss[p] = 0.f; }
+        if (TM == 1 && (t & 28) == 28) raise();
     }
     if (kg == 1) fold();
+    if (TM == 1) {
+        raise();
+        tot[0][0] = top[0];
+        tot[0][1] = top[1];
+    }
     bool inf = false;
 #pragma unroll
     for (int p = 0; p < TM; ++p) {
@@ -605,7 +626,8 @@ static F32Plan f32_plan(const Problem& p)
 // one to a compute unit and slow down as the chip fills (power), the 64 x 64 tiles above run two, or one in a last round
 // that has no more, and a split over K fills the chip better than larger tiles would.  Fitted to 13 shapes, 5 to 8 % rms.  us above, on
 // 64 and on 128 rows: 512 x 4096 x 4096 171, 119, 157; 1000 x 2000 x 3000 135, 116, 84; 1500 x 256 x 1000 20.4, 12.6, 17.7;
-// 300 x 1000 x 8192 75, 63, 46; 256 x 4096 x 4096 87, 108, 156; 1024^3 26, 30, 44.
+// 300 x 1000 x 8192 75, 63, 46; 256 x 4096 x 4096 87, 108, 156; 1024^3 26, 30, 44.  Above K = 4096, where 128 rows would be further from fp64:
+// 2048 x 8192 x 2048 658, 451 (388); 700 x 8192 x 3072 490, 419 (317).
 // One block of rows: the kernel above then works on 16 MB of them, a tile always on 64, and its time no longer follows the
 // estimate, which is that of 64 rows.  Measured on wide N (16k to 64k, K 64 to 12000), tiles over the kernel above: M 1 to 16 1.3 to 2.5
 // (1 x 152 x 34028 21.6 against 8.7 us, 1 x 1912 x 64532 117 against 86), 17 to 32 0.92 to 1.43, 1.12 in the mean of 76 shapes: not used.
@@ -623,7 +645,7 @@ static int f32_tiles(const Problem& p, const F32Plan& pl)
         const double last = double(n % 256);
         return double(n / 256) * (fixed + empty + full) + (last > 0. ? fixed + empty + full * last / 256. : 0.);
     };
-    const double t1 = rounds(n1, 5.0, 0.0243 * p.K, 0.0035 * p.K), t2 = rounds(n2, 5.5, 0.0372 * p.K, 0.0085 * p.K);
+    const double t1 = rounds(n1, 5.0, 0.0243 * p.K, 0.0035 * p.K), t2 = p.K > kFtMaxK2 ? 1e30 : rounds(n2, 5.5, 0.0372 * p.K, 0.0085 * p.K);
     const int64_t last = small % 512;
     const double t0 = double(small / 512) * (7.0 + 0.041 * p.K) + (last > 256 ? 7.0 + 0.041 * p.K : last ? 4.0 + 0.0203 * p.K : 0.0);
     return std::min(t1, t2) >= (pl.MB == 3 ? 0.80 : 0.93) * t0 ? 0 : t1 < t2 ? 1 : 2;
