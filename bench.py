@@ -33,8 +33,13 @@ MFMA_PEAK_TFLOPS = 2500.0        # MI355X dense bf16/fp16 matrix, published (2.5
 MFMA_PEAK_TFLOPS_F32 = 157.3     # MI355X fp32 matrix, published
 
 
-def mfma_peak(dtype):
-    return MFMA_PEAK_TFLOPS_F32 if dtype == "f32" else MFMA_PEAK_TFLOPS
+def mfma_peak(dtype, launch):
+    """Of the instructions that the launch (rl_last_launch) runs on: fp32 tiles of 128 columns take six bf16 products for one."""
+    if dtype != "f32":
+        return MFMA_PEAK_TFLOPS
+    return MFMA_PEAK_TFLOPS / 6 if tuple(launch[:2]) == ("f32", 128) else MFMA_PEAK_TFLOPS_F32
+
+
 ROTATE_BYTES = 512 << 20
 MIN_REGION_MS = 50.0             # a timed region is the K-step graph replayed until it lasts at least this long
 # HBM-side bytes per launch from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (two runs), scaled by what the same
@@ -237,7 +242,7 @@ def run_workload(rl, torch, name, steps, warmup, variant, use_graph=True, check=
     if mem_bound:
         res["roofline_frac"] = res["TBps"] * 1e3 / HBM_PEAK_GBS
     else:
-        res["roofline_frac"] = res["TFLOPs"] / mfma_peak(w.dtype)
+        res["roofline_frac"] = res["TFLOPs"] / mfma_peak(w.dtype, launch)
     return res, w
 
 
@@ -524,12 +529,12 @@ def main():
 
 def roofline_of(name, res, w, auto):
     """The roofline object of one workload's dominant kernel."""
+    launch = [res["launch"][k] for k in ("variant", "columns", "slabs", "workgroups")]
     if w.M <= 64:
         roof = {"bound": "hbm", "achieved": res["TBps"] * 1e3, "peak": HBM_PEAK_GBS, "unit": "GB/s"}
     else:
-        roof = {"bound": "mfma", "achieved": res["TFLOPs"], "peak": mfma_peak(w.dtype), "unit": "TFLOP/s"}
+        roof = {"bound": "mfma", "achieved": res["TFLOPs"], "peak": mfma_peak(w.dtype, launch), "unit": "TFLOP/s"}
     roof["frac"] = roof["achieved"] / roof["peak"]
-    launch = [res["launch"][k] for k in ("variant", "columns", "slabs", "workgroups")]
     rec = MEASURED_TRAFFIC.get(name)
     if auto and rec is not None and list(rec[1]) == launch:
         roof["traffic"] = rec[0]
@@ -547,7 +552,7 @@ def roofline_of(name, res, w, auto):
         # one fused kernel is timed beside it and priced the same way
         one = res["us_per_step_one_fused_kernel"]
         roof["form"] = "two kernels: X-hat and 1/rms written once by a first kernel, then the tile product scaled per row"
-        roof["one_fused_kernel"] = {"us_per_launch": one, "achieved": w.flops / one / 1e6, "frac": w.flops / one / 1e6 / mfma_peak(w.dtype)}
+        roof["one_fused_kernel"] = {"us_per_launch": one, "achieved": w.flops / one / 1e6, "frac": w.flops / one / 1e6 / MFMA_PEAK_TFLOPS}
     return roof
 
 
