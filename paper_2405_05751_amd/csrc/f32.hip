@@ -220,7 +220,7 @@ __global__ __launch_bounds__(256) void f32_kernel(F32Args a)
 // are nearly exact: rows with one entry 6.6e-8 against 6.2e-8; |N(0, 1)| 8.1e-8 against 7.8e-8 (128 x 128) at K = 192, 7.2e-8 against 7.5e-8
 // (64 rows) at 4096; all entries +-(1 + 2^-8 - 2^-17) times powers of two 1.3e-7 against 0.9e-7.
 // 2048 x 4096 x 4096: 590-612 us on fp32 instructions, 364-378 here, 182-189 TFLOP/s (fp32 peak: 157). Parts left out: loads 55 us,
-// splitting 49, second accumulator 20.  Counters: the matrix pipes are busy 49 % of the cycles at 2.0 GHz, and the vector instructions, 89 M
+// splitting 49, second accumulator 20.  Counters: the matrix pipes are busy 52 % of the cycles at 2.0 GHz, and the vector instructions, 84 M
 // of them, would take 44 % by themselves; where they stand between the matrix instructions is worth 1 %.
 constexpr int kFtN = 128, kFtK = 32, kFtMinK = 64, kFtMaxK = 16000, kFtMaxK2 = 4096;        // (g in LDS; of 128 rows)
 constexpr unsigned kFtOut = 0x80000000u;     // beyond every resource (sizes below 2^31), with any tile offset added
@@ -625,8 +625,8 @@ static F32Plan f32_plan(const Problem& p)
 // Which problems, and the tile's rows / 64 (0: the kernel above).  By the rounds of workgroups that each needs, K in us: tiles run
 // one to a compute unit and slow down as the chip fills (power), the 64 x 64 tiles above run two, or one in a last round
 // that has no more, and a split over K fills the chip better than larger tiles would.  Fitted to 13 shapes, 5 to 8 % rms.  us above, on
-// 64 and on 128 rows: 512 x 4096 x 4096 171, 119, 157; 1000 x 2000 x 3000 135, 116, 84; 1500 x 256 x 1000 20.4, 12.6, 17.7;
-// 300 x 1000 x 8192 75, 63, 46; 256 x 4096 x 4096 87, 108, 156; 1024^3 26, 30, 44.  Above K = 4096, where 128 rows would be further from fp64:
+// 64 and on 128 rows: 512 x 4096 x 4096 168, 119, 151; 1000 x 2000 x 3000 133, 114, 85; 1500 x 256 x 1000 19.8, 12.8, 18.0;
+// 300 x 1000 x 8192 73, 61, 46; 256 x 4096 x 4096 85, 102, 150; 1024^3 26, 29, 45; 64 x 4096 x 28672 171, 138, 185.  Above K = 4096, where 128 rows would be further from fp64:
 // 2048 x 8192 x 2048 658, 451 (388); 700 x 8192 x 3072 490, 419 (317).
 // One block of rows: the kernel above then works on 16 MB of them, a tile always on 64, and its time no longer follows the
 // estimate, which is that of 64 rows.  Measured on wide N (16k to 64k, K 64 to 12000), tiles over the kernel above: M 1 to 16 1.3 to 2.5
