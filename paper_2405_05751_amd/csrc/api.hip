@@ -347,7 +347,8 @@ rl_status run(Problem& p, void* stream, const Workspace* fixed = nullptr, const 
     auto then = [&](rl_variant v) {
         const bool spares = spares_workspace(v, p);
         order[n_order++] = Step{v, 0, 0, spares, false};
-        if (spares) order[n_order++] = Step{v, 0, 0, false, true};
+        // (in place of row blocks that are split, and so would be refused: mid_plan has the form, if any)
+        if (spares || (v == RL_MFMA_TILE_PRE && skinny_row_blocks(p))) order[n_order++] = Step{v, 0, 0, false, true};
     };
     if (forced != RL_AUTO) {
         order[n_order++] = Step{with_columns(forced, p), p.n_tile, p.k_split, false, false};

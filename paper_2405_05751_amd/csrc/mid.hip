@@ -340,9 +340,12 @@ static hipError_t mid_t(const MidArgs& a, bool gated, int S, hipStream_t s)
     return gated ? mid_go<T, BN, true, false, false>(a, S, s) : mid_go<T, BN, false, false, false>(a, S, s);
 }
 
+// where that is not the slower form
+static bool mid_forms(const Problem& p, int cols) { return p.dt == F16 || (cols == 64 && p.N <= 3 * int64_t(p.M)); }
+
 bool mid_fused(const Problem& p, int cols, int S)
 {
-    return p.fused && S == 1 && (p.dt == F16 || (cols == 64 && p.N <= 3 * int64_t(p.M)) || p.no_ws) && mid_lds(cols) + mid_gain_lds(p.K) <= kMidLdsMost / (cols == 64 ? 2 : 1);
+    return p.fused && S == 1 && (mid_forms(p, cols) || p.no_ws) && mid_lds(cols) + mid_gain_lds(p.K) <= kMidLdsMost / (cols == 64 ? 2 : 1);
 }
 
 // The tile width and the split over K for the product of this problem; false: another form is the better choice, or the
@@ -363,6 +366,7 @@ bool mid_fused(const Problem& p, int cols, int S)
 // 887 x 3696 x 2*904 40 against 31; with one row of tiles nobody shares W either), and so is, against 256 x 256 tiles, a chip full of 128
 // columns (3414 x 7632 x 2*2584 447 against 366).  Of 1264 shapes whose choice a tenth anywhere or here changes, this rule takes the fastest form measured within
 // 0.3 % (geometric mean), 0.83 of the time with no tenth; 19 are 3 to 16 % slower than without, 149 were (up to 48 %) with it everywhere.
+// Against row blocks alone it holds everywhere (1000 x 3200 x 2*672 fp16 24 against 35 us).
 // (220 shapes not used for the rule: 0.80; 4 of 106 against row blocks and 2 of 114 against the rest are 3 to 11 % slower.)
 bool mid_plan(const Problem& p, int* cols, int* S, int* k_slab)
 {
@@ -389,27 +393,36 @@ bool mid_plan(const Problem& p, int* cols, int* S, int* k_slab)
     const double other = skinny ? skinny_us(p) : tile_pre_us(p);
     if (skinny && other < 16.) return false;
     const bool split = skinny && skinny_workspace_bytes(p) != 0;
-    double best = !skinny ? 0.85 * other : p.no_ws ? std::min(0.87 * other, tile_pre_us(p)) : 0.96 * other;
+    // no workspace; or none where row blocks need one: then a form without is taken only if it was ahead of them and the splits by a tenth anywhere
+    const bool none = p.no_ws && !split, last = p.no_ws && split;
+    double best = !skinny ? 0.85 * other : none ? std::min(0.87 * other, tile_pre_us(p)) : 0.96 * other;
+    // row blocks are all there is to beat: the tenth wherever X-hat is formed
+    double alone = best;
+    int alone_cols = 0;
     *cols = 0;
     for (int c = 64; c <= 128; c += 64)
         for (int s = 1; s <= 8; ++s) {
             const int ks = slab(s), real = (p.K + ks - 1) / ks;
-            if (real != s || (p.no_ws && !mid_fused(p, c, s)) || (s > 1 && (ks < 192 || double(s) * mn * 4. > 40.)) || !fits(c, s)) continue;
+            const bool fused = mid_fused(p, c, s) && (none || mid_forms(p, c));
+            if (real != s || (none && !fused) || (s > 1 && (ks < 192 || double(s) * mn * 4. > 40.)) || !fits(c, s)) continue;
             // in place of row blocks only with what the entry point that allocates nothing has for it: both then run the
             // same launches and give the same bits (no shape of 12 000 needs more than 43 MiB); where the row blocks are not
             // split, and so need no workspace, with what a stream's region holds (none needs more than 23 MiB)
-            if (skinny && !mid_fused(p, c, s) && mid_workspace_bytes(p, s) + kHeadBytes > (split ? kRowScratchBytes : kRegionBytes)) continue;
+            if (skinny && !fused && mid_workspace_bytes(p, s) + kHeadBytes > (split ? kRowScratchBytes : kRegionBytes)) continue;
             const int64_t tiles_n = p.gated && s == 1 ? (p.N / 2 + c / 2 - 1) / (c / 2) : (p.N + c - 1) / c;
             const double rounds = double((tiles_m * tiles_n * s + 255) / 256), kt = double((ks + kMidK - 1) / kMidK);
             const double run = c == 128 ? rounds * (4.1 + 0.62 * kt)
                                         : std::ceil(rounds / 2.) * 3.1 + (rounds > 1. ? 0.445 * rounds : 0.48) * kt;
-            const bool tenth = mid_fused(p, c, s) && !p.no_ws &&
-                (c == 128 ? tiles_m * tiles_n <= 496 || (tiles_m >= 16 && p.K <= 2500)
-                          : rounds > 1. || tiles_m >= 16 || p.K <= (tiles_m > 1 ? 2500 : 1280));
-            const double us = (3.6 + 0.135 * mk + std::max(run, w_us) + (s > 1 ? 0.9 + 2.2 * s * mn : 0.)) * (tenth ? 0.9 : 1.);
+            const bool forms = fused && !none;
+            const bool tenth = forms && (last || (c == 128 ? tiles_m * tiles_n <= 496 || (tiles_m >= 16 && p.K <= 2500)
+                                                           : rounds > 1. || tiles_m >= 16 || p.K <= (tiles_m > 1 ? 2500 : 1280)));
+            const double full = 3.6 + 0.135 * mk + std::max(run, w_us) + (s > 1 ? 0.9 + 2.2 * s * mn : 0.), us = full * (tenth ? 0.9 : 1.);
             if (skinny && s > 1 && other < 19. && us >= 0.87 * other) continue;          // three launches take the host 18 us
             if (us < best) { best = us; *cols = c; *S = s; *k_slab = ks; }
+            if (forms && 0.9 * full < alone) { alone = 0.9 * full; alone_cols = c; }
         }
+    if (*cols == 0 && skinny && alone_cols != 0) { *cols = alone_cols; *S = 1; *k_slab = slab(1); }
+    if (last && *cols != 0 && !(mid_fused(p, *cols, *S) && mid_forms(p, *cols))) *cols = 0;
     return *cols != 0;
 }
 

@@ -251,3 +251,17 @@ lib.rmsnorm_gated_mlp.argtypes = [V, V, V, F, V, L, L, L, I, V]
 print(linear({M}, {K}, {N}, {dt}, 0, {fn!r}), [n for n in names() if "scratch_clear" not in n])
 """)
     assert out == [f"0 {kernels}"]
+
+
+@pytest.mark.parametrize("fn,M,K,N,dt", [("rmsnorm_linear", 66, 1344, 7776, "F16"), ("rmsnorm_linear", 128, 1712, 6144, "F16"),
+                                        ("rmsnorm_gated_mlp", 93, 1464, 3232, "F16")])
+def test_tiles_in_place_of_split_row_blocks_without_a_workspace(fn, M, K, N, dt):
+    """A split is the faster form here; without a workspace (under capture before any other call) the one that needs none runs."""
+    out = routes.run(f"""
+lib.rmsnorm_gated_mlp.argtypes = [V, V, V, F, V, L, L, L, I, V]
+rec.rec_capture(V(7), 1)
+print(linear({M}, {K}, {N}, {dt}, 7, {fn!r}), rec.rec_mallocs(), names())
+rec.rec_capture(V(7), 0)
+print(linear({M}, {K}, {N}, {dt}, 7, {fn!r}), [n for n in names() if "clear" not in n])
+""")
+    assert out[0] == "0 0 ['mid_kernel']" and out[1] == f"0 {SPLIT}"
