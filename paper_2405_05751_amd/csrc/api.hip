@@ -239,6 +239,7 @@ rl_variant choose_auto(const Problem& p)
     // (measured at N <= 8192; at N = 11008, 13824, 14336 the matrix-core kernel is 10-17 % ahead).  Two
     // to four rows: the GEMV kernel's shorter chain of dependent steps wins while W is small (2 x 2048 x
     // 2048: 6.5 against 8.8 us, 4 x 2048 x 2048: 7.6 against 8.8 us; 2 x 3072 x 3072: 12.9 against 11.3 us).
+    if (small_wins_over_gemv(p)) return RL_MFMA_SKINNY;
     if (p.M == 1 && p.N < 10240) return RL_GEMV_SPLITK;
     if (p.M <= 4 && double(p.K) * p.N <= 6.0e6) return RL_GEMV_SPLITK;
     if (p.M <= 64) return RL_MFMA_SKINNY;
@@ -620,7 +621,7 @@ static rl_status autotune_core(const void* X, const void* g, const void* const* 
             }
         if (M <= 1024)
             for (int nt : {0, 64})
-                for (int ks = 1; ks <= 16; ++ks) cands.push_back({RL_MFMA_SKINNY, nt, ks});
+                for (int ks = nt ? 1 : 0; ks <= 16; ++ks) cands.push_back({RL_MFMA_SKINNY, nt, ks});
         if (M > 16)
             for (int shape : {256, 512})
                 for (int nw : {4, 8}) cands.push_back({RL_MFMA_TILE, shape, nw});

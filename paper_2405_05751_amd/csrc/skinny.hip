@@ -375,7 +375,7 @@ __global__ __launch_bounds__(64 * skinny_waves(MB)) void skinny_kernel(
 
 // ------------------------------------------------------------------------------------------- host
 constexpr int kSkinnyMaxM = 1024;
-struct SkinnyPlan { int MB, RB, S, k_slab, n_tiles, n_tile; size_t lds; bool ok; const char* why; };
+struct SkinnyPlan { int MB, RB, S, k_slab, n_tiles, n_tile, small; size_t lds; bool ok; const char* why; };     // small: launch_small's NC, or 0
 
 static SkinnyPlan skinny_plan(const Problem& p)
 {
@@ -399,6 +399,7 @@ static SkinnyPlan skinny_plan(const Problem& p)
     const int runs = (p.K + 63) / 64;        // 64-row runs of W; a slab is a whole number of them
     const int nw = skinny_waves(pl.MB);
     int n_tile = p.n_tile, S = p.k_split;
+    if (small_wins_over_gemv(p)) pl.small = small_columns(p, 0.);
     if (n_tile == 0 || S <= 0) {
         // Pick the slab count with a small cost model, fitted to a sweep of every slab count over 65
         // shapes (M 2 to 64; W from 1024 x 4096 to 28672 x 8192): the pick is within 1.5 % of the best
@@ -441,6 +442,9 @@ static SkinnyPlan skinny_plan(const Problem& p)
         }
         n_tile = best_nt;
         S = best_s;
+        if (pl.RB == 1 && !pl.small)
+            pl.small = small_columns(p, 2.89 + 0.62 * best + 1.29 * pl.MB + (S > 1 ? 1.17 : 0.) + (p.gated ? 1.70 : 0.) +
+                                            double(p.K) * p.N * 2.0 / 27.0e6);
         // a launch that would fill at most half the chip runs 64-column tiles instead, twice the
         // workgroups: 4 to 10 % faster on 13 small shapes (8 x 512 x 512 to 16 x 4096 x 1024), while
         // a W that fills the chip streams faster in 256-byte row segments
@@ -493,7 +497,7 @@ double skinny_us(const Problem& p)
 size_t skinny_workspace_bytes(const Problem& p)
 {
     SkinnyPlan pl = skinny_plan(p);
-    if (!pl.ok || pl.S <= 1) return 0;
+    if (!pl.ok || pl.S <= 1 || pl.small) return 0;
     return size_t(pl.RB) * pl.S * std::min(p.M, 64) * p.N * 4;    // [row block][slab][rows][N]
 }
 
@@ -535,6 +539,7 @@ hipError_t launch_skinny(const Problem& p, hipStream_t s, const char** why)
 {
     SkinnyPlan pl = skinny_plan(p);
     if (!pl.ok) { if (why) *why = pl.why; return hipErrorInvalidValue; }
+    if (pl.small) return launch_small(p, pl.small, s);
     if (pl.S > 1 && (!p.ws_partial || !p.ws_sumsq || !p.ws_counter)) {
         if (why) *why = "split-K needs the workspace";
         return hipErrorInvalidValue;
