@@ -146,9 +146,17 @@ def _check(status: int) -> None:
         raise RmsnlError(status, lib().rl_last_error().decode())
 
 
+# torch.cuda.current_stream() makes a Stream object, 2.5 us of the 9.2 that an 8 x 512 x 512 call took the host; the handle
+# alone is 0.13 us (6.7 then).  (Both names are torch's own and private: without them the public way.)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream) -> int:
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        if _raw_stream is None or _device is None or not torch.cuda.is_initialized():
+            return torch.cuda.current_stream().cuda_stream
+        return _raw_stream(_device())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
