@@ -243,7 +243,7 @@ rl_variant choose_auto(const Problem& p)
     if (p.M == 1 && p.N < 10240) return RL_GEMV_SPLITK;
     if (p.M <= 4 && double(p.K) * p.N <= 6.0e6) return RL_GEMV_SPLITK;
     if (p.M <= 64) return RL_MFMA_SKINNY;
-    if (skinny_row_blocks(p)) return RL_MFMA_SKINNY;
+    if (small_blocks(p) || skinny_row_blocks(p)) return RL_MFMA_SKINNY;
     return RL_MFMA_TILE;
 }
 
@@ -262,7 +262,7 @@ bool prefers_two_kernels(const Problem& p)
 bool prefers_mid_tiles(const Problem& p)
 {
     int cols, S, k_slab;
-    return p.M > 64 && mid_plan(p, &cols, &S, &k_slab);
+    return p.M > 64 && !small_blocks(p) && mid_plan(p, &cols, &S, &k_slab);
 }
 
 // Is the automatic choice of v a form that the call could do without a workspace (get_region)?  The odd-size kernel runs unsplit,

@@ -57,6 +57,7 @@ hipError_t launch_gemv(const Problem& p, hipStream_t s, const char** why);
 hipError_t launch_skinny(const Problem& p, hipStream_t s, const char** why);
 // the skinny variant's form for a small W (small.hip): columns per workgroup / 16, 0 = the one it is measured against is better
 int small_columns(const Problem& p, double other_us);
+int small_blocks(const Problem& p);       // (above 64 rows)
 bool small_wins_over_gemv(const Problem& p);
 hipError_t launch_small(const Problem& p, int NC, hipStream_t s);
 hipError_t launch_tile(const Problem& p, hipStream_t s, const char** why);

@@ -442,6 +442,7 @@ static SkinnyPlan skinny_plan(const Problem& p)
         }
         n_tile = best_nt;
         S = best_s;
+        if (pl.RB > 1) pl.small = small_blocks(p);
         if (pl.RB == 1 && !pl.small)
             pl.small = small_columns(p, 2.89 + 0.62 * best + 1.29 * pl.MB + (S > 1 ? 1.17 : 0.) + (p.gated ? 1.70 : 0.) +
                                             double(p.K) * p.N * 2.0 / 27.0e6);

@@ -1,4 +1,4 @@
-// Fused RMSNorm + MatMul for M <= 64 where W is so small that a launch is a chain of latencies and not a stream.
+// Fused RMSNorm + MatMul where M is at most a few hundred and W is so small that a launch is a chain of latencies and not a stream.
 //
 // What such a launch spent its time on in the skinny kernel (8 x 512 x 512 in fp16, 5.4 us in a graph, its stages): 1.7 us to issue a
 // ring of loads that is deeper than the slab is long (a load takes its place in the address unit whether or not there is a row for it),
@@ -48,13 +48,14 @@ struct SmallCold {                               // what the first loads do not 
     u16* Y;
     float eps, inv_K;
     int H, G;
+    int RB;
     unsigned long long* trace; int trace_groups;
 };
 
-// Tiles of 16 MB rows (all of M) x 16 NC columns; a wave takes every NW-th step of 32 k.
+// Tiles of 16 MB rows (all of M, or of a row block of 64) x 16 NC columns; a wave takes every NW-th step of 32 k.
 template <typename T, int MB, int NC, bool FUSED, bool GATED>
 __global__ __launch_bounds__(64 * small_waves(MB)) void small_kernel(
-    const u16* W, const u16* X, const u16* g, int M, int K, int N, int n_tiles, SmallCold a)
+    const u16* W, const u16* X, const u16* g, int M, int K, int N, SmallCold a)
 {
     constexpr int NW = small_waves(MB), MT = 16 * MB, TN = 16 * NC, CH = 2 * NC, HALF = TN / 2;
     typedef Arith<T> Ar;
@@ -65,7 +66,14 @@ __global__ __launch_bounds__(64 * small_waves(MB)) void small_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i = lane & 15, q = lane >> 4;
     trace_stamp(a.trace, a.trace_groups, 0);
-    const int tile = xcd_run(blockIdx.x, n_tiles);
+    // row blocks of 64 rows that take the same columns of W side by side on an XCD
+    const int b = xcd_run(blockIdx.x, gridDim.x);
+    const int tile = MB == 4 ? b / a.RB : b, rb = MB == 4 ? b - tile * a.RB : 0;
+    if (MB == 4) {
+        M = min(M - 64 * rb, 64);
+        X += size_t(rb) * 64 * K;
+        a.Y += size_t(rb) * 64 * (GATED ? a.H : N);
+    }
     const int n0 = GATED ? tile * HALF : tile * TN;              // gated: first output
 
     // direct loads of W: lane l of a load fills 16 bytes at byte 16 l of a KiB, which is 32 / NC rows of the tile
@@ -189,10 +197,10 @@ static hipError_t small_go(const Problem& p, int n_tiles, hipStream_t s)
     hipError_t e = raise_lds_once(once, {(const void*)small_kernel<T, MB, NC, true, false>, (const void*)small_kernel<T, MB, NC, false, false>,
                                          (const void*)small_kernel<T, MB, NC, true, true>}, int(small_lds(MB, NC)));
     if (e != hipSuccess) return e;
-    const SmallCold c{(u16*)p.Y, p.eps, 1.0f / float(p.K), p.gated ? p.N / 2 : 0, p.gate_group, p.trace, p.trace_groups};
+    const SmallCold c{(u16*)p.Y, p.eps, 1.0f / float(p.K), p.gated ? p.N / 2 : 0, p.gate_group, (p.M + 63) / 64, p.trace, p.trace_groups};
 #define RL_SMALL_GO(F, G) \
-    small_kernel<T, MB, NC, F, G><<<n_tiles, 64 * small_waves(MB), small_lds(MB, NC), s>>>( \
-        (const u16*)p.W, (const u16*)p.X, (const u16*)p.g, p.M, p.K, p.N, n_tiles, c)
+    small_kernel<T, MB, NC, F, G><<<n_tiles * c.RB, 64 * small_waves(MB), small_lds(MB, NC), s>>>( \
+        (const u16*)p.W, (const u16*)p.X, (const u16*)p.g, p.M, p.K, p.N, c)
     if (p.gated)      RL_SMALL_GO(true, true);
     else if (p.fused) RL_SMALL_GO(true, false);
     else              RL_SMALL_GO(false, false);
@@ -209,7 +217,7 @@ static hipError_t small_cols(const Problem& p, int NC, int n_tiles, hipStream_t 
 template <typename T>
 static hipError_t small_rows(const Problem& p, int NC, int n_tiles, hipStream_t s)
 {
-    switch ((p.M + 15) / 16) {
+    switch (p.M > 64 ? 4 : (p.M + 15) / 16) {
     case 1:  return small_cols<T, 1>(p, NC, n_tiles, s);
     case 2:  return small_cols<T, 2>(p, NC, n_tiles, s);
     case 3:  return small_cols<T, 3>(p, NC, n_tiles, s);
@@ -238,6 +246,28 @@ int small_columns(const Problem& p, double other_us)
     return other_us == 0. || best < 0.88 * other_us ? cols : 0;
 }
 
+// The same above 64 rows, in row blocks of 64, against what the skinny kernel's row blocks and 128-row tiles take (a fit of its own, 11 % rms
+// on 120 shapes, M 65 to 1024): 10 us and more however small the problem is, 5 of them in a graph here.  While the narrow tiles are
+// about one round of workgroups they take 0.34 to 0.7 of that (141 x 408 x 272 fp16 11.7 -> 4.2 us, 127 x 752 x 552 14.0 -> 5.8,
+// 278 x 824 x 1720 14.8 -> 8.3), several rounds up to twice as much.  At 0.75 of the other estimate 56 of the 120 shapes run here,
+// none slower, at 0.71 of the time over all 120 (the faster form each time: 0.66); at 0.8 60, one of them 4 % slower, at 0.9 64, three up to 13 %.
+// M <= 512, K <= 1536, N <= 12288: beyond, where the other estimate was less sure, no shape was worth it.
+int small_blocks(const Problem& p)
+{
+    if (p.dt == F32 || p.M <= 64 || p.M > 512 || p.n_tile != 0 || p.k_split != 0 || p.K > 1536 || p.N > 12288) return 0;
+    const double w_us = double(p.K) * p.N * 2.0 / 6.3e6, k = 1e-3 * p.K;
+    const double other = 9.33 + 3.58 * k + 0.44 * w_us + 1e-6 * p.M * (0.66 * p.N - 0.79 * p.K) + (p.gated ? 0.5 : 0.);
+    double best = 0.75 * other;
+    int cols = 0;
+    for (int NC = 1; NC <= 4; NC *= 2) {
+        const double wgs = double((p.M + 63) / 64) * ((p.N + 16 * NC - 1) / (16 * NC)), rounds = double((int64_t(wgs) + 255) / 256);
+        const double us = 2.72 + rounds * (0.53 + k * (0.60 * NC + 2.41 + (p.gated && NC == 1 ? 0.47 : 0.))) + 1.37 * w_us +
+                          wgs / 256. * k * (0.90 * NC - 1.56) + (p.gated ? 0.87 : 0.);
+        if (us < best) { best = us; cols = NC; }
+    }
+    return cols;
+}
+
 // Up to four rows where choose_auto would take the GEMV kernel: the narrow tiles are ahead of it on all of 23 shapes with K <= 1024 and
 // K N <= 2e6 (0.5 to 0.91 of the time), level at K = 1500 and behind at 1900, and beyond 2e6 the GEMV kernel streams.
 bool small_wins_over_gemv(const Problem& p)
@@ -248,7 +278,7 @@ bool small_wins_over_gemv(const Problem& p)
 hipError_t launch_small(const Problem& p, int NC, hipStream_t s)
 {
     const int n_tiles = p.gated ? (p.N / 2 + 8 * NC - 1) / (8 * NC) : (p.N + 16 * NC - 1) / (16 * NC);
-    if (p.plan) { p.plan[0] = 16 * NC; p.plan[1] = 1; p.plan[2] = n_tiles; }
+    if (p.plan) { p.plan[0] = 16 * NC; p.plan[1] = 1; p.plan[2] = n_tiles * ((p.M + 63) / 64); }
     return p.dt == F16 ? small_rows<Fp16>(p, NC, n_tiles, s) : small_rows<Bf16>(p, NC, n_tiles, s);
 }
 

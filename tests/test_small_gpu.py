@@ -51,8 +51,22 @@ def test_edges(rl, M, K, N, columns, dtype):
     assert torch.equal(Y.view(torch.int16), Y2.view(torch.int16))
 
 
+@pytest.mark.parametrize("M,K,N,dtype", [(65, 8, 8, "bf16"), (65, 264, 136, "f16"), (127, 520, 1016, "bf16"), (128, 512, 512, "f16"), (129, 40, 24, "bf16"),
+                                         (200, 1000, 1016, "bf16"), (320, 256, 4104, "f16"), (512, 264, 520, "bf16"), (66, 1536, 2048, "f16")])
+def test_row_blocks(rl, M, K, N, dtype):
+    import torch
+    w = workloads.make(M, K, N, dtype, 1e-5, 9400 + M + N)
+    X, g, W = upload(w)
+    Y = torch.full((M, N), float("nan"), dtype=X.dtype, device="cuda")
+    rl.rmsnorm_linear(X, g, W, w.eps, Y)
+    torch.cuda.synchronize()
+    assert small(rl) and rl.rl_last_launch()[3] == -(-M // 64) * -(-N // rl.rl_last_launch()[1])
+    compare(to_host_f64(Y, dtype), oracle.rmsnorm_linear(w.X, w.g, w.W, dtype, w.eps), dtype, f"{M}x{K}x{N}")
+    assert rl.rl_workspace_bytes(M, K, N, X.dtype) == 0
+
+
 @pytest.mark.parametrize("interleaved", [False, True])
-@pytest.mark.parametrize("M,K,H,dtype", [(1, 40, 64, "bf16"), (4, 520, 128, "f16"), (16, 776, 1024, "bf16"), (32, 264, 2112, "f16"), (33, 512, 576, "bf16"),
+@pytest.mark.parametrize("M,K,H,dtype", [(100, 520, 448, "f16"), (300, 264, 1024, "bf16"), (1, 40, 64, "bf16"), (4, 520, 128, "f16"), (16, 776, 1024, "bf16"), (32, 264, 2112, "f16"), (33, 512, 576, "bf16"),
                                          (64, 272, 6400, "f16")])
 def test_gated(rl, M, K, H, dtype, interleaved):
     import torch
