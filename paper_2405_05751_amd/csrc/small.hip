@@ -229,27 +229,33 @@ static hipError_t small_rows(const Problem& p, int NC, int n_tiles, hipStream_t 
 // workgroups with their K steps, W from memory, and narrow row segments of two halves.  At 0.88 of the other form's time (skinny_plan's
 // estimate with a constant of the same fit, 8 %) 4 of 215 shapes were slower than with it, by 3 to 15 %, at 0.95 8, and it gives
 // 0.71 of the time over all of them where the faster form each time gives 0.69.
+// Rows of W that are a multiple of 512 bytes suit wide tiles (their estimate is 6 % high there) and not narrow ones, the more the longer K is
+// (K = 512 1.0, 1024 1.1, 1536 1.25 of the estimate, whichever XCD takes which line): of 237 such shapes, K 256 to 2048, N 512 to 16384,
+// 22 were 3 to 34 % slower without that in the rule, one by 3 % with it, at 0.73 of the time over all of them (the faster form each time 0.71).
+// Two halves of a tile in two places are the slower the longer K is, too (14 x 1832 x 2*1640 11.0 -> 12.3 us without that term).
 // Columns per workgroup / 16 (1, 2 or 4) for this problem, or 0 where another form is the better choice.  other_us: the estimate for
 // that one, in the unit of this one's, or 0 for none to beat.
 int small_columns(const Problem& p, double other_us)
 {
     if (p.dt == F32 || p.M > 64 || p.n_tile != 0 || p.k_split != 0 || p.K > kSmallMaxK || p.N > kSmallMaxN) return 0;
     const int MB = (p.M + 15) / 16;
+    const bool whole = p.N % 256 == 0;
     double best = 0.;
     int cols = 0;
     for (int NC = 1; NC <= 4; NC *= 2) {
         const double rounds = double(((p.N + 16 * NC - 1) / (16 * NC) + 255) / 256), k = 1e-3 * rounds * p.K;
-        const double us = 1.98 + 0.10 * MB + 0.43 * rounds + k * (0.62 * NC + 0.83 * MB + (p.gated && NC == 1 ? 0.72 : 0.)) +
+        double us = 1.98 + 0.10 * MB + 0.43 * rounds + k * (0.62 * NC + 0.83 * MB + (p.gated && NC == 1 ? 0.72 : 0.)) +
                           double(p.K) * p.N * 2.0 / 6.3e6 + (p.gated ? 0.90 : 0.);
+        us *= 1. + 1e-3 * p.K * ((whole ? 0.15 : 0.) + (p.gated ? 0.08 : 0.));
         if (cols == 0 || us < best) { best = us; cols = NC; }
     }
-    return other_us == 0. || best < 0.88 * other_us ? cols : 0;
+    return other_us == 0. || best < (whole ? 0.82 : 0.88) * other_us ? cols : 0;
 }
 
 // The same above 64 rows, in row blocks of 64, against what the skinny kernel's row blocks and 128-row tiles take (a fit of its own, 11 % rms
-// on 120 shapes, M 65 to 1024): 10 us and more however small the problem is, 5 of them in a graph here.  While the narrow tiles are
-// about one round of workgroups they take 0.34 to 0.7 of that (141 x 408 x 272 fp16 11.7 -> 4.2 us, 127 x 752 x 552 14.0 -> 5.8,
-// 278 x 824 x 1720 14.8 -> 8.3), several rounds up to twice as much.  At 0.75 of the other estimate 56 of the 120 shapes run here,
+// on 120 shapes, M 65 to 1024): 10 us and more however small the problem is, 4 to 9 here.  While the narrow tiles are
+// one round of workgroups they take 0.34 to 0.7 of that (141 x 408 x 272 fp16 11.7 -> 4.2 us, 127 x 752 x 552 14.0 -> 5.8,
+// 278 x 824 x 1720 14.8 -> 8.3), with more from 0.97 of it to twice as much.  At 0.75 of the other estimate 56 of the 120 shapes run here,
 // none slower, at 0.71 of the time over all 120 (the faster form each time: 0.66); at 0.8 60, one of them 4 % slower, at 0.9 64, three up to 13 %.
 // M <= 512, K <= 1536, N <= 12288: beyond, where the other estimate was less sure, no shape was worth it.
 int small_blocks(const Problem& p)
@@ -260,8 +266,9 @@ int small_blocks(const Problem& p)
     double best = 0.75 * other;
     int cols = 0;
     for (int NC = 1; NC <= 4; NC *= 2) {
-        const double wgs = double((p.M + 63) / 64) * ((p.N + 16 * NC - 1) / (16 * NC)), rounds = double((int64_t(wgs) + 255) / 256);
-        const double us = 2.72 + rounds * (0.53 + k * (0.60 * NC + 2.41 + (p.gated && NC == 1 ? 0.47 : 0.))) + 1.37 * w_us +
+        const double wgs = double((p.M + 63) / 64) * ((p.N + 16 * NC - 1) / (16 * NC));
+        if (wgs > 256.) continue;
+        const double us = 3.25 + k * (0.60 * NC + 2.41 + (p.gated && NC == 1 ? 0.47 : 0.)) + 1.37 * w_us +
                           wgs / 256. * k * (0.90 * NC - 1.56) + (p.gated ? 0.87 : 0.);
         if (us < best) { best = us; cols = NC; }
     }
