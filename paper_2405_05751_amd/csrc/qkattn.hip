@@ -135,7 +135,7 @@ __global__ __launch_bounds__(256) void qkattn_kernel(QkArgs a)
     const int off0 = (tl * D + EC * cl) * EB;
 
     uint4_t kx[R], vx[R];
-    // Every load is issued whether or not its iteration exists (one past the split reads zeros
+    // A load is issued whether or not its iteration exists (one past the split reads zeros
     // through the range check, at no memory traffic) and the issues are pinned in program order, so that the compiler
     // can count the loads younger than the one it waits for.
     auto issue = [&](int i, int r) {
@@ -220,14 +220,20 @@ __global__ __launch_bounds__(256) void qkattn_kernel(QkArgs a)
     };
 
     static_assert(R % 2 == 0, "iterations are taken in pairs");
-    for (int i0 = 0; i0 < nIter; i0 += R) {
+    int i0 = 0;
+    for (; i0 + R < nIter; i0 += R) {
 #pragma unroll
         for (int r = 0; r < R; r += 2) {
-            if (i0 + r < nIter) consume(i0 + r, r);      // uniform; only the arithmetic is skipped
+            consume(i0 + r, r);
             issue(i0 + r + R, r);
             issue(i0 + r + R + 1, r + 1);
         }
     }
+    // The last ones ask for nothing more: a load past the split brings nothing, but takes its place among the unit's (3 x 40 x 1105 x 80
+    // fp16 14.2 -> 13.6 us, 1 x 16 x 8192 x 256 25.3 -> 24.4, 1 x 32 x 3001 x 96 11.7 -> 11.4).
+#pragma unroll
+    for (int r = 0; r < R; r += 2)
+        if (i0 + r < nIter) consume(i0 + r, r);      // uniform
 
     // ---- merge the key groups of the wave (lanes l, l ^ LPK, l ^ 2 LPK, ...)
 #pragma unroll
