@@ -140,7 +140,7 @@ __global__ __launch_bounds__(64 * skinny_waves(MB)) void skinny_kernel(
     const int klen = min(run1 * 64, a.K) - k0;
     // runs of this wave: wave w takes runs w, w + NW, ... of the slab (the waves of a workgroup may
     // differ by one; nothing in the K loop is shared between them)
-    const int nPairs = (run1 - run0 - wave + NW - 1) / NW;
+    const int nPairs = __builtin_amdgcn_readfirstlane((run1 - run0 - wave + NW - 1) / NW);
 
     const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint4_t*>(a.W + size_t(k0) * (a.N >> 3)), 0, klen * a.N * 2, kSkFlags);
@@ -295,11 +295,13 @@ __global__ __launch_bounds__(64 * skinny_waves(MB)) void skinny_kernel(
     };
 
     constexpr int PU = (D % 2 == 0) ? D / 2 : D;    // runs per trip: ring slots repeat every 2 PU steps
-    for (int t0 = 0; t0 < nPairs; t0 += PU) {
+    constexpr bool DRAIN = XLDS;
+    int t0 = 0;
+    for (; t0 + (DRAIN ? PU : 0) < nPairs; t0 += PU) {
 #pragma unroll
         for (int p = 0; p < PU; ++p) {
             const int t = t0 + p;
-            const bool there = t < nPairs;   // uniform over the workgroup; only the arithmetic is skipped
+            const bool there = DRAIN || t < nPairs;   // uniform over the wave; only the arithmetic is skipped
             const char* stg = stage + (XLDS ? (t & 1) * STG : 0);
             if (XLDS) {
                 // this run's X was asked for a run ago; the 16 loads of W issued since are younger
@@ -328,6 +330,67 @@ __global__ __launch_bounds__(64 * skinny_waves(MB)) void skinny_kernel(
                 asm volatile("" ::: "memory");
                 __builtin_amdgcn_sched_barrier(0);
             }
+        }
+    }
+    // The last runs (up to PU of them) ask for no step past the slab's end: such a load brings nothing, but takes its turn in the
+    // address unit, and a wave has 2 to 16 runs in all.  One piece of code for each count, so that the waits still know how many
+    // loads are younger than theirs; at 64 rows, where the copies would not fit the registers (54 spilled, 64 x 4096 x 4096 17.7 -> 21.0 us),
+    // one piece for all, with conditions, whose waits are for everything.  In graphs, us: 16 x 4096 x 6144 14.6 -> 14.2, 8 x 2048 x 4096
+    // 8.7 -> 8.2, 21 x 2496 x 2224 11.7 -> 10.7, 48 x 2464 x 6144 14.5 -> 13.6, 64 x 4096 x 2*14336 54.9 -> 53.8, 200 x 2048 x 2048 14.5 -> 12.8,
+    // 509 x 4096 x 4096 35.3 -> 34.0, 128 x 8192 x 8192 44.9 -> 44.2.
+    if constexpr (DRAIN) {
+        auto last_runs = [&](auto count) {
+            constexpr int n = decltype(count)::value;
+#pragma unroll
+            for (int p = 0; p < n; ++p) {
+                // loads of W issued since this run's X: 16 by the run before, fewer where that one is among the last itself
+                const int since = p == 0 ? 16 : 8 * std::max(0, std::min(2, 2 * n - D - 2 * (p - 1)));
+                const char* stg = stage + ((t0 + p) & 1) * STG;
+                if (since == 16) __builtin_amdgcn_s_waitcnt((16 & 15) | ((16 >> 4) << 14) | (7 << 4) | (15 << 8));
+                else if (since == 8) __builtin_amdgcn_s_waitcnt(8 | (7 << 4) | (15 << 8));
+                else __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8));
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_sched_barrier(0);
+                if (p + 1 < n) issue_x(t0 + p + 1);
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    consume((2 * p + h) % D, h, stg);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (2 * p + h + D < 2 * n) issue_w(2 * (t0 + p) + h + D, (2 * p + h) % D);
+                    asm volatile("" ::: "memory");
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        };
+        if constexpr (MB == 4) {
+#pragma unroll
+            for (int p = 0; p < PU; ++p) {
+                const int t = t0 + p;
+                if (t >= nPairs) break;
+                const char* stg = stage + (t & 1) * STG;
+                if (p == 0) __builtin_amdgcn_s_waitcnt((16 & 15) | ((16 >> 4) << 14) | (7 << 4) | (15 << 8));
+                else __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8));
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_sched_barrier(0);
+                if (t + 1 < nPairs) issue_x(t + 1);
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    consume((2 * p + h) % D, h, stg);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (2 * t + h + D < 2 * nPairs) issue_w(2 * t + h + D, (2 * p + h) % D);
+                    asm volatile("" ::: "memory");
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        } else {
+            const int left = nPairs - t0;    // uniform over the wave
+            if (left == 1) last_runs(std::integral_constant<int, 1>{});
+            if (left == 2) last_runs(std::integral_constant<int, 2>{});
+            if constexpr (PU > 2) if (left == 3) last_runs(std::integral_constant<int, 3>{});
         }
     }
     trace_stamp(a.trace, a.trace_groups, 2);
