@@ -18,7 +18,7 @@
 // the splits of the sequence (by the last of them to arrive, through the workspace) are merged at
 // the end.  A vector with fewer chunks than its group has lanes (D = 96: 12 of 16) leaves the last lanes without
 // one: they fetch the vector's last chunk again, a line that is on its way anyhow, and stay out of the sums.
-// Measured at 32 heads x 3001 positions x D = 96, fp16: 11.5 us (3.2 TB/s) against 1216 us in the
+// Measured at 32 heads x 3001 positions x D = 96, fp16: 10.2 us (3.6 TB/s) against 1216 us in the
 // plain kernel, which until then ran every D but 64, 128 and 256.  Any other D: that plain kernel.
 #include <algorithm>
 #include "common.hpp"
