@@ -56,8 +56,8 @@ typedef enum {
                              workgroups; up to 4 rows W goes through LDS by direct loads, above that through registers */
     RL_MFMA_SKINNY = 2,   /* 16-bit types, matrix cores, 64 rows per workgroup (M <= 1024: a row block per 64 rows in the same
                              launch), K split over the waves of a workgroup and into 1 to 16 slabs over workgroups; 128
-                             columns of W per workgroup, 64 when that leaves half the chip idle.  Where W is small (M <= 64, K <= 2560,
-                             by estimate) and no shape is asked for, 16, 32 or 64 columns and all of K in one workgroup, without
+                             columns of W per workgroup, 64 when that leaves half the chip idle.  Where W is small (M <= 64, K <= 2560, and
+                             in row blocks of 64 M <= 512, K <= 1536, by estimate) and no shape is asked for, 16, 32 or 64 columns and all of K in one workgroup, without
                              a workspace */
     RL_MFMA_TILE = 3,     /* 16-bit types, large M: 256x256 (or 128x512) output tiles on matrix cores, one fused kernel; K < 2^22,
                              N < 2^25; a W of 2 GiB or more is addressed row by row */

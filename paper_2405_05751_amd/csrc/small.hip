@@ -3,8 +3,8 @@
 // What such a launch spent its time on in the skinny kernel (8 x 512 x 512 in fp16, 5.4 us in a graph, its stages): 1.7 us to issue a
 // ring of loads that is deeper than the slab is long (a load takes its place in the address unit whether or not there is a row for it),
 // 1.8 us for two runs per wave one after the other, 0.4 us to meet, and where K is split over workgroups 3 us or more for the exchange.
-// Here all of K lies in one workgroup, so there is no exchange and no workspace; 16 waves (8 above 32 rows, where their sums would not
-// fit) take a step of 32 k each, so that the chain is one load, one conversion, 2 MB NC matrix instructions and one sum over the
+// Here all of K lies in one workgroup, so there is no exchange and no workspace; 16 waves (8 above 32 rows, where 16 are 0 to 14 %
+// slower) take a step of 32 k each, so that the chain is one load, one conversion, 2 MB NC matrix instructions and one sum over the
 // waves; tiles of 16, 32 or 64 columns make up for the missing split with more workgroups.  W goes straight into the wave's corner of
 // LDS and comes back by the transposing read: one load per 32 x 16 block in place of eight and their permutes.  Further trips are not
 // overlapped: the other waves' loads fill what a unit keeps in flight (two or four steps per trip, and a wave's steps next to each
