@@ -276,10 +276,12 @@ int small_blocks(const Problem& p)
 }
 
 // Up to four rows where choose_auto would take the GEMV kernel: the narrow tiles are ahead of it on all of 23 shapes with K <= 1024 and
-// K N <= 2e6 (0.5 to 0.91 of the time), level at K = 1500 and behind at 1900, and beyond 2e6 the GEMV kernel streams.
+// K N <= 2e6 (0.5 to 0.91 of the time), level at K = 1500 and behind at 1900, and beyond 2e6 the GEMV kernel streams.  Not the fused
+// block in fp16: the GEMV kernel keeps X (.) g in fp32, whose products leave the range of the two fp16 operands they would have to
+// be here (beyond 65504 an infinity and its opposite; X near 1e-5 1.6e-3 from fp64 in place of 2.1e-4).
 bool small_wins_over_gemv(const Problem& p)
 {
-    return p.M <= 4 && p.K <= 1024 && p.N <= kSmallMaxN && int64_t(p.K) * p.N <= 2000000 && p.n_tile == 0 && p.k_split == 0;
+    return (p.dt == BF16 || !p.fused) && p.M <= 4 && p.K <= 1024 && p.N <= kSmallMaxN && int64_t(p.K) * p.N <= 2000000 && p.n_tile == 0 && p.k_split == 0;
 }
 
 hipError_t launch_small(const Problem& p, int NC, hipStream_t s)

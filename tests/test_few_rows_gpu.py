@@ -1,0 +1,71 @@
+"""One to four rows and a small W, where the narrow tiles of the matrix cores stand in for the GEMV kernel: what that one
+gives for the ends of a type's range and for infinite weights.  Needs an MI355X."""
+import numpy as np
+import pytest
+
+import oracle
+from util import to_host_f64
+
+pytestmark = pytest.mark.gpu
+
+# (hidden size, columns): one trip of the waves over K and two, whole and ragged tiles
+SIZES = [(512, 512), (1000, 1016)]
+
+
+@pytest.fixture(scope="module")
+def rl():
+    import torch
+    import paper_2405_05751_amd as pkg
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    pkg.rl_set_variant("auto")
+    pkg.rl_set_tuning(0, 0)
+    return pkg
+
+
+def inputs(M, K, N, dtype, seed):
+    import torch
+    r = torch.Generator().manual_seed(seed)
+    X, g = torch.randn(M, K, generator=r), torch.rand(K, generator=r) + 0.5
+    W = torch.randn(K, N, generator=r) * K ** -0.5
+    return X, g, W
+
+
+def call(rl, X, g, W, eps, dtype):
+    """The library's Y and the one of 64 bits on the same (rounded) inputs."""
+    import torch
+    t = {"f16": torch.float16, "bf16": torch.bfloat16}[dtype]
+    X, g, W = X.to(t), g.to(t), W.to(t)
+    Y = rl.rmsnorm_linear(X.cuda(), g.cuda(), W.cuda(), eps)
+    torch.cuda.synchronize()
+    x, w = X.double().numpy(), W.double().numpy()
+    with np.errstate(all="ignore"):
+        Z = (x * g.double().numpy()) @ w / np.sqrt((x * x).mean(1, keepdims=True) + eps)
+    return to_host_f64(Y, dtype), Z
+
+
+def close(Y, Z, dtype):
+    """Each output is one rounding off (2^-11 or 2^-8 of itself at most), the sums before it are fp32: products of two
+    16-bit numbers are exact in them, and K 2^-24 is far below that rounding.  A quarter of it more for them."""
+    assert np.isfinite(Y).all()
+    err = np.linalg.norm(Y - Z) / np.linalg.norm(Z)
+    assert err <= 1.25 * 2.0 ** -{"f16": 11, "bf16": 8}[dtype], err
+
+
+@pytest.mark.parametrize("K,N", SIZES)
+@pytest.mark.parametrize("M", [1, 4])
+@pytest.mark.parametrize("x,gain", [(50000.0, 1.5), (2500.0, 30.0), (60000.0, 4.0)])
+def test_products_beyond_fp16(rl, M, K, N, x, gain):
+    """x g beyond 65504, X, g and Y within it."""
+    X, g, W = inputs(M, K, N, "f16", 31 + K)
+    X[M - 1, 5], g[5] = x, gain
+    close(*call(rl, X, g, W, 1e-5, "f16"), "f16")
+
+
+@pytest.mark.parametrize("K,N", SIZES)
+@pytest.mark.parametrize("M", [1, 4])
+@pytest.mark.parametrize("dtype,scale,gain", [("f16", 1e-4, 1.0), ("f16", 1e-5, 1.0), ("f16", 3e-6, 1.0), ("f16", 1e-4, 0.02),
+                                              ("bf16", 1e-5, 1.0), ("bf16", 1e-18, 1.0), ("bf16", 1e17, 1.0)])
+def test_small_and_large_products(rl, M, K, N, dtype, scale, gain):
+    """Products near and below a type's smallest numbers keep the bits that fp32 has for them."""
+    X, g, W = inputs(M, K, N, dtype, 37 + K)
+    close(*call(rl, X * scale, g * gain, W, 0.0, dtype), dtype)

@@ -265,3 +265,16 @@ rec.rec_capture(V(7), 0)
 print(linear({M}, {K}, {N}, {dt}, 7, {fn!r}), [n for n in names() if "clear" not in n])
 """)
     assert out[0] == "0 0 ['mid_kernel']" and out[1] == f"0 {SPLIT}"
+
+
+@pytest.mark.parametrize("M,K,N", [(1, 8, 16), (1, 1024, 1952), (3, 304, 6472), (4, 1000, 1016), (4, 64, 31248)])
+def test_one_to_four_rows_of_a_small_w(M, K, N):
+    """Narrow tiles where they keep what the GEMV kernel has for a product: in bf16 and for the plain product, not with the norm in fp16."""
+    out = routes.run(f"""
+lib.rmsnorm_gated_mlp.argtypes = [V, V, V, F, V, L, L, L, I, V]
+print(linear({M}, {K}, {N}), names(), linear({M}, {K}, {N}, F16), names(), linear({M}, {K}, {N // 16 * 8}, BF16, 0, "rmsnorm_gated_mlp"), names(),
+      linear({M}, {K}, {N // 16 * 8}, F16, 0, "rmsnorm_gated_mlp"), names())
+print([(lib.matmul(P[0], P[2], P[3], {M}, {K}, {N}, dt, None), names()) for dt in (F16, BF16)])
+""")
+    small, gemv = "['small_kernel']", "['gemv_splitk_kernel']"
+    assert out == [f"0 {small} 0 {gemv} 0 {small} 0 {gemv}", f"[(0, {small}), (0, {small})]"]

@@ -39,11 +39,14 @@ def test_edges(rl, M, K, N, columns, dtype):
     Y = torch.full((M, N), float("nan"), dtype=X.dtype, device="cuda")
     rl.rmsnorm_linear(X, g, W, w.eps, Y)
     torch.cuda.synchronize()
-    assert small(rl) and rl.rl_last_launch()[1] == columns
+    if M <= 4 and dtype == "f16":            # (fp32 arithmetic: see test_few_rows_gpu.py)
+        assert rl.rl_last_variant() == "gemv"
+    else:
+        assert small(rl) and rl.rl_last_launch()[1] == columns
+        assert rl.rl_workspace_bytes(M, K, N, X.dtype) == 0
     Z = oracle.rmsnorm_linear(w.X, w.g, w.W, dtype, w.eps)
     compare(to_host_f64(Y, dtype), Z, dtype, f"{M}x{K}x{N}")
-    # no workspace, so the same bits whatever the entry point
-    assert rl.rl_workspace_bytes(M, K, N, X.dtype) == 0
+    # the same bits whatever the entry point
     Y2 = torch.full_like(Y, float("nan"))
     assert rl.lib().rmsnorm_linear_noalloc(X.data_ptr(), g.data_ptr(), W.data_ptr(), float(w.eps), Y2.data_ptr(), M, K, N,
                                            {"f16": 0, "bf16": 1}[dtype], torch.cuda.current_stream().cuda_stream) == 0
@@ -66,7 +69,7 @@ def test_row_blocks(rl, M, K, N, dtype):
 
 
 @pytest.mark.parametrize("interleaved", [False, True])
-@pytest.mark.parametrize("M,K,H,dtype", [(100, 520, 448, "f16"), (300, 264, 1024, "bf16"), (1, 40, 64, "bf16"), (4, 520, 128, "f16"), (16, 776, 1024, "bf16"), (32, 264, 2112, "f16"), (33, 512, 576, "bf16"),
+@pytest.mark.parametrize("M,K,H,dtype", [(100, 520, 448, "f16"), (300, 264, 1024, "bf16"), (1, 40, 64, "bf16"), (4, 520, 128, "bf16"), (5, 520, 128, "f16"), (16, 776, 1024, "bf16"), (32, 264, 2112, "f16"), (33, 512, 576, "bf16"),
                                          (64, 272, 6400, "f16")])
 def test_gated(rl, M, K, H, dtype, interleaved):
     import torch
