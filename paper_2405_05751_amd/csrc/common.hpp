@@ -327,6 +327,28 @@ __device__ __forceinline__ float2_t ld_dev2(const float* p) {
     return __builtin_bit_cast(float2_t, u);
 }
 
+// Products (p0, p1) in fp32, neither of them -0, as two packed 16-bit operands with hi + lo = p: hi is the product cut off (not
+// rounded) one fp32 ulp below its value, lo what is left.  Both have the product's sign and neither is zero unless the product is, so that
+// an infinite factor beside them gives what it gives in fp32; an infinite product has it in lo.
+// In bf16 they are the product of two bf16 numbers exactly (8 + 8 bits).
+template <typename T> struct TwoPart;
+template <> struct TwoPart<Bf16> {
+    static __device__ __forceinline__ void split(float p0, float p1, uint32_t* hi, uint32_t* lo) {
+        const uint32_t b0 = __builtin_elementwise_sub_sat(__float_as_uint(p0), 1u), b1 = __builtin_elementwise_sub_sat(__float_as_uint(p1), 1u);
+        *hi = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
+        const float l0 = p0 - __uint_as_float(b0 & 0xffff0000u), l1 = p1 - __uint_as_float(b1 & 0xffff0000u);
+        *lo = __builtin_amdgcn_perm(__float_as_uint(l1), __float_as_uint(l0), 0x07060302u);
+    }
+};
+template <> struct TwoPart<Fp16> {
+    static __device__ __forceinline__ void split(float p0, float p1, uint32_t* hi, uint32_t* lo) {
+        const float c0 = __uint_as_float(__builtin_elementwise_sub_sat(__float_as_uint(p0), 1u));
+        const float c1 = __uint_as_float(__builtin_elementwise_sub_sat(__float_as_uint(p1), 1u));
+        *hi = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(c0, c1));
+        *lo = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(p0 - Elem<Fp16>::lo(*hi), p1 - Elem<Fp16>::hi(*hi)));
+    }
+};
+
 // A direct load to LDS: lane l's 16 bytes at byte offset v of the resource (zeros beyond it) go to byte dst + 16 l.  In assembly:
 // as a builtin, the compiler takes every later LDS read for a possible reader of the bytes in flight and waits for all
 // loads first.  So the waits for these are placed by hand.

@@ -57,25 +57,6 @@ template <> struct MfmaOdd<Fp16> {
     }
 };
 
-// products (p0, p1), neither -0, as two packed operands with hi + lo = p (see the header comment)
-template <typename T> struct TwoPart;
-template <> struct TwoPart<Bf16> {
-    static __device__ __forceinline__ void split(float p0, float p1, uint32_t* hi, uint32_t* lo) {
-        const uint32_t b0 = __builtin_elementwise_sub_sat(__float_as_uint(p0), 1u), b1 = __builtin_elementwise_sub_sat(__float_as_uint(p1), 1u);
-        *hi = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
-        const float l0 = p0 - __uint_as_float(b0 & 0xffff0000u), l1 = p1 - __uint_as_float(b1 & 0xffff0000u);
-        *lo = __builtin_amdgcn_perm(__float_as_uint(l1), __float_as_uint(l0), 0x07060302u);
-    }
-};
-template <> struct TwoPart<Fp16> {
-    static __device__ __forceinline__ void split(float p0, float p1, uint32_t* hi, uint32_t* lo) {
-        const float c0 = __uint_as_float(__builtin_elementwise_sub_sat(__float_as_uint(p0), 1u));
-        const float c1 = __uint_as_float(__builtin_elementwise_sub_sat(__float_as_uint(p1), 1u));
-        *hi = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(c0, c1));
-        *lo = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(p0 - Elem<Fp16>::lo(*hi), p1 - Elem<Fp16>::hi(*hi)));
-    }
-};
-
 // ------------------------------------------------------------------------------------- the product
 struct OddCold {                             // what the first loads do not need
     u16* Y;

@@ -15,6 +15,7 @@
 // 2600 and W to 140 MB the 170 that run here take 0.60 of the time (geometric mean; 0.39 to 1.00), at the same distance from fp64 (ratio
 // 0.9999 to 1.001).  What bounds it: launch and first loads, 2 us; then a unit's intake, K (32 NC + 32 MB) bytes per workgroup.
 #include <algorithm>
+#include <type_traits>
 #include "common.hpp"
 
 namespace rmsnl {
@@ -98,7 +99,9 @@ __global__ __launch_bounds__(64 * small_waves(MB)) void small_kernel(
 #pragma unroll
         for (int c = 0; c < NC; ++c) acc[mb][c] = float4_t{0.f, 0.f, 0.f, 0.f};
     }
-    constexpr bool TWO = FUSED && MB <= 2;
+    // Two operands for a product, up to 32 rows.  In bf16 cut off, not rounded: the calls of one to four rows that come here in place of
+    // the GEMV kernel keep its infinities (rounded, lo is zero or of the other sign, and an infinite W gave NaN).
+    constexpr bool TWO = FUSED && MB <= 2, CUT = TWO && std::is_same<T, Bf16>::value;
     const u16* const frag = stage + (8 * q + (i >> 2)) * TN + 4 * (i & 3);       // transposing read: 4 k x 16 columns per 16 lanes
     for (int k0 = 32 * wave; k0 < K; k0 += 32 * NW) {
         uint4_t x[MB], gq;
@@ -114,7 +117,7 @@ __global__ __launch_bounds__(64 * small_waves(MB)) void small_kernel(
         __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8));    // all of them: the compiler does not know of the direct loads
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
-        // X-hat in the storage type, up to 32 rows with its rounding's remainder as a second operand; squares of the raw X
+        // X-hat in the storage type, up to 32 rows with its remainder as a second operand; squares of the raw X
         uint4_t hi[MB], lo[TWO ? MB : 1];
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
@@ -124,9 +127,16 @@ __global__ __launch_bounds__(64 * small_waves(MB)) void small_kernel(
                 const float x0 = Elem<T>::lo(x[mb][e]), x1 = Elem<T>::hi(x[mb][e]);
                 ss[mb] = __fmaf_rn(x0, x0, ss[mb]);
                 ss[mb] = __fmaf_rn(x1, x1, ss[mb]);
-                const float p0 = x0 * Elem<T>::lo(gq[e]), p1 = x1 * Elem<T>::hi(gq[e]);
-                hi[mb][e] = Elem<T>::pack(p0, p1);
-                if (TWO) lo[mb][e] = Elem<T>::pack(p0 - Elem<T>::lo(hi[mb][e]), p1 - Elem<T>::hi(hi[mb][e]));
+                const float g0 = Elem<T>::lo(gq[e]), g1 = Elem<T>::hi(gq[e]);
+                if constexpr (CUT) {
+                    uint32_t h, l;
+                    TwoPart<T>::split(__fmaf_rn(x0, g0, 0.f), __fmaf_rn(x1, g1, 0.f), &h, &l);       // (the sum with +0 turns -0 into +0)
+                    hi[mb][e] = h; lo[mb][e] = l;
+                } else {
+                    const float p0 = x0 * g0, p1 = x1 * g1;
+                    hi[mb][e] = Elem<T>::pack(p0, p1);
+                    if (TWO) lo[mb][e] = Elem<T>::pack(p0 - Elem<T>::lo(hi[mb][e]), p1 - Elem<T>::hi(hi[mb][e]));
+                }
             }
         }
 #pragma unroll

@@ -64,8 +64,36 @@ def test_products_beyond_fp16(rl, M, K, N, x, gain):
 @pytest.mark.parametrize("K,N", SIZES)
 @pytest.mark.parametrize("M", [1, 4])
 @pytest.mark.parametrize("dtype,scale,gain", [("f16", 1e-4, 1.0), ("f16", 1e-5, 1.0), ("f16", 3e-6, 1.0), ("f16", 1e-4, 0.02),
-                                              ("bf16", 1e-5, 1.0), ("bf16", 1e-18, 1.0), ("bf16", 1e17, 1.0)])
+                                              ("bf16", 1e-5, 1.0), ("bf16", 1e-18, 1.0), ("bf16", 1e-18, 1e-18), ("bf16", 1e17, 1.0)])
 def test_small_and_large_products(rl, M, K, N, dtype, scale, gain):
     """Products near and below a type's smallest numbers keep the bits that fp32 has for them."""
     X, g, W = inputs(M, K, N, dtype, 37 + K)
     close(*call(rl, X * scale, g * gain, W, 0.0, dtype), dtype)
+
+
+@pytest.mark.parametrize("K,N", SIZES)
+@pytest.mark.parametrize("M", [1, 4])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("gain", ["ones", "any"])
+def test_infinite_weights(rl, M, K, N, dtype, gain):
+    """One infinity in a column of W, or in g, gives the infinities that it gives in 64 bits; the other columns stay as they are,
+    with products of zero of either sign among theirs.  (Gains of one: products that one 16-bit number holds.)"""
+    import torch
+    X, g, W = inputs(M, K, N, dtype, 41 + K)
+    if gain == "ones":
+        g[:] = 1.0
+    X[:, 9], X[M - 1, 11], g[13] = X[:, 9].abs() + 0.5, -0.0, 0.0
+    plain = W.clone()
+    W[9, 3], W[K - 1, 17], W[100, N - 1] = float("inf"), float("-inf"), float("inf")
+    Y, Z = call(rl, X, g, W, 1e-5, dtype)
+    infinite = [3, 17, N - 1]
+    assert np.isinf(Z[:, infinite]).all() and np.array_equal(Y[:, infinite], Z[:, infinite])
+    rest = [n for n in range(N) if n not in infinite]
+    close(Y[:, rest], Z[:, rest], dtype)
+    t = {"f16": torch.float16, "bf16": torch.bfloat16}[dtype]
+    P = rl.matmul(X.to(t).cuda(), W.to(t).cuda())
+    torch.cuda.synchronize()
+    assert np.array_equal(to_host_f64(P, dtype)[:, infinite], Z[:, infinite])
+    g[9] = float("inf")                      # an infinite product of every column
+    Y, Z = call(rl, X, g, plain, 1e-5, dtype)
+    assert np.isinf(Z).all() and np.array_equal(Y, Z)
