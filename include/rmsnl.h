@@ -380,8 +380,8 @@ rl_status rl_ff_pairs(const void* X, const void* g, const void* W, void* Y, int6
  * NULL returns to the library's own buffer.  With a lent buffer too small for a call, the split-K variants
  * return RL_ERR_WORKSPACE; the two-kernel tile form is then skipped by RL_AUTO (the fused tile kernel runs), and
  * the kernel for K or N not a multiple of 8 runs unsplit.
- * rl_workspace_bytes gives the bytes of it an rmsnorm_linear call of that shape would like (0 if none, also where the
- * call has them in its stream's region).
+ * rl_workspace_bytes gives the bytes of it that an rmsnorm_linear call of that shape, or a gated block with H = N / 2 in either
+ * layout, would like, whichever wants more (0 if none, also where the call has them in its stream's region).
  */
 rl_status rl_set_workspace(void* dev_ptr, size_t bytes);
 size_t rl_workspace_bytes(int64_t M, int64_t K, int64_t N, rl_dtype dt);

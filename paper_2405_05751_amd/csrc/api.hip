@@ -985,11 +985,9 @@ rl_status rl_set_workspace(void* dev_ptr, size_t bytes)
     return RL_OK;
 }
 
-size_t rl_workspace_bytes(int64_t M, int64_t K, int64_t N, rl_dtype dt)
+// of the workspace that calls share: what this call would like
+static size_t shared_workspace_of(Problem p)
 {
-    if (check_dims(M, K, N, dt) != RL_OK) return 0;
-    Problem p{};
-    p.M = int(M); p.K = int(K); p.N = int(N); p.dt = DType(dt); p.fused = 1;
     rl_variant v;
     Tuned tuned{RL_AUTO, 0, 0};
     {
@@ -998,7 +996,7 @@ size_t rl_workspace_bytes(int64_t M, int64_t K, int64_t N, rl_dtype dt)
         v = g_variant;
         if (v != RL_AUTO) { p.n_tile = g_n_tile; p.k_split = g_k_split; }
         else {
-            auto it = g_tuned.find(TuneKey(p.M, p.K, p.N, int(p.dt), 0));
+            auto it = g_tuned.find(TuneKey(p.M, p.K, p.N, int(p.dt), p.gated | (p.gate_group ? 2 : 0)));
             if (it != g_tuned.end()) tuned = it->second;
         }
     }
@@ -1010,19 +1008,31 @@ size_t rl_workspace_bytes(int64_t M, int64_t K, int64_t N, rl_dtype dt)
         if (var == kOddSizes) return odd_workspace_bytes(q);
         return 0;
     };
-    size_t need = 0;
-    if (v == RL_AUTO) {
-        v = choose_auto(p);
-        if (v == RL_NAIVE) v = kOddSizes;
-        if ((v == RL_MFMA_TILE && prefers_two_kernels(p)) || prefers_mid_tiles(p)) v = RL_MFMA_TILE_PRE;   // optional: without it the fused kernel runs
-        need = spares_workspace(v, p) ? 0 : need_of(v, p);
-        if (tuned.variant != RL_AUTO) {        // a shape found by rl_autotune runs first: room for whichever needs more
-            Problem q = p;
-            q.n_tile = tuned.n_tile; q.k_split = tuned.k_split;
-            if (tuned.variant != kOddSizes) need = std::max(need, need_of(tuned.variant, q));    // (that one: its stream's region)
-        }
-    } else {
-        need = need_of(with_columns(v, p), p);
+    if (v != RL_AUTO) return need_of(with_columns(v, p), p);
+    v = choose_auto(p);
+    if (v == RL_NAIVE) v = kOddSizes;
+    if ((v == RL_MFMA_TILE && prefers_two_kernels(p)) || prefers_mid_tiles(p)) v = RL_MFMA_TILE_PRE;   // optional: without it the fused kernel runs
+    size_t need = spares_workspace(v, p) ? 0 : need_of(v, p);
+    if (tuned.variant != RL_AUTO) {            // a shape found by rl_autotune runs first: room for whichever needs more
+        Problem q = p;
+        q.n_tile = tuned.n_tile; q.k_split = tuned.k_split;
+        if (tuned.variant != kOddSizes) need = std::max(need, need_of(tuned.variant, q));    // (that one: its stream's region)
+    }
+    return need;
+}
+
+size_t rl_workspace_bytes(int64_t M, int64_t K, int64_t N, rl_dtype dt)
+{
+    if (check_dims(M, K, N, dt) != RL_OK) return 0;
+    Problem p{};
+    p.M = int(M); p.K = int(K); p.N = int(N); p.dt = DType(dt); p.fused = 1;
+    size_t need = shared_workspace_of(p);
+    // The gated block with H = N / 2 is asked for with the same question, and its launch need not be the plain one's.
+    if (N % 2 == 0) {
+        p.gated = 1;
+        need = std::max(need, shared_workspace_of(p));
+        p.gate_group = 64;                     // its own entry in what rl_autotune found
+        if (N % 128 == 0) need = std::max(need, shared_workspace_of(p));
     }
     return need ? need + kHeadBytes : 0;
 }

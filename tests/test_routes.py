@@ -278,3 +278,40 @@ print([(lib.matmul(P[0], P[2], P[3], {M}, {K}, {N}, dt, None), names()) for dt i
 """)
     small, gemv = "['small_kernel']", "['gemv_splitk_kernel']"
     assert out == [f"0 {small} 0 {gemv} 0 {small} 0 {gemv}", f"[(0, {small}), (0, {small})]"]
+
+
+def test_workspace_query_covers_the_gated_block():
+    """What rl_workspace_bytes says of (M, K, N) holds for the plain call and for the gated block with H = N / 2 in both layouts: 0 only
+    if none takes partial sums (or X-hat) through the shared workspace, else enough for each to launch what it would with any amount."""
+    out = routes.run("""
+import math, random
+for fn in ("rmsnorm_gated_mlp", "rmsnorm_gated_mlp_interleaved"):
+    getattr(lib, fn).argtypes = [V, V, V, F, V, L, L, L, I, V]
+r = random.Random(5)
+spread = lambda lo, hi: int(math.exp(r.uniform(math.log(lo), math.log(hi))))
+def go(fn, M, K, N, dt):
+    st = linear(M, K, N if fn == "rmsnorm_linear" else N // 2, dt, 7, fn)
+    return st, [(l.mangled, l.grid) for l in launches()]
+shapes = [(5, 1984, 2880, BF16), (29, 2224, 1040, F16), (5, 2456, 1504, BF16), (12, 2216, 128, BF16)]
+for n in range(1500):
+    shapes.append((spread(1, 64) if n % 3 else spread(65, 1024), 8 * spread(8, 1024), 128 * spread(1, 128) if n % 2 else 16 * spread(4, 1024),
+                   r.choice((F16, BF16, BF16, F32))))
+shared = 0
+for M, K, N, dt in shapes:
+    need = lib.rl_workspace_bytes(M, K, N, dt)
+    for fn in ["rmsnorm_linear", "rmsnorm_gated_mlp"] + ["rmsnorm_gated_mlp_interleaved"] * (N % 128 == 0):
+        rec.rec_capture(V(7), 1)                         # no workspace can be had then
+        without = go(fn, M, K, N, dt)
+        rec.rec_capture(V(7), 0)
+        lib.rl_set_workspace(V(1 << 43), 1 << 32)
+        any_amount = go(fn, M, K, N, dt)
+        assert any_amount[0] == 0
+        if need:
+            lib.rl_set_workspace(V(1 << 43), need)
+            assert go(fn, M, K, N, dt) == any_amount, (fn, M, K, N, dt)
+        lib.rl_set_workspace(None, 0)
+        assert need or without == any_amount, (fn, M, K, N, dt)
+        shared += need != 0
+print(shared > 500)
+""")
+    assert out == ["True"]
