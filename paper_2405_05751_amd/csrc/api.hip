@@ -21,7 +21,7 @@ constexpr int kMaxDevices = 16;
 
 thread_local char tl_error[512] = "";
 thread_local rl_variant tl_last_variant = RL_AUTO;
-thread_local int tl_last_plan[3] = {0, 0, 0};
+thread_local int tl_last_plan[4] = {0, 0, 0, 0};
 
 std::mutex g_mu;
 // Held while the kernels of a call that pass data through a workspace are enqueued: another thread's call on the same
@@ -340,7 +340,7 @@ rl_status run(Problem& p, void* stream, const Workspace* fixed = nullptr, const 
         }
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    tl_last_plan[0] = tl_last_plan[1] = tl_last_plan[2] = 0;
+    std::fill(tl_last_plan, tl_last_plan + 4, 0);
     p.plan = tl_last_plan;
     struct Step { rl_variant variant; int n_tile, k_split; bool own, without; };
     Step order[9];                         // what is tried, one after the other; without = only in a form that needs no workspace
@@ -648,8 +648,8 @@ static rl_status autotune_core(const void* X, const void* g, const void* const* 
     Tuned best{RL_AUTO, 0, 0};
     float best_ms = 0.f;
     rl_status result = RL_OK;
-    std::vector<std::tuple<int, int, int, int>> seen;           // (variant, columns, slabs, workgroups) already timed
-    int plan[3];
+    std::vector<std::tuple<int, int, int, int, int>> seen;      // (variant, columns, slabs, workgroups, form) already timed
+    int plan[4];
     for (const Cand& c : cands) {
         if (c.v == RL_NAIVE && best.variant != RL_AUTO) break;      // the fallback only if nothing else runs
         Problem p = base;
@@ -661,12 +661,12 @@ static rl_status autotune_core(const void* X, const void* g, const void* const* 
         for (int i = 0; i < 2 + reps && ok; ++i) {
             if (i == 2) he = hipEventRecord(e0, s);
             p.W = Ws[i % n_w];
-            plan[0] = plan[1] = plan[2] = 0;
+            std::fill(plan, plan + 4, 0);
             hipError_t le = launch_variant(c.v, p, s, &why, &ws_status, nullptr, nullptr, c.v == kOddSizes);
             if (ws_status != RL_OK || le == hipErrorInvalidValue) { (void)hipGetLastError(); ok = false; break; }
             if (le != hipSuccess) { result = fail(RL_ERR_HIP, "kernel launch: %s", hipGetErrorString(le)); ok = false; }
             if (i == 0) {                                           // the same launch as an earlier candidate: once is enough
-                const auto key = std::make_tuple(int(c.v), plan[0], plan[1], plan[2]);
+                const auto key = std::make_tuple(int(c.v), plan[0], plan[1], plan[2], plan[3]);
                 if (plan[2] != 0 && std::find(seen.begin(), seen.end(), key) != seen.end()) { ok = false; break; }
                 seen.push_back(key);
             }
@@ -903,7 +903,7 @@ rl_status rl_ff_pairs(const void* X, const void* g, const void* W, void* Y, int6
     p.X = X; p.g = g; p.W = W; p.Y = Y;
     p.M = int(M); p.K = int(K); p.N = int(N);
     p.fused = 1; p.gated = gated ? 1 : 0; p.dt = BF16; p.n_tile = 128; p.k_split = slabs;
-    tl_last_plan[0] = tl_last_plan[1] = tl_last_plan[2] = 0;
+    std::fill(tl_last_plan, tl_last_plan + 4, 0);
     p.plan = tl_last_plan;
     const size_t need = gemv_workspace_bytes(p);
     if (need) {

@@ -39,7 +39,8 @@ struct Problem {
     int n_tile;
     int k_split;
     // where a launcher reports the launch shape it used (columns per workgroup or tile shape, K slabs or
-    // waves, workgroups of the main kernel), or null
+    // waves, workgroups of the main kernel, and 1 where that is the skinny variant's form for a small W, which the others do not tell
+    // from its 64 columns in one slab), or null
     int* plan;
     // optional stage trace: kTraceSlots 64-bit time stamps per workgroup, or null
     unsigned long long* trace;

@@ -297,7 +297,7 @@ bool small_wins_over_gemv(const Problem& p)
 hipError_t launch_small(const Problem& p, int NC, hipStream_t s)
 {
     const int n_tiles = p.gated ? (p.N / 2 + 8 * NC - 1) / (8 * NC) : (p.N + 16 * NC - 1) / (16 * NC);
-    if (p.plan) { p.plan[0] = 16 * NC; p.plan[1] = 1; p.plan[2] = n_tiles * ((p.M + 63) / 64); }
+    if (p.plan) { p.plan[0] = 16 * NC; p.plan[1] = 1; p.plan[2] = n_tiles * ((p.M + 63) / 64); p.plan[3] = 1; }
     return p.dt == F16 ? small_rows<Fp16>(p, NC, n_tiles, s) : small_rows<Bf16>(p, NC, n_tiles, s);
 }
 

@@ -315,3 +315,22 @@ for M, K, N, dt in shapes:
 print(shared > 500)
 """)
     assert out == ["True"]
+
+
+@pytest.mark.parametrize("M,K,N", [(16, 264, 12808), (64, 264, 12296), (64, 272, 12800), (8, 512, 512)])
+def test_tuner_times_both_kernels_of_the_skinny_variant(M, K, N):
+    """The narrow tiles in 64 columns and the 64-column tiles in one slab are different launches of as many workgroups."""
+    out = routes.run(f"""
+lib.rl_autotune.argtypes = [V, V, V, F, V, L, L, L, I, I, I, V, V]
+assert lib.rl_autotune(P[0], P[1], P[2], 1e-5, P[3], {M}, {K}, {N}, BF16, 0, 20, None, None) == 0
+tried = [(l.name, l.grid) for l in launches()]           # (a candidate that is dropped has been launched once)
+lib.rl_set_variant(2)
+lib.rl_set_tuning(64, 1)
+assert linear({M}, {K}, {N}) == 0
+tiles = launches()[-1]
+lib.rl_set_tuning(0, 0)
+assert linear({M}, {K}, {N}) == 0
+narrow = launches()[-1]
+print(tiles.name, narrow.name, *[tried.count((l.name, l.grid)) >= 20 for l in (tiles, narrow)], narrow.grid == tiles.grid)
+""")
+    assert out == [f"skinny_kernel small_kernel True True {N > 10000}"]
