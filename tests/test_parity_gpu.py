@@ -8,7 +8,7 @@ import pytest
 
 import oracle
 import workloads
-from util import TOL, compare, to_device, to_host_f64, upload
+from util import TOL, compare, compare_gated, to_device, to_host_f64, upload
 
 pytestmark = pytest.mark.gpu
 
@@ -36,12 +36,15 @@ def _workload(name):
 
 def _run(rl, w, variant="auto", tuning=(0, 0), rows=None):
     import torch
+    if variant == "skinny_128":              # its kernel with 128 columns, also where the variant takes narrow tiles by itself
+        variant, tuning = "skinny", (128, 0)
     rl.rl_set_variant(variant)
     rl.rl_set_tuning(*tuning)
     X, g, W = upload(w)
     Y = rl.rmsnorm_linear(X, g, W, w.eps)
     torch.cuda.synchronize()
     used = rl.rl_last_variant()
+    assert tuning != (128, 0) or rl.rl_last_launch()[1] == 128
     rl.rl_set_variant("auto")
     rl.rl_set_tuning(0, 0)
     if rows is not None:
@@ -58,7 +61,7 @@ def _supported(variant, w):
         return False
     if variant == "gemv":
         return w.M <= 16
-    if variant == "skinny":
+    if variant in ("skinny", "skinny_128"):
         return w.M <= 1024
     if variant == "tile_pre":
         return w.M > 64
@@ -96,7 +99,7 @@ def test_config_forced_variant(rl, name, variant):
 
 # ------------------------------------------------------------------ the paper's own shape
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
-@pytest.mark.parametrize("variant", ["auto", "naive", "gemv", "skinny", "tile"])
+@pytest.mark.parametrize("variant", ["auto", "naive", "gemv", "skinny", "skinny_128", "tile"])
 def test_paper_shape(rl, dtype, variant):
     """X[16,1024], G[1024], W[1024,4096] -> Z[16,4096] (shapes of the case-study figure)."""
     w = workloads.make(16, 1024, 4096, dtype, 1e-6, 901)
@@ -116,7 +119,7 @@ RAGGED = [
 ]
 
 
-@pytest.mark.parametrize("variant", ["auto", "gemv", "skinny", "tile"])
+@pytest.mark.parametrize("variant", ["auto", "gemv", "skinny", "skinny_128", "tile"])
 @pytest.mark.parametrize("M,K,N", RAGGED)
 def test_ragged_shapes(rl, M, K, N, variant):
     w = workloads.make(M, K, N, "bf16", 1e-5, 1000 + M * 7 + K + N, outlier_frac=0.1 if M > 8 else 0.0)
@@ -260,13 +263,53 @@ def test_random_shapes_automatic_choice(rl, M, K, N, gated):
 
 # ------------------------------------------------------------------ skinny kernel, block after block
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("variant", ["skinny", "skinny_128"])
 @pytest.mark.parametrize("M,K,N", [(65, 264, 136), (128, 1032, 520), (200, 4096, 1024), (1024, 520, 264)])
-def test_skinny_runs_larger_m_in_blocks_of_64_rows(rl, M, K, N, dtype):
+def test_skinny_runs_larger_m_in_blocks_of_64_rows(rl, M, K, N, variant, dtype):
     w = workloads.make(M, K, N, dtype, 1e-5, 4800 + M + K + N, outlier_frac=0.05)
     Z = oracle.rmsnorm_linear(w.X, w.g, w.W, w.dtype, w.eps)
-    Y, used = _run(rl, w, "skinny")
+    Y, used = _run(rl, w, variant)
     assert used == "skinny"
-    compare(Y, Z, w.dtype, f"skinny in blocks {M}x{K}x{N} {dtype}")
+    compare(Y, Z, w.dtype, f"{variant} in blocks {M}x{K}x{N} {dtype}")
+
+
+# 64-row runs of W in all, four waves: 0 to 7 runs fall to a wave
+RUNS = [1, 3, 6, 8, 11, 14, 19, 22, 25, 28]
+
+
+@pytest.mark.parametrize("R", RUNS)
+@pytest.mark.parametrize("M", [3, 16, 17, 33, 64, 65, 130])
+def test_skinny_kernel_every_number_of_runs(rl, M, R):
+    """The K loop of the 128-column kernel ends in code of its own for each number of runs that is left (and at 64 rows and in row
+    blocks in code with conditions): all of K in one slab, a last run of 40 rows, one whole tile and one of 8 columns; the
+    fused block, the gated one and the plain product."""
+    import torch
+    K, N = 64 * R - 24, 136
+    dtype = "bf16" if (M + R) % 2 else "f16"
+    w = workloads.make(M, K, N, dtype, 1e-5, 4850 + 31 * M + R)
+    X, g, W = upload(w)
+    Z = oracle.rmsnorm_linear(w.X, w.g, w.W, dtype, w.eps)
+    wg = workloads.make(M, K, 2 * N, dtype, 1e-5, 4860 + 31 * M + R)
+    Xg, gg, Wg = upload(wg)
+    rl.rl_set_variant("skinny")
+    rl.rl_set_tuning(128, 1)
+    try:
+        launches = []
+        Y = rl.rmsnorm_linear(X, g, W, w.eps)
+        launches.append(rl.rl_last_launch())
+        U = rl.rmsnorm_gated_mlp(Xg, gg, Wg, wg.eps)
+        launches.append(rl.rl_last_launch())
+        P = rl.matmul(X, W)
+        launches.append(rl.rl_last_launch())
+        torch.cuda.synchronize()
+    finally:
+        rl.rl_set_variant("auto")
+        rl.rl_set_tuning(0, 0)
+    blocks = -(-M // 64)
+    assert launches == [("skinny", 128, 1, 2 * blocks), ("skinny", 128, 1, 3 * blocks), ("skinny", 128, 1, 2 * blocks)]
+    compare(to_host_f64(Y, dtype), Z, dtype, f"{R} runs, {M} rows")
+    compare_gated(to_host_f64(U, dtype), oracle.rmsnorm_linear(wg.X, wg.g, wg.W, dtype, wg.eps), dtype, f"{R} runs, {M} rows, gated")
+    compare(to_host_f64(P, dtype), to_host_f64(X, dtype) @ to_host_f64(W, dtype), dtype, f"{R} runs, {M} rows, plain")
 
 
 def test_mid_m_automatic_choice(rl):
@@ -380,7 +423,7 @@ def test_hand_cases_on_gpu(rl, golden_hand_cases, dtype):
 
 
 # ------------------------------------------------------------------ invariants on the GPU
-@pytest.mark.parametrize("variant", ["gemv", "skinny", "tile", "naive"])
+@pytest.mark.parametrize("variant", ["gemv", "skinny", "skinny_128", "tile", "naive"])
 def test_scale_invariance_on_gpu(rl, variant):
     """eps = 0: Y(cX) = Y(X); with c a power of two the inputs stay exact and so do the outputs."""
     w = workloads.make(8, 512, 512, "bf16", 0.0, 5001)
@@ -412,7 +455,7 @@ def test_zero_row_nan_positions(rl):
     with np.errstate(all="ignore"):
         Z0 = oracle.rmsnorm_linear(w.X, w.g, w.W, w.dtype, 0.0)
     assert np.isnan(Z0[2]).all()
-    for variant in ("gemv", "naive", "skinny"):
+    for variant in ("gemv", "naive", "skinny", "skinny_128"):
         if _supported(variant, w):
             Y, _ = _run(rl, w, variant)
             compare(Y, Z0, w.dtype, f"zero row eps=0/{variant}")
@@ -434,7 +477,7 @@ def test_bit_reproducible(rl, name, variant):
         assert np.array_equal(Y1, Y2), f"{name}/{variant} differs between runs"
 
 
-@pytest.mark.parametrize("variant", ["auto", "gemv", "skinny", "tile", "naive"])
+@pytest.mark.parametrize("variant", ["auto", "gemv", "skinny", "skinny_128", "tile", "naive"])
 def test_output_canaries(rl, variant):
     """Y sits inside a larger buffer filled with a sentinel: nothing outside Y may change."""
     import torch
@@ -447,10 +490,12 @@ def test_output_canaries(rl, variant):
     buf = torch.full((pad + w.M * w.N + pad,), 123.0, dtype=torch.bfloat16, device="cuda")
     Y = buf[pad:pad + w.M * w.N].view(w.M, w.N)
     Y.fill_(float("nan"))
-    rl.rl_set_variant(variant)
+    rl.rl_set_variant(variant.split("_")[0])
+    rl.rl_set_tuning(128 if variant == "skinny_128" else 0, 0)
     rl.rmsnorm_linear(X, g, W, w.eps, Y)
     torch.cuda.synchronize()
     rl.rl_set_variant("auto")
+    rl.rl_set_tuning(0, 0)
     assert torch.all(buf[:pad] == 123.0) and torch.all(buf[pad + w.M * w.N:] == 123.0)
     compare(to_host_f64(Y, w.dtype), Z, w.dtype, f"canary/{variant}")
 

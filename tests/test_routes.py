@@ -334,3 +334,72 @@ narrow = launches()[-1]
 print(tiles.name, narrow.name, *[tried.count((l.name, l.grid)) >= 20 for l in (tiles, narrow)], narrow.grid == tiles.grid)
 """)
     assert out == [f"skinny_kernel small_kernel True True {N > 10000}"]
+
+
+SMALL = r"_ZN5rmsnl12small_kernelINS_4(Bf16|Fp16)ELi(\d+)ELi(\d+)ELb(\d)ELb(\d)E"
+
+
+def test_kernel_of_every_narrow_tile_test():
+    """tests/test_small_gpu.py reads columns and slabs, which 64-column tiles of the other kernel report as well: here its calls by name."""
+    import test_small_gpu as t
+    out = routes.run(f"""
+for fn in ("rmsnorm_gated_mlp", "rmsnorm_gated_mlp_interleaved"):
+    getattr(lib, fn).argtypes = [V, V, V, F, V, L, L, L, I, V]
+def went():
+    l, = launches()
+    m = re.match(r"{SMALL}", l.mangled)
+    return (m.group(1), *map(int, m.groups()[1:])) if m else l.name
+blocks = lambda M: 4 if M > 64 else -(-M // 16)
+kinds = ((F16, "Fp16"), (BF16, "Bf16"))
+for M, K, N, columns in {t.EDGES}:
+    for dt, name in kinds:
+        assert linear(M, K, N, dt) == 0
+        want = "gemv_splitk_kernel" if M <= 4 and dt == F16 else (name, blocks(M), columns // 16, 1, 0)
+        assert went() == want, (M, K, N, dt)
+for sizes, fns in (({t.BLOCKS}, ["rmsnorm_linear"]), ({t.GATED}, ["rmsnorm_gated_mlp", "rmsnorm_gated_mlp_interleaved"])):
+    for M, K, N, dtype in sizes:
+        for fn in fns:
+            dt, name = kinds[dtype == "bf16"]
+            assert linear(M, K, N, dt, 0, fn) == 0
+            w = went()
+            assert w[:2] == (name, blocks(M)) and w[3:] == (1, int(len(fns) == 2)), (M, K, N, dt, fn, w)
+for M, dt in ((7, BF16), (40, F16)):
+    assert linear(M, 264, 520, dt) == 0
+    a = went()
+    assert lib.matmul(P[0], P[2], P[3], M, 264, 520, dt, None) == 0
+    b = went()
+    assert (a[1], a[3:]) == (blocks(M), (1, 0)) and (b[1], b[3:]) == (blocks(M), (0, 0))
+print("ok")
+""")
+    assert out == ["ok"]
+
+
+def test_kernel_of_every_128_column_test():
+    """The tests that ask the skinny variant for 128 columns run its own kernel, in all its row counts."""
+    import test_gated_gpu as g
+    import test_parity_gpu as t
+    runs = [(M, 64 * R - 24, 136) for M in (3, 16, 17, 33, 64, 65, 130) for R in t.RUNS]
+    out = routes.run(f"""
+lib.rl_set_variant(2)
+def went(call):
+    assert call() == 0
+    l = [l for l in launches() if l.name != "clear_counters_kernel"]
+    m = re.match(r"_ZN5rmsnl13skinny_kernelINS_4(?:Bf16|Fp16)ELi(\\d)ELb(\\d)ELb(\\d)ELi(\\d)E", l[0].mangled)
+    assert len(l) == 1 and m, l[0].mangled
+    return tuple(map(int, m.groups()))
+seen = set()
+lib.rl_set_tuning(128, 0)
+for M, K, N in {t.RAGGED + [(16, 1024, 4096), (5, 520, 776), (8, 512, 512), (4, 256, 256), (65, 264, 136), (128, 1032, 520), (200, 4096, 1024), (1024, 520, 264)]}:
+    w = went(lambda: linear(M, K, N))
+    assert w[:3] == (4 if M > 64 else -(-M // 16), 1, 0) and (w[3] > 0) == (M > 64), (M, K, N, w)
+for M, K, H in {g.SHAPES}:
+    w = went(lambda: linear(M, K, H, BF16, 0, "rmsnorm_gated_mlp"))
+    assert w[:3] == (4 if M > 64 else -(-M // 16), 1, 1), (M, K, H, w)
+lib.rl_set_tuning(128, 1)
+for M, K, N in {runs}:
+    seen.add(went(lambda: linear(M, K, N)))
+    seen.add(went(lambda: linear(M, K, N, BF16, 0, "rmsnorm_gated_mlp")))
+    seen.add(went(lambda: lib.matmul(P[0], P[2], P[3], M, K, N, BF16, None)))
+print(len(seen))
+""")
+    assert out == ["15"]

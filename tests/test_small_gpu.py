@@ -10,6 +10,19 @@ from util import compare, compare_gated, to_host_f64, upload
 pytestmark = pytest.mark.gpu
 
 
+# (tests/test_routes.py pins the kernel that each of these launches, which the columns and slabs alone do not tell)
+EDGES = [
+    (1, 8, 8, 16), (1, 24, 16, 16), (2, 32, 24, 16), (5, 40, 40, 16), (7, 504, 264, 16), (16, 512, 512, 16), (16, 520, 4096, 16),
+    (17, 480, 136, 16), (32, 1032, 1000, 16), (33, 248, 72, 16), (48, 256, 1016, 16), (49, 264, 2048, 16), (64, 776, 1048, 16),
+    (3, 304, 6472, 32), (16, 544, 5000, 32), (31, 1000, 4968, 32), (57, 768, 6008, 32), (16, 264, 12808, 64), (24, 264, 10248, 64), (64, 264, 12296, 64),
+]
+BLOCKS = [(65, 8, 8, "bf16"), (65, 264, 136, "f16"), (127, 520, 1016, "bf16"), (128, 512, 512, "f16"), (129, 40, 24, "bf16"),
+          (200, 1000, 1016, "bf16"), (320, 256, 2056, "f16"), (512, 264, 520, "bf16"), (66, 1536, 2048, "f16")]
+GATED = [(100, 520, 448, "f16"), (300, 264, 1024, "bf16"), (1, 40, 64, "bf16"), (4, 520, 128, "bf16"), (5, 520, 128, "f16"),
+         (16, 776, 1024, "bf16"), (32, 264, 2112, "f16"), (33, 512, 576, "bf16"),
+         (64, 272, 6400, "f16")]
+
+
 @pytest.fixture(scope="module")
 def rl():
     import torch
@@ -21,17 +34,13 @@ def rl():
 
 
 def small(rl):
-    """Tiles narrower than 128 columns that nobody asked for, unsplit: what the form reports."""
+    """Tiles narrower than 128 columns that nobody asked for, unsplit: what the form reports (and the 64-column tiles in one slab too)."""
     used, cols, slabs, _ = rl.rl_last_launch()
     return used == "skinny" and cols in (16, 32, 64) and slabs == 1
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-@pytest.mark.parametrize("M,K,N,columns", [
-    (1, 8, 8, 16), (1, 24, 16, 16), (2, 32, 24, 16), (5, 40, 40, 16), (7, 504, 264, 16), (16, 512, 512, 16), (16, 520, 4096, 16),
-    (17, 480, 136, 16), (32, 1032, 1000, 16), (33, 248, 72, 16), (48, 256, 1016, 16), (49, 264, 2048, 16), (64, 776, 1048, 16),
-    (3, 304, 6472, 32), (16, 544, 5000, 32), (31, 1000, 4968, 32), (57, 768, 6008, 32), (16, 264, 12808, 64), (24, 264, 10248, 64), (64, 264, 12296, 64),
-])
+@pytest.mark.parametrize("M,K,N,columns", EDGES)
 def test_edges(rl, M, K, N, columns, dtype):
     import torch
     w = workloads.make(M, K, N, dtype, 1e-5, 9100 + K + N)
@@ -54,8 +63,7 @@ def test_edges(rl, M, K, N, columns, dtype):
     assert torch.equal(Y.view(torch.int16), Y2.view(torch.int16))
 
 
-@pytest.mark.parametrize("M,K,N,dtype", [(65, 8, 8, "bf16"), (65, 264, 136, "f16"), (127, 520, 1016, "bf16"), (128, 512, 512, "f16"), (129, 40, 24, "bf16"),
-                                         (200, 1000, 1016, "bf16"), (320, 256, 2056, "f16"), (512, 264, 520, "bf16"), (66, 1536, 2048, "f16")])
+@pytest.mark.parametrize("M,K,N,dtype", BLOCKS)
 def test_row_blocks(rl, M, K, N, dtype):
     import torch
     w = workloads.make(M, K, N, dtype, 1e-5, 9400 + M + N)
@@ -69,8 +77,7 @@ def test_row_blocks(rl, M, K, N, dtype):
 
 
 @pytest.mark.parametrize("interleaved", [False, True])
-@pytest.mark.parametrize("M,K,H,dtype", [(100, 520, 448, "f16"), (300, 264, 1024, "bf16"), (1, 40, 64, "bf16"), (4, 520, 128, "bf16"), (5, 520, 128, "f16"), (16, 776, 1024, "bf16"), (32, 264, 2112, "f16"), (33, 512, 576, "bf16"),
-                                         (64, 272, 6400, "f16")])
+@pytest.mark.parametrize("M,K,H,dtype", GATED)
 def test_gated(rl, M, K, H, dtype, interleaved):
     import torch
     w = workloads.make(M, K, 2 * H, dtype, 1e-5, 9200 + K + H)
