@@ -47,7 +47,7 @@ typedef enum {
     RL_AUTO = 0,          /* pick by shape: fp32: its matrix-core kernel, or the plain kernel for what that one does not run.  K or N not
                              a multiple of 8: RL_NAIVE's form with 128 columns (without room for its partial sums it is not split; the
                              plain kernel for K <= 96 with M N <= 131072, for matmul, and for the gated block, there also with N not a multiple of 16).  Else GEMV
-                             for M = 1 and N < 10240, and for M <= 4 while K N <= 6e6 (K <= 1024 and K N <= 2e6: skinny, but for fp16 with the norm); M <= 64 skinny, and up to M = 1024 while
+                             for M = 1 and N < 10240, and for M <= 4 while K N <= 6e6 (K <= 1024, N <= 16384 and K N <= 2e6: skinny, but for fp16 with the norm and one gated row beyond K = 896); M <= 64 skinny, and up to M = 1024 while
                              ceil(M / 64) K N <= 1.4e8 (0.9e8 for N > 6144 and M > 128); else the two-kernel tile form (above 64 rows also where
                              its 128-row tiles are estimated to be clearly ahead), or the
                              fused tile kernel when the workspace has no room for it.  A shape remembered by rl_autotune is
@@ -56,7 +56,7 @@ typedef enum {
                              workgroups; up to 4 rows W goes through LDS by direct loads, above that through registers */
     RL_MFMA_SKINNY = 2,   /* 16-bit types, matrix cores, 64 rows per workgroup (M <= 1024: a row block per 64 rows in the same
                              launch), K split over the waves of a workgroup and into 1 to 16 slabs over workgroups; 128
-                             columns of W per workgroup, 64 when that leaves half the chip idle.  Where W is small (M <= 64, K <= 2560, and
+                             columns of W per workgroup, 64 when that leaves half the chip idle.  Where W is small (M <= 64, K <= 2560, N <= 16384, and
                              in row blocks of 64 M <= 512, K <= 1536, by estimate) and no shape is asked for, 16, 32 or 64 columns and all of K in one workgroup, without
                              a workspace */
     RL_MFMA_TILE = 3,     /* 16-bit types, large M: 256x256 (or 128x512) output tiles on matrix cores, one fused kernel; K < 2^22,

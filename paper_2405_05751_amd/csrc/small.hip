@@ -21,7 +21,10 @@
 namespace rmsnl {
 
 constexpr int kSmallFlags = 0x00020000;
-constexpr int kSmallMaxK = 2560, kSmallMaxN = 32768;        // of the measurements that the choice rests on
+constexpr int kSmallMaxK = 2560;         // of the measurements that the choice rests on
+// One round of 64-column tiles.  With more, and the short K that is then left by the estimates, the two rounds lose to the one round of the 128-column
+// kernels: 29 x 128 x 17408 6.1 -> 9.15 us, 25 x 24 x 24576 5.7 -> 7.5, and of one row in place of the GEMV kernel 1 x 40 x 18432 3.6 -> 5.4.
+constexpr int kSmallMaxN = 16384;
 constexpr unsigned kSmallOut = 0x80000000u;      // beyond every resource (sizes below 2^31), with any row offset added
 
 template <typename T> struct MfmaSmall;
@@ -236,9 +239,12 @@ static hipError_t small_rows(const Problem& p, int NC, int n_tiles, hipStream_t 
 }
 
 // By a model fitted (log least squares) to 260 shapes at all three widths, M 1 to 64, K 256 to 2600, N to 28672, 10 % rms: launch, rounds of
-// workgroups with their K steps, W from memory, and narrow row segments of two halves.  At 0.88 of the other form's time (skinny_plan's
-// estimate with a constant of the same fit, 8 %) 4 of 215 shapes were slower than with it, by 3 to 15 %, at 0.95 8, and it gives
-// 0.71 of the time over all of them where the faster form each time gives 0.69.
+// workgroups with their K steps, W from memory, and narrow row segments of two halves.  Chosen at 0.88 of the other form's time
+// (skinny_plan's estimate with a constant of the same fit), at 0.84 from K N = 4e6 on and 0.78 at long K, where the other kernel is up to 15 % below
+// its estimate (12 x 2432 x 2008 8.6 us there, 9.75 here; 15 x 2384 x 3208 9.4, 10.6; 32 x 2304 x 1344 10.8, 12.0).  Of 5900 random shapes, K 8 to
+// 2560, N to 32768, both forms timed in graphs, 4271 run here at 0.65 of the time (geometric mean), 2 of them slower by 2 %;
+// over all of them 0.732 of the time, where the faster form each time gives 0.718 (0.88 throughout and N to 32768: 139 slower, by up to half).
+// Of 2500 others that the line was not laid with five are 1 to 5 % slower, 8 x 1664 x 2*968 15 % and 10 x 1408 x 2560 10 %.
 // Rows of W that are a multiple of 512 bytes suit wide tiles (their estimate is 6 % high there) and not narrow ones, the more the longer K is
 // (K = 512 1.0, 1024 1.1, 1536 1.25 of the estimate, whichever XCD takes which line): of 237 such shapes, K 256 to 2048, N 512 to 16384,
 // 22 were 3 to 34 % slower without that in the rule, one by 3 % with it, at 0.73 of the time over all of them (the faster form each time 0.71).
@@ -259,14 +265,16 @@ int small_columns(const Problem& p, double other_us)
         us *= 1. + 1e-3 * p.K * ((whole ? 0.15 : 0.) + (p.gated ? 0.08 : 0.));
         if (cols == 0 || us < best) { best = us; cols = NC; }
     }
-    return other_us == 0. || best < (whole ? 0.82 : 0.88) * other_us ? cols : 0;
+    const double w = double(p.K) * p.N;
+    const double margin = p.K > 1800 && w > 2.6e6 ? 0.78 : whole ? 0.82 : w > 4.0e6 ? 0.84 : 0.88;
+    return other_us == 0. || best < margin * other_us ? cols : 0;
 }
 
 // The same above 64 rows, in row blocks of 64, against what the skinny kernel's row blocks and 128-row tiles take (a fit of its own, 11 % rms
 // on 120 shapes, M 65 to 1024): 10 us and more however small the problem is, 4 to 9 here.  While the narrow tiles are
 // one round of workgroups they take 0.34 to 0.7 of that (141 x 408 x 272 fp16 11.7 -> 4.2 us, 127 x 752 x 552 14.0 -> 5.8,
-// 278 x 824 x 1720 14.8 -> 8.3), with more from 0.97 of it to twice as much.  At 0.75 of the other estimate 56 of the 120 shapes run here,
-// none slower, at 0.71 of the time over all 120 (the faster form each time: 0.66); at 0.8 60, one of them 4 % slower, at 0.9 64, three up to 13 %.
+// 278 x 824 x 1720 14.8 -> 8.3), with more from 0.97 of it to twice as much.  At 0.75 of the other estimate 1178 of 1500 random shapes run here,
+// at 0.55 of the time, none slower (0.93 at most); of the 120, at 0.9 three were slower by up to 13 %.
 // M <= 512, K <= 1536, N <= 12288: beyond, where the other estimate was less sure, no shape was worth it.
 int small_blocks(const Problem& p)
 {
@@ -286,12 +294,13 @@ int small_blocks(const Problem& p)
 }
 
 // Up to four rows where choose_auto would take the GEMV kernel: the narrow tiles are ahead of it on all of 23 shapes with K <= 1024 and
-// K N <= 2e6 (0.5 to 0.91 of the time), level at K = 1500 and behind at 1900, and beyond 2e6 the GEMV kernel streams.  Not the fused
+// K N <= 2e6 (0.5 to 0.91 of the time), level at K = 1500 and behind at 1900, and beyond 2e6 the GEMV kernel streams.  One gated row: level at
+// K = 900 and up to 14 % behind at 1024 (1 x 1024 x 2*320 5.5 us there, 6.3 here).  Of 400 more shapes with N to 16384 none is slower otherwise.  Not the fused
 // block in fp16: the GEMV kernel keeps X (.) g in fp32, whose products leave the range of the two fp16 operands they would have to
 // be here (beyond 65504 an infinity and its opposite; X near 1e-5 1.6e-3 from fp64 in place of 2.1e-4).
 bool small_wins_over_gemv(const Problem& p)
 {
-    return (p.dt == BF16 || !p.fused) && p.M <= 4 && p.K <= 1024 && p.N <= kSmallMaxN && int64_t(p.K) * p.N <= 2000000 && p.n_tile == 0 && p.k_split == 0;
+    return (p.dt == BF16 || !p.fused) && p.M <= 4 && p.K <= (p.gated && p.M == 1 ? 896 : 1024) && p.N <= kSmallMaxN && int64_t(p.K) * p.N <= 2000000 && p.n_tile == 0 && p.k_split == 0;
 }
 
 hipError_t launch_small(const Problem& p, int NC, hipStream_t s)

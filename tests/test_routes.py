@@ -267,7 +267,7 @@ print(linear({M}, {K}, {N}, {dt}, 7, {fn!r}), [n for n in names() if "clear" not
     assert out[0] == "0 0 ['mid_kernel']" and out[1] == f"0 {SPLIT}"
 
 
-@pytest.mark.parametrize("M,K,N", [(1, 8, 16), (1, 1024, 1952), (3, 304, 6472), (4, 1000, 1016), (4, 64, 31248)])
+@pytest.mark.parametrize("M,K,N", [(1, 8, 16), (1, 896, 2232), (2, 1024, 1952), (3, 304, 6472), (4, 1000, 1016), (4, 120, 16384)])
 def test_one_to_four_rows_of_a_small_w(M, K, N):
     """Narrow tiles where they keep what the GEMV kernel has for a product: in bf16 and for the plain product, not with the norm in fp16."""
     out = routes.run(f"""
@@ -278,6 +278,20 @@ print([(lib.matmul(P[0], P[2], P[3], {M}, {K}, {N}, dt, None), names()) for dt i
 """)
     small, gemv = "['small_kernel']", "['gemv_splitk_kernel']"
     assert out == [f"0 {small} 0 {gemv} 0 {small} 0 {gemv}", f"[(0, {small}), (0, {small})]"]
+
+
+@pytest.mark.parametrize("M,K,N,gated,want", [
+    (1, 40, 18432, 0, "gemv_splitk_kernel"), (1, 8, 17152, 1, "gemv_splitk_kernel"), (4, 64, 31248, 0, "gemv_splitk_kernel"),
+    (29, 128, 17408, 1, "skinny_kernel"), (55, 32, 17680, 0, "skinny_kernel"), (5, 96, 21504, 1, "skinny_kernel"), (6, 24, 24320, 0, "skinny_kernel"),
+    (12, 2432, 2008, 0, "skinny_kernel"), (15, 2384, 3208, 0, "skinny_kernel"), (48, 1328, 8872, 0, "skinny_kernel"), (16, 1488, 4032, 1, "skinny_kernel"),
+    (32, 2304, 1344, 0, "skinny_kernel"), (1, 1024, 640, 1, "gemv_splitk_kernel"), (1, 1024, 640, 0, "small_kernel"), (1, 896, 640, 1, "small_kernel"),
+    (55, 32, 16384, 0, "small_kernel"), (1, 40, 16384, 0, "small_kernel"), (15, 1168, 6208, 0, "small_kernel"), (22, 2272, 448, 0, "small_kernel")])
+def test_small_w_where_narrow_tiles_are_slower(M, K, N, gated, want):
+    """More than one round of 64-column tiles, a large W or a long K near the line, one gated row: timed slower in narrow tiles; and sizes beside them."""
+    out = routes.run(f"""
+print(linear({M}, {K}, {N // 2 if gated else N}, BF16, 0, {"rmsnorm_gated_mlp" if gated else "rmsnorm_linear"!r}), [n for n in names() if "clear" not in n])
+""")
+    assert out == [f"0 ['{want}']"]
 
 
 def test_workspace_query_covers_the_gated_block():
