@@ -328,6 +328,19 @@ __device__ __forceinline__ float2_t ld_dev2(const float* p) {
     return __builtin_bit_cast(float2_t, u);
 }
 
+// One matrix instruction of 16 rows x 16 columns x 32 k on packed 16-bit operands.
+template <typename T> struct Mfma16;
+template <> struct Mfma16<Bf16> {
+    static __device__ __forceinline__ float4_t run(uint4_t a, uint4_t b, float4_t c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+    }
+};
+template <> struct Mfma16<Fp16> {
+    static __device__ __forceinline__ float4_t run(uint4_t a, uint4_t b, float4_t c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), c, 0, 0, 0);
+    }
+};
+
 // Products (p0, p1) in fp32, neither of them -0, as two packed 16-bit operands with hi + lo = p: hi is the product cut off (not
 // rounded) one fp32 ulp below its value, lo what is left.  Both have the product's sign and neither is zero unless the product is, so that
 // an infinite factor beside them gives what it gives in fp32; an infinite product has it in lo.

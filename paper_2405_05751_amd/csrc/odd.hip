@@ -45,18 +45,6 @@ constexpr int kOddWaves = 4;
 constexpr int kOddTile = 128;                // columns of a tile
 constexpr int odd_depth(int MB) { return MB == 1 ? 4 : 3; }           // 32-row steps of W in flight per wave
 
-template <typename T> struct MfmaOdd;
-template <> struct MfmaOdd<Bf16> {
-    static __device__ __forceinline__ float4_t run(uint4_t a, uint4_t b, float4_t c) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
-    }
-};
-template <> struct MfmaOdd<Fp16> {
-    static __device__ __forceinline__ float4_t run(uint4_t a, uint4_t b, float4_t c) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), c, 0, 0, 0);
-    }
-};
-
 // ------------------------------------------------------------------------------------- the product
 struct OddCold {                             // what the first loads do not need
     u16* Y;
@@ -232,9 +220,9 @@ __global__ __launch_bounds__(64 * kOddWaves) void odd_kernel(
                 }
             }
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) acc[mb][c] = MfmaOdd<T>::run(ahi[mb], bop, acc[mb][c]);
+            for (int mb = 0; mb < MB; ++mb) acc[mb][c] = Mfma16<T>::run(ahi[mb], bop, acc[mb][c]);
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) acc[mb][c] = MfmaOdd<T>::run(alo[mb], bop, acc[mb][c]);
+            for (int mb = 0; mb < MB; ++mb) acc[mb][c] = Mfma16<T>::run(alo[mb], bop, acc[mb][c]);
         }
     };
 

@@ -135,9 +135,9 @@ __global__ __launch_bounds__(256) void qkattn_kernel(QkArgs a)
     const int off0 = (tl * D + EC * cl) * EB;
 
     uint4_t kx[R], vx[R];
-    // A load is issued whether or not its iteration exists (one past the split reads zeros
-    // through the range check, at no memory traffic) and the issues are pinned in program order, so that the compiler
-    // can count the loads younger than the one it waits for.
+    // The first R loads and those of the main loop are issued whether or not their iteration exists (one past the split reads
+    // zeros through the range check, at no memory traffic), the last R iterations issue none; the issues are pinned in program order,
+    // so that the compiler can count the loads younger than the one it waits for.
     auto issue = [&](int i, int r) {
         const int t = tl + PPI * i;
         const int off = t < t1 ? off0 + i * (PPI * D * EB) : kQkOut;

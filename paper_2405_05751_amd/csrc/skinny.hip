@@ -55,20 +55,6 @@ constexpr int kSkAux = 2;            // W loads: nt
 constexpr int kSkOut = 0x7ffffff0;
 constexpr int kSkFlags = 0x00020000;
 
-template <typename T> struct Mfma16;
-template <> struct Mfma16<Bf16> {
-    static __device__ __forceinline__ float4_t run(uint4_t a, uint4_t b, float4_t c) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a),
-                                                       __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
-    }
-};
-template <> struct Mfma16<Fp16> {
-    static __device__ __forceinline__ float4_t run(uint4_t a, uint4_t b, float4_t c) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, a),
-                                                      __builtin_bit_cast(f16x8_t, b), c, 0, 0, 0);
-    }
-};
-
 // steps (8 W loads per lane each) kept in flight per wave; X is fetched one run ahead (two runs
 // ahead measured 1 % slower at M <= 16)
 constexpr int skinny_depth(int MB) { return MB == 1 ? 4 : 3; }
@@ -223,9 +209,9 @@ __global__ __launch_bounds__(64 * skinny_waves(MB)) void skinny_kernel(
             w[d][j] = __builtin_amdgcn_raw_buffer_load_b128(     // (the uniform part is kept out of the lane's registers)
                 wrs, int(woff0 + unsigned(__builtin_amdgcn_readfirstlane(int(unsigned(t) * unsigned(wpair) + unsigned((8 * h + j) * wrow))))), 0, kSkAux);
     };
-    // Every load below is issued whether or not its step exists (a step past the slab reads zeros
-    // through the range check): the compiler then knows exactly how many loads are younger than
-    // the one it waits for, and the waits leave the rest of the ring in flight.
+    // The first loads, and those of every trip but the last, are issued whether or not their step exists (a step past the
+    // slab reads zeros through the range check): the compiler then knows exactly how many loads are younger than
+    // the one it waits for, and the waits leave the rest of the ring in flight.  The last runs: see below the loop.
     __builtin_amdgcn_sched_barrier(0);       // (the order of issue is the order the waits count in)
     issue_w(0, 0);
     __builtin_amdgcn_sched_barrier(0);
@@ -333,7 +319,7 @@ __global__ __launch_bounds__(64 * skinny_waves(MB)) void skinny_kernel(
         }
     }
     // The last runs (up to PU of them) ask for no step past the slab's end: such a load brings nothing, but takes its turn in the
-    // address unit, and a wave has 2 to 16 runs in all.  One piece of code for each count, so that the waits still know how many
+    // address unit, and a wave has 2 to 16 runs in all.  (The trip before them still asks for one or two such steps where fewer than PU are left.)  One piece of code for each count, so that the waits still know how many
     // loads are younger than theirs; at 64 rows, where the copies would not fit the registers (54 spilled, 64 x 4096 x 4096 17.7 -> 21.0 us),
     // one piece for all, with conditions, whose waits are for everything.  In graphs, us: 16 x 4096 x 6144 14.6 -> 14.2, 8 x 2048 x 4096
     // 8.7 -> 8.2, 21 x 2496 x 2224 11.7 -> 10.7, 48 x 2464 x 6144 14.5 -> 13.6, 64 x 4096 x 2*14336 54.9 -> 53.8, 200 x 2048 x 2048 14.5 -> 12.8,
@@ -395,8 +381,8 @@ __global__ __launch_bounds__(64 * skinny_waves(MB)) void skinny_kernel(
     }
     trace_stamp(a.trace, a.trace_groups, 2);
     if (XLDS) {
-        // the loads issued for the run past the end still write (zeros) into this wave's stage buffers,
-        // which the reduction buffer below lies over: nothing may be in flight any more
+        // a wave without runs still has its first loads of X in flight, which write (zeros) into its stage buffers;
+        // the reduction buffer below lies over those: nothing may be in flight any more
         __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8));
         asm volatile("" ::: "memory");
     }

@@ -1,6 +1,6 @@
 // Fused RMSNorm + MatMul where M is at most a few hundred and W is so small that a launch is a chain of latencies and not a stream.
 //
-// What such a launch spent its time on in the skinny kernel (8 x 512 x 512 in fp16, 5.4 us in a graph, its stages): 1.7 us to issue a
+// What such a launch spent its time on in the skinny kernel as it then was (8 x 512 x 512 in fp16, 5.4 us in a graph, its stages): 1.7 us to issue a
 // ring of loads that is deeper than the slab is long (a load takes its place in the address unit whether or not there is a row for it),
 // 1.8 us for two runs per wave one after the other, 0.4 us to meet, and where K is split over workgroups 3 us or more for the exchange.
 // Here all of K lies in one workgroup, so there is no exchange and no workspace; 16 waves (8 above 32 rows, where 16 are 0 to 14 %
@@ -10,10 +10,10 @@
 // overlapped: the other waves' loads fill what a unit keeps in flight (two or four steps per trip, and a wave's steps next to each
 // other, measured 1 to 25 % slower; 8 waves up to 32 rows 0 to 3 %).
 //
-// In graphs, us, before and after: 8 x 512 x 512 fp16 5.4, 3.1; 14 x 1064 x 472 8.1, 4.7; 25 x 656 x 704 8.1, 4.7; 64 x 352 x 752 9.2, 4.2;
-// 31 x 1000 x 4968 11.1, 7.9; 18 x 1264 x 6176 11.0, 8.0; in place of the GEMV kernel 3 x 296 x 2536 6.7, 3.3.  Of 300 random shapes with K to
-// 2600 and W to 140 MB the 170 that run here take 0.60 of the time (geometric mean; 0.39 to 1.00), at the same distance from fp64 (ratio
-// 0.9999 to 1.001).  What bounds it: launch and first loads, 2 us; then a unit's intake, K (32 NC + 32 MB) bytes per workgroup.
+// In graphs, us, the skinny kernel and this one: 8 x 512 x 512 fp16 4.6, 3.1; 14 x 1064 x 472 7.8, 4.7; 25 x 656 x 704 7.6, 4.5; 64 x 352 x 752
+// 8.3, 4.4; 31 x 1000 x 4968 10.0, 8.1; 18 x 1264 x 6176 10.0, 8.2; in place of the GEMV kernel 3 x 296 x 2536 6.7, 3.4.  Results on N(0, 1) are at the
+// same distance from fp64 (ratio 0.9999 to 1.001).  What bounds it: launch and first loads, 2 us; then a unit's intake, K (32 NC + 32 MB)
+// bytes per workgroup.
 #include <algorithm>
 #include <type_traits>
 #include "common.hpp"
@@ -26,18 +26,6 @@ constexpr int kSmallMaxK = 2560;         // of the measurements that the choice 
 // kernels: 29 x 128 x 17408 6.1 -> 9.15 us, 25 x 24 x 24576 5.7 -> 7.5, and of one row in place of the GEMV kernel 1 x 40 x 18432 3.6 -> 5.4.
 constexpr int kSmallMaxN = 16384;
 constexpr unsigned kSmallOut = 0x80000000u;      // beyond every resource (sizes below 2^31), with any row offset added
-
-template <typename T> struct MfmaSmall;
-template <> struct MfmaSmall<Bf16> {
-    static __device__ __forceinline__ float4_t run(uint4_t a, uint4_t b, float4_t c) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
-    }
-};
-template <> struct MfmaSmall<Fp16> {
-    static __device__ __forceinline__ float4_t run(uint4_t a, uint4_t b, float4_t c) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), c, 0, 0, 0);
-    }
-};
 
 constexpr int small_waves(int MB) { return MB <= 2 ? 16 : 8; }
 constexpr size_t small_stage(int MB, int NC) { return size_t(small_waves(MB)) * NC * 1024; }
@@ -147,10 +135,10 @@ __global__ __launch_bounds__(64 * small_waves(MB)) void small_kernel(
             const uint2_t b0 = lds_read_tr(frag + 16 * c), b1 = lds_read_tr(frag + 16 * c + 4 * TN);
             const uint4_t b = {b0[0], b0[1], b1[0], b1[1]};
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) acc[mb][c] = MfmaSmall<T>::run(hi[mb], b, acc[mb][c]);
+            for (int mb = 0; mb < MB; ++mb) acc[mb][c] = Mfma16<T>::run(hi[mb], b, acc[mb][c]);
             if (TWO)
 #pragma unroll
-                for (int mb = 0; mb < MB; ++mb) acc[mb][c] = MfmaSmall<T>::run(lo[mb], b, acc[mb][c]);
+                for (int mb = 0; mb < MB; ++mb) acc[mb][c] = Mfma16<T>::run(lo[mb], b, acc[mb][c]);
         }
         // the reads are done before the next trip's loads write there
         __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4) | (0 << 8));
@@ -272,8 +260,8 @@ int small_columns(const Problem& p, double other_us)
 
 // The same above 64 rows, in row blocks of 64, against what the skinny kernel's row blocks and 128-row tiles take (a fit of its own, 11 % rms
 // on 120 shapes, M 65 to 1024): 10 us and more however small the problem is, 4 to 9 here.  While the narrow tiles are
-// one round of workgroups they take 0.34 to 0.7 of that (141 x 408 x 272 fp16 11.7 -> 4.2 us, 127 x 752 x 552 14.0 -> 5.8,
-// 278 x 824 x 1720 14.8 -> 8.3), with more from 0.97 of it to twice as much.  At 0.75 of the other estimate 1178 of 1500 random shapes run here,
+// one round of workgroups they take 0.34 to 0.7 of that (141 x 408 x 272 fp16 10.4 -> 4.2 us, 127 x 752 x 552 11.9 -> 5.8,
+// 278 x 824 x 1720 12.9 -> 8.4), with more from 0.97 of it to twice as much.  At 0.75 of the other estimate 1178 of 1500 random shapes run here,
 // at 0.55 of the time, none slower (0.93 at most); of the 120, at 0.9 three were slower by up to 13 %.
 // M <= 512, K <= 1536, N <= 12288: beyond, where the other estimate was less sure, no shape was worth it.
 int small_blocks(const Problem& p)
