@@ -379,7 +379,8 @@ rl_status rl_ff_pairs(const void* X, const void* g, const void* W, void* Y, int6
  * caller-owned DEVICE buffer instead (for the current device; the first 256 KiB must be zero when lent);
  * NULL returns to the library's own buffer.  With a lent buffer too small for a call, the split-K variants
  * return RL_ERR_WORKSPACE; the two-kernel tile form is then skipped by RL_AUTO (the fused tile kernel runs), and
- * the kernel for K or N not a multiple of 8 runs unsplit.
+ * the kernel for K or N not a multiple of 8 runs unsplit.  Where W is small (M <= 4, K <= 1024 and K N <= 2e6, or about what the narrow
+ * tiles of RL_MFMA_SKINNY are for) RL_AUTO takes a form without a split then.
  * rl_workspace_bytes gives the bytes of it that an rmsnorm_linear call of that shape, or a gated block with H = N / 2 in either
  * layout, would like, whichever wants more (0 if none, also where the call has them in its stream's region).
  */

@@ -272,6 +272,18 @@ bool spares_workspace(rl_variant v, const Problem& p)
     return v == kOddSizes || (v == RL_MFMA_TILE_PRE && skinny_row_blocks(p) && skinny_workspace_bytes(p) == 0);
 }
 
+// Does the automatic choice of v, which splits K here, give way to a form without a split where no workspace is to be had?  Where W is
+// small it does: the narrow tiles by the line that they were first chosen by, and up to four rows the GEMV kernel in one slab (for the
+// fused block in fp16 with its fp32 products; 4 x 1000 x 1016 13.4 us in one slab, 7.2 split into eight).  Other splits are refused then.
+bool unsplit_form(rl_variant v, const Problem& p)
+{
+    if (v == RL_GEMV_SPLITK)
+        return p.M <= 4 && p.K <= 1024 && p.N <= 32768 && int64_t(p.K) * p.N <= 2000000 && gemv_workspace_bytes(p) != 0;
+    Problem q = p;
+    q.no_ws = 1;
+    return v == RL_MFMA_SKINNY && p.M <= 64 && skinny_workspace_bytes(p) != 0 && skinny_workspace_bytes(q) == 0;
+}
+
 // one attempt at one variant; hipErrorInvalidValue = the variant cannot run the shape; with *ws_status set, hipErrorOutOfMemory = no
 // workspace because there was no room in the one there is or no memory for one
 // fixed: the one workspace this call may use (nothing is allocated), or null for the library's own or the lent one, or with own
@@ -350,6 +362,7 @@ rl_status run(Problem& p, void* stream, const Workspace* fixed = nullptr, const 
         order[n_order++] = Step{v, 0, 0, spares, false};
         // (in place of row blocks that are split, and so would be refused: mid_plan has the form, if any)
         if (spares || (v == RL_MFMA_TILE_PRE && skinny_row_blocks(p))) order[n_order++] = Step{v, 0, 0, false, true};
+        if (unsplit_form(v, p)) order[n_order++] = Step{v, 0, v == RL_GEMV_SPLITK ? 1 : 0, false, true};
     };
     if (forced != RL_AUTO) {
         order[n_order++] = Step{with_columns(forced, p), p.n_tile, p.k_split, false, false};
@@ -376,10 +389,11 @@ rl_status run(Problem& p, void* stream, const Workspace* fixed = nullptr, const 
         hipError_t e = launch_variant(v, p, s, &why, &ws_status, fixed, fixed_rows, order[i].own);
         if (ws_status != RL_OK) {
             // the two-kernel form is an optimisation: without room for it the fused kernel runs; a
-            // tuned launch shape likewise gives way to the built-in one, and the odd-size kernel to
-            // itself without a split
+            // tuned launch shape likewise gives way to the built-in one, and the odd-size kernel and what a small W
+            // is split by to a form without a split
             if (forced == RL_AUTO && e == hipErrorOutOfMemory &&
-                (v == RL_MFMA_TILE_PRE || v == kOddSizes || (i == 0 && tuned.variant != RL_AUTO))) continue;
+                (v == RL_MFMA_TILE_PRE || v == kOddSizes || (i == 0 && tuned.variant != RL_AUTO) || (i + 1 < n_order && order[i + 1].without)))
+                continue;
             return ws_status;
         }
         if (e == hipSuccess) { tl_last_variant = public_variant(v); return RL_OK; }

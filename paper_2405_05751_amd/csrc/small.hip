@@ -241,7 +241,7 @@ static hipError_t small_rows(const Problem& p, int NC, int n_tiles, hipStream_t 
 // that one, in the unit of this one's, or 0 for none to beat.
 int small_columns(const Problem& p, double other_us)
 {
-    if (p.dt == F32 || p.M > 64 || p.n_tile != 0 || p.k_split != 0 || p.K > kSmallMaxK || p.N > kSmallMaxN) return 0;
+    if (p.dt == F32 || p.M > 64 || p.n_tile != 0 || p.k_split != 0 || p.K > kSmallMaxK || p.N > (p.no_ws ? 2 : 1) * kSmallMaxN) return 0;
     const int MB = (p.M + 15) / 16;
     const bool whole = p.N % 256 == 0;
     double best = 0.;
@@ -254,7 +254,9 @@ int small_columns(const Problem& p, double other_us)
         if (cols == 0 || us < best) { best = us; cols = NC; }
     }
     const double w = double(p.K) * p.N;
-    const double margin = p.K > 1800 && w > 2.6e6 ? 0.78 : whole ? 0.82 : w > 4.0e6 ? 0.84 : 0.88;
+    const double line = whole ? 0.82 : 0.88;
+    // (no_ws: in place of a split that finds no workspace, where the narrow tiles are not much the slower form)
+    const double margin = p.no_ws ? line : p.K > 1800 && w > 2.6e6 ? 0.78 : !whole && w > 4.0e6 ? 0.84 : line;
     return other_us == 0. || best < margin * other_us ? cols : 0;
 }
 

@@ -97,3 +97,23 @@ def test_infinite_weights(rl, M, K, N, dtype, gain):
     g[9] = float("inf")                      # an infinite product of every column
     Y, Z = call(rl, X, g, plain, 1e-5, dtype)
     assert np.isinf(Z).all() and np.array_equal(Y, Z)
+
+
+@pytest.mark.parametrize("M,K,N,dtype,want", [(1, 512, 512, "f16", "gemv"), (4, 1000, 1016, "f16", "gemv"), (3, 1024, 1952, "f16", "gemv"),
+                                              (15, 2384, 3208, "bf16", "skinny"), (32, 2304, 1344, "f16", "skinny")])
+def test_no_room_for_a_split(rl, M, K, N, dtype, want):
+    """A lent buffer with no room for partial sums: a small W runs without a split, and with one again afterwards."""
+    import torch
+    X, g, W = inputs(M, K, N, dtype, 43 + K)
+    lent = torch.zeros((1280 << 10) + 1024, dtype=torch.uint8, device="cuda")
+    rl.rl_set_workspace(lent)
+    try:
+        Y, Z = call(rl, X, g, W, 1e-5, dtype)
+        used = rl.rl_last_launch()
+    finally:
+        rl.rl_set_workspace(None)
+    assert used[0] == want and used[2] == 1
+    close(Y, Z, dtype)
+    Y, Z = call(rl, X, g, W, 1e-5, dtype)
+    assert rl.rl_last_launch()[2] > 1
+    close(Y, Z, dtype)

@@ -294,6 +294,41 @@ print(linear({M}, {K}, {N // 2 if gated else N}, BF16, 0, {"rmsnorm_gated_mlp" i
     assert out == [f"0 ['{want}']"]
 
 
+@pytest.mark.parametrize("why", ["capture", "lent", "memory"])
+def test_small_w_without_a_workspace(why):
+    """Where W is small a call that would be split over K runs unsplit when no workspace is to be had: the GEMV kernel in one slab up to
+    four rows (with the norm in fp16 as with one), the narrow tiles near their line.  Other splits are refused."""
+    out = routes.run(f"""
+import math, random
+why = {why!r}
+lib.rmsnorm_gated_mlp_interleaved.argtypes = [V, V, V, F, V, L, L, L, I, V]
+def none(on):
+    if why == "capture": rec.rec_capture(V(7), int(on))
+    elif why == "lent": lib.rl_set_workspace(V(1 << 43) if on else None, (1280 << 10) + 16)
+    else: rec.rec_fail_mallocs(100000 if on else 0)
+def call(M, K, N, dt, fn="rmsnorm_linear"):
+    st = linear(M, K, N if fn == "rmsnorm_linear" else N // 2, dt, 7, fn)
+    return st, [n for n in names() if "clear" not in n], last()[2]
+r = random.Random(8)
+spread = lambda lo, hi: int(math.exp(r.uniform(math.log(lo), math.log(hi))))
+none(True)
+for n in range(600):
+    K = 8 * spread(1, 128)
+    M, N, dt = r.randint(1, 4), 16 * spread(1, max(1, min(2048, 2000000 // K // 16))), r.choice((F16, BF16))
+    fn = r.choice(("rmsnorm_linear", "rmsnorm_gated_mlp"))
+    st, ks, slabs = call(M, K, N, dt, fn)
+    assert st == 0 and ks in (["gemv_splitk_kernel"], ["small_kernel"], ["skinny_kernel"]) and slabs == 1, (M, K, N, dt, fn, st, ks, slabs)
+    assert dt == BF16 or (M == 1 and N >= 10240) or ks == ["gemv_splitk_kernel"], (M, K, N, fn, ks)
+for M, K, N, fn in ((15, 2384, 3208, "rmsnorm_linear"), (32, 2304, 1344, "rmsnorm_linear"), (16, 1488, 4032, "rmsnorm_gated_mlp")):
+    print(call(M, K, N, BF16, fn)[:2])
+print([call(*s)[:2] for s in ((16, 4096, 6144, BF16), (4, 1504, 1000, F16), (1, 4096, 4096, BF16))])
+none(False)
+print([call(15, 2384, 3208, BF16)[1], call(4, 1000, 1016, F16)[1:]])
+""")
+    bad = 3 if why == "memory" else 4
+    assert out == ["(0, ['small_kernel'])"] * 3 + [f"[({bad}, []), ({bad}, []), ({bad}, [])]", "[['skinny_kernel'], (['gemv_splitk_kernel'], 8)]"]
+
+
 def test_workspace_query_covers_the_gated_block():
     """What rl_workspace_bytes says of (M, K, N) holds for the plain call and for the gated block with H = N / 2 in both layouts: 0 only
     if none takes partial sums (or X-hat) through the shared workspace, else enough for each to launch what it would with any amount."""
